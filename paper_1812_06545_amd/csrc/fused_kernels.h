@@ -219,6 +219,10 @@ __device__ __forceinline__ ArithF32::Acc pair_swap(const ArithF32::Acc &v)
 {
     return ArithF32::Acc{pair_swap(v.P), pair_swap(v.Q)};
 }
+__device__ __forceinline__ ArithF64::Acc pair_swap(const ArithF64::Acc &v)
+{
+    return ArithF64::Acc{pair_swap(v.P), pair_swap(v.Q)};
+}
 
 // Value of lane ^ 16: the sibling quarter of a layered row, whose four
 // quarters sit in lanes l, l + 16, l + 32 and l + 48 (l < 16).
@@ -226,17 +230,20 @@ __device__ __forceinline__ uint32_t quad_swap(uint32_t v)
 {
     return static_cast<uint32_t>(__shfl_xor(static_cast<int>(v), 16));
 }
-__device__ __forceinline__ double quad_swap(double v) { return __shfl_xor(v, 16); }
 __device__ __forceinline__ ArithF32::Acc quad_swap(const ArithF32::Acc &v)
 {
     return ArithF32::Acc{__shfl_xor(v.P, 16), __shfl_xor(v.Q, 16)};
+}
+__device__ __forceinline__ ArithF64::Acc quad_swap(const ArithF64::Acc &v)
+{
+    return ArithF64::Acc{__shfl_xor(v.P, 16), __shfl_xor(v.Q, 16)};
 }
 
 // One half of a check row, run-time length dh <= D, as the straight-line
 // body of length D: this lane owns dh edges of the row (the first half, or
 // the second), its partner lane the other half.  Slots j >= dh are
 // dummies: they enter as q = +inf, whose terms are the exact identity of the
-// combination (t = 1, u = 0 in FP32; phi = 0 in FP64) with a + sign; they
+// combination (t = 1, u = 0) with a + sign; they
 // read the +inf posterior word and this thread's dummy slot, and write only
 // to the dummy slot.  All of the half row's offsets and loads are issued
 // before its arithmetic.  The forward pass parks (part of) a_k in the edge's
