@@ -204,8 +204,8 @@ typedef struct {
 } ldpc_job;
 
 /*
- * Workspace for ldpc_decode_batch over these jobs (all of one dtype): the job
- * tables of its persistent launches (Section III-A), and the streaming
+ * Workspace for ldpc_decode_batch over these jobs (all of one dtype): the item
+ * counters of its launches (Section III-A), 4 KiB for each, and the streaming
  * workspace of the largest job that takes the plain path.
  */
 ldpc_status ldpc_batch_workspace_bytes(const ldpc_job *jobs, int32_t njobs, ldpc_dtype dtype, size_t *bytes);
@@ -216,8 +216,9 @@ ldpc_status ldpc_batch_workspace_bytes(const ldpc_job *jobs, int32_t njobs, ldpc
  * for many frames at once, a workgroup per frame here; Section III-C: work
  * from several sources kept in flight together, here in one launch).
  * Jobs whose code fits the fused frame-resident kernel (messages of one
- * frame held in LDS) run together in ONE persistent launch whose workgroups
- * pull (job, frame) items from a device-side queue; each workgroup runs every
+ * frame held in LDS) run together in ONE launch: one workgroup per (job, frame)
+ * item, or, for more items than the device holds workgroups at once, resident
+ * workgroups that draw items from a device-side queue.  A workgroup runs every
  * iteration of its frame, with per-frame early stop, on the schedule its job's
  * flags select (flooding or LDPC_LAYERED: block-rows, or the code's layers,
  * one at a time with a workgroup barrier between them).  Jobs whose code
@@ -233,9 +234,9 @@ ldpc_status ldpc_decode_batch(const ldpc_job *jobs, int32_t njobs, ldpc_dtype dt
  * ldpc_decode_batch for callers that cannot allocate device memory: code
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * allocation.  Same jobs, results (bit for bit) and errors as
- * ldpc_decode_batch, without a workspace: the batch tables and work counters
+ * ldpc_decode_batch, without a workspace: the item counters
  * live in a static device array of the library (LDPC_NOALLOC_MAX_GROUPS
- * slices of about 4 KiB each, about 64 KiB, held on every device the call
+ * slices of 4 KiB each, 64 KiB, held on every device the call
  * runs on until the process ends).  The call allocates nothing, on the
  * device or the host, and creates no events (ldpc_profile_* does not time
  * it).  Every job's code must fit the fused kernel (ldpc_batch_fits_fused)
@@ -245,9 +246,8 @@ ldpc_status ldpc_decode_batch(const ldpc_job *jobs, int32_t njobs, ldpc_dtype dt
  * otherwise LDPC_EUNSUPPORTED and nothing is enqueued.  The array is shared
  * by every call on a device: calls whose work overlaps on one device
  * (different streams, or threads) race on it and must be serialised by the
- * caller, e.g. by using one stream.  Each launch rewrites its slice (table
- * and counter) with a kernel before using it, so nothing must be cleared
- * between calls.
+ * caller, e.g. by using one stream.  A launch that uses its slice clears it
+ * with a kernel first, so nothing must be cleared between calls.
  */
 #define LDPC_NOALLOC_MAX_GROUPS 16
 ldpc_status ldpc_decode_batch_noalloc(const ldpc_job *jobs, int32_t njobs, ldpc_dtype dtype, void *stream);

@@ -2,10 +2,10 @@
 //
 // Jobs whose code fits the fused frame-resident kernel (row degree <= 32 and
 // one frame's messages within the LDS of one workgroup) are packed into as
-// few persistent launches as the kernel-argument table allows (<= 24 jobs and
+// few launches as the kernel-argument table allows (<= 24 jobs and
 // <= 16 distinct codes per launch); the others run through the plain
-// per-iteration path on the same stream.  The batch table of each launch is
-// written on the device by a tiny kernel that receives it by value.
+// per-iteration path on the same stream.  A launch's job table is a kernel
+// argument.
 #include <algorithm>
 #include <chrono>
 #include <cstdio>
@@ -293,21 +293,12 @@ int plan(const ldpc_job *jobs, int32_t njobs, ldpc_dtype dt, const LaunchCfg &cf
     return ng;
 }
 
-constexpr size_t kGroupBytes = (sizeof(fused::Batch) + 255) / 256 * 256 + 256;
+// Workspace bytes of one fused launch: its item counter (its job table is a
+// kernel argument).  Callers have sized their workspaces by this figure, from
+// when it held the table too, and the entry points keep requiring it.
+constexpr size_t kGroupBytes = 4096;
 
-// Writes a launch's batch table (passed by value as the kernel argument, so
-// nothing on the host must outlive the call, and the launch sequence can be
-// captured in a graph) and resets the launch's work counter.
-__global__ __launch_bounds__(256) void k_store_batch(fused::Batch b, fused::Batch *__restrict__ dst,
-                                                     unsigned long long *counter)
-{
-    const int32_t *src = reinterpret_cast<const int32_t *>(&b);
-    int32_t *out = reinterpret_cast<int32_t *>(dst);
-    for (int w = threadIdx.x; w < static_cast<int>(sizeof(fused::Batch) / sizeof(int32_t)); w += blockDim.x)
-        out[w] = src[w];
-    if (threadIdx.x == 0)
-        *counter = 0ull;
-}
+__global__ void k_zero_counter(uint32_t *counter) { *counter = 0u; }
 
 ldpc_status validate_jobs(const ldpc_job *jobs, int32_t njobs, ldpc_dtype dtype)
 {
@@ -367,9 +358,8 @@ fused::Code code_entry(const ldpc_code_s *c, size_t tsize)
     return e;
 }
 
-// Writes group g's batch table into ws (kGroupBytes: the table, then the
-// work counter in its last 256 bytes) with a kernel, and launches the fused
-// kernel on it.  profile: as launch_fused_bucket.
+// Launches the fused kernel on group g's jobs; ws: kGroupBytes of its own.
+// profile: as launch_fused_bucket.
 template <class A>
 ldpc_status launch_group(const ldpc_job *jobs, const Group &g, char *ws, int threads, hipStream_t s, bool profile)
 {
@@ -386,9 +376,13 @@ ldpc_status launch_group(const ldpc_job *jobs, const Group &g, char *ws, int thr
         b.mb_max = std::max(b.mb_max, b.codes[k].mb);
         nblocks_max = std::max(nblocks_max, b.codes[k].nblocks);
     }
-    int64_t items = 0;
+    int32_t items = 0;  // at most kMaxJobs x LDPC_MAX_FRAMES, below 2^29
     const int fpw = g.fpw;
-    for (int32_t k = 0; k < g.njobs; ++k) {
+    for (int32_t k = 0; k < fused::kMaxJobs; ++k) {
+        if (k >= g.njobs) {
+            b.begin[k] = INT32_MAX;
+            continue;
+        }
         const ldpc_job &j = jobs[g.jobs[k]];
         fused::Job &e = b.jobs[k];
         e.code = g.code_index(j.code);
@@ -397,30 +391,25 @@ ldpc_status launch_group(const ldpc_job *jobs, const Group &g, char *ws, int thr
         e.flags = j.flags;
         e.ms_scale = j.ms_scale;
         e.ms_offset = j.ms_offset;
-        e.item_begin = items;
         e.llr = j.llr;
         e.bits = j.bits;
         e.iters = j.iters;
         e.post = j.posterior;
+        b.begin[k] = items;
         items += (j.frames + fpw - 1) / fpw;  // one item per frame, or per pair of frames
     }
     b.nitems = items;
     const size_t lds = fused::frame_lds_bytes(b.emax, b.nmax, b.words_max, nblocks_max, b.mb_max,
                                               sizeof(typename A::T), fpw);
-    auto *d_batch = reinterpret_cast<fused::Batch *>(ws);
-    auto *counter = reinterpret_cast<unsigned long long *>(ws + kGroupBytes - 256);
-    {
-        ProfScope ps(LDPC_KERNEL_OTHER, s, profile);
-        LDPC_LAUNCH(ps, k_store_batch, dim3(1), dim3(256), 0, s, b, d_batch, counter);
-    }
+    auto *counter = reinterpret_cast<uint32_t *>(ws);
     switch (g.bucket) {
-    case 8: return launch_fused_bucket<A, 8>(b, d_batch, counter, lds, threads, fpw, s, profile);
-    case 16: return launch_fused_bucket<A, 16>(b, d_batch, counter, lds, threads, fpw, s, profile);
+    case 8: return launch_fused_bucket<A, 8>(b, counter, lds, threads, fpw, s, profile);
+    case 16: return launch_fused_bucket<A, 16>(b, counter, lds, threads, fpw, s, profile);
     case 24:
         if constexpr (std::is_same<A, ArithF32>::value)
-            return launch_fused_bucket<A, 24>(b, d_batch, counter, lds, threads, fpw, s, profile);
-        return launch_fused_bucket<A, 32>(b, d_batch, counter, lds, threads, fpw, s, profile);
-    default: return launch_fused_bucket<A, 32>(b, d_batch, counter, lds, threads, fpw, s, profile);
+            return launch_fused_bucket<A, 24>(b, counter, lds, threads, fpw, s, profile);
+        return launch_fused_bucket<A, 32>(b, counter, lds, threads, fpw, s, profile);
+    default: return launch_fused_bucket<A, 32>(b, counter, lds, threads, fpw, s, profile);
     }
 }
 
@@ -428,14 +417,20 @@ ldpc_status launch_group(const ldpc_job *jobs, const Group &g, char *ws, int thr
 
 size_t fused_group_bytes() { return kGroupBytes; }
 
+void launch_zero_counter(uint32_t *counter, hipStream_t s, bool profile)
+{
+    ProfScope ps(LDPC_KERNEL_OTHER, s, profile);
+    LDPC_LAUNCH(ps, k_zero_counter, dim3(1), dim3(1), 0, s, counter);
+}
+
 }  // namespace ldpc
 
-// Scratch memory of ldpc_decode_batch_noalloc: the batch tables and work
-// counters of up to LDPC_NOALLOC_MAX_GROUPS launch groups, one kGroupBytes
-// slice each, as ldpc_decode_batch lays them out in its workspace.  Every
-// device holds its own copy for the life of the process.  Host code never
-// uses this name as an address: it uses the per-device address that
-// hipGetSymbolAddress returns (noalloc_scratch).
+// Scratch memory of ldpc_decode_batch_noalloc: the item counters of up to
+// LDPC_NOALLOC_MAX_GROUPS launch groups, one kGroupBytes slice each, as
+// ldpc_decode_batch lays them out in its workspace.  Every device holds its
+// own copy for the life of the process.  Host code never uses this name as an
+// address: it uses the per-device address that hipGetSymbolAddress returns
+// (noalloc_scratch).
 constexpr size_t kNoallocScratchBytes = static_cast<size_t>(LDPC_NOALLOC_MAX_GROUPS) * ldpc::kGroupBytes;
 static __device__ __align__(256) unsigned char scratch[kNoallocScratchBytes];
 
@@ -565,7 +560,7 @@ try {
     Group groups[LDPC_NOALLOC_MAX_GROUPS];
     const int ng = plan(jobs, njobs, dtype, cfg, groups, LDPC_NOALLOC_MAX_GROUPS, nullptr, nullptr);
     if (ng < 0)
-        return LDPC_EUNSUPPORTED;  // a code too large for the fused kernel, or more groups than the scratch holds
+        return LDPC_EUNSUPPORTED;  // a code too large for the fused kernel, or more groups than the call takes
     if (ng == 0)
         return LDPC_OK;
     char *ws = nullptr;

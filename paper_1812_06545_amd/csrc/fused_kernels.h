@@ -9,10 +9,9 @@
 // and one workgroup owns a whole frame.  HBM traffic per frame is the channel
 // LLRs (read once per iteration, from L2 after the first) and the outputs.
 //
-// Persistent launch: workgroups pull (job, frame) items from a device counter
-// until the queue is empty, so one launch decodes a batch of jobs of
-// different codes, lengths and rates, and a frame that stops early frees its
-// workgroup for the next item.
+// One launch decodes a batch of jobs of different codes, lengths and rates, in
+// items of one (job, frame) each; a frame that stops early frees its workgroup
+// for the next item.
 //
 // Thread mapping: check rows are visited in slot order (for QC codes
 // block-rows sorted by decreasing degree).  A wavefront's 64 rows may differ
@@ -35,6 +34,7 @@
 // the messages of its blocks without any modular arithmetic.
 #pragma once
 
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 #include <vector>
@@ -64,20 +64,33 @@ struct Job {
     int32_t code, frames, max_iter;
     uint32_t flags;
     float ms_scale, ms_offset;  // min-sum correction (LDPC_MIN_SUM), natural LLR units
-    int64_t item_begin;
     const void *llr;
     uint8_t *bits;
     int32_t *iters;
     void *post;
 };
 
+// One launch's jobs, passed to the kernel by value.  Item i (a frame, or in
+// the pair kernel two) belongs to the last job j with begin[j] <= i; the
+// entries past njobs hold INT32_MAX.
 struct Batch {
     int32_t njobs, ncodes;
-    int64_t nitems;
+    int32_t nitems;
     int32_t emax, nmax, words_max, mb_max;
+    int32_t begin[kMaxJobs];
     Code codes[kMaxCodes];
     Job jobs[kMaxJobs];
 };
+static_assert(sizeof(Batch) <= 4096, "a launch's kernel arguments are limited to 4 KiB");
+
+__device__ __forceinline__ int32_t job_of_item(const Batch &b, int32_t item)
+{
+    int32_t j = 0;
+#pragma unroll
+    for (int32_t k = 1; k < kMaxJobs; ++k)
+        j += b.begin[k] <= item;
+    return j;
+}
 
 // One message-sized LDS word per thread (up to 512) after the +inf word: the
 // target of dummy-edge stores, so that a half row's stores need no
@@ -99,7 +112,11 @@ __host__ __device__ inline uint32_t align16(size_t x) { return static_cast<uint3
 //   n                   +inf: dummy edges read their posterior there
 //   n + 1 + t           dummy slot of thread t
 //   r0 ..               messages r, one word per edge
-// and the code's tables (int32 words) follow the last frame, at t0.
+// The workgroup's flags (kFlagWords int32 words, Vote below) follow the last
+// frame, at t0 - 4 kFlagWords, and the code's tables (int32 words) them, at t0.
+// All of a workgroup's LDS is dynamic and starts at address 0 (the kernels
+// have no static LDS), so the offsets above are LDS addresses.
+constexpr int kFlagWords = 4, kItemFlag = 3;  // three vote words, then the workgroup's next item
 struct FrameLayout {
     uint32_t r0, span, t0;
     size_t bytes;
@@ -110,7 +127,7 @@ __host__ __device__ inline FrameLayout frame_layout(int64_t E, int32_t n, int32_
     FrameLayout f;
     f.r0 = align16((static_cast<size_t>(n) + 1 + kDummySlots) * tsize);
     f.span = align16(f.r0 + static_cast<size_t>(E) * tsize);
-    f.t0 = f.span * static_cast<uint32_t>(frames);
+    f.t0 = f.span * static_cast<uint32_t>(frames) + kFlagWords * static_cast<uint32_t>(sizeof(int32_t));
     f.bytes = f.t0 + static_cast<size_t>(words + 2 * nblocks + mb + kColSpare) * sizeof(int32_t);
     return f;
 }
@@ -122,17 +139,51 @@ __host__ __device__ inline size_t frame_lds_bytes(int64_t E, int32_t n, int32_t 
     return frame_layout(E, n, words, nblocks, mb, tsize, frames).bytes;
 }
 
+// LDS is addressed by integers: a workgroup's LDS starts at address 0, and an
+// array symbol for it would be resolved too late for the compiler to fold its
+// address into an access (one addition per slot of every row).
+template <class T>
+using Lds = __attribute__((address_space(3))) T;
+template <class T>
+__device__ __forceinline__ Lds<T> *lds_at(uint32_t addr)
+{
+    return (Lds<T> *)addr;
+}
 // Loads and stores of LDS words by byte offset from the frame's base.
 template <class T>
-__device__ __forceinline__ T lds_ld(const unsigned char *base, uint32_t off)
+__device__ __forceinline__ T lds_ld(uint32_t base, uint32_t off)
 {
-    return *reinterpret_cast<const T *>(base + off);
+    return *lds_at<T>(base + off);
 }
 template <class T>
-__device__ __forceinline__ void lds_st(unsigned char *base, uint32_t off, T v)
+__device__ __forceinline__ void lds_st(uint32_t base, uint32_t off, T v)
 {
-    *reinterpret_cast<T *>(base + off) = v;
+    *lds_at<T>(base + off) = v;
 }
+
+// Workgroup-wide OR at a barrier, through an LDS word per use: any(v) is
+// nonzero on every thread if v was on some thread.  Three words take turns.
+// After the barrier of use u thread 0 clears the word of use u + 2: every
+// thread has read it (for use u - 1) before that barrier, and use u + 2 sets
+// it after the barrier of use u + 1, which thread 0 reaches after the clear.
+// One barrier and one LDS word per use, where __syncthreads_or takes several
+// barriers and 272 bytes of static LDS (which moved every address below by a
+// constant, one more addition per edge).
+struct Vote {
+    Lds<int32_t> *w;  // three words, zero at the start
+    uint32_t k = 0;   // uses so far, mod 3
+    __device__ __forceinline__ int32_t any(uint32_t v)
+    {
+        if (__any(static_cast<int>(v)) && (threadIdx.x & 63) == 0)
+            w[k] = 1;
+        __syncthreads();
+        const int32_t r = w[k];
+        if (threadIdx.x == 0)
+            w[k == 0 ? 2 : k - 1] = 0;
+        k = k == 2 ? 0 : k + 1;
+        return r;
+    }
+};
 
 __device__ __forceinline__ int32_t div_z(int32_t x, uint32_t zmagic)
 {
@@ -153,7 +204,7 @@ struct RowQC {
     uint32_t r_t;          // tsize * r
     uint32_t z_t;          // tsize * Z
     uint32_t base;         // r0 + tsize * Z * (first block of this half)
-    const uint32_t *pack;  // LDS, from this half's first block: (tsize * j * Z) | (tsize * s) << 16
+    const Lds<uint32_t> *pack;  // from this half's first block: (tsize * j * Z) | (tsize * s) << 16
     __device__ __forceinline__ void offsets(int k, uint32_t &ri, uint32_t &ci) const
     {
         const uint32_t w = pack[k];
@@ -254,7 +305,7 @@ __device__ __forceinline__ ArithF64::Acc quad_swap(const ArithF64::Acc &v)
 // TAIL: the caller has checked that every lane of the wave has dh >= D - 1,
 // so only the last slot can be a dummy.
 template <class A, int D, bool PAR, bool TAIL, class Row>
-__device__ __forceinline__ void fused_half_row(const Row &row, int dh, unsigned char *__restrict__ s, Slots sl,
+__device__ __forceinline__ void fused_half_row(const Row &row, int dh, uint32_t s, Slots sl,
                                                uint32_t &parity)
 {
     using T = typename A::T;
@@ -313,7 +364,7 @@ __device__ __forceinline__ void fused_half_row(const Row &row, int dh, unsigned 
 // dummy select but the last.  (With the syndrome the same body measured
 // slower on most codes, so early-stop jobs keep the general one.)
 template <class A, int D, bool PAR, class Row>
-__device__ __forceinline__ void fused_row_exact(const Row &row, int dh, unsigned char *__restrict__ s, Slots sl,
+__device__ __forceinline__ void fused_row_exact(const Row &row, int dh, uint32_t s, Slots sl,
                                                 uint32_t &parity)
 {
     if constexpr (!PAR && D > 1) {
@@ -329,7 +380,7 @@ __device__ __forceinline__ void fused_row_exact(const Row &row, int dh, unsigned
 // FP32 circulant codes, the hot case; one padded body of length DB for FP64
 // and for CSR codes (fewer instantiations, same results).
 template <class A, int D, int DB, bool PAR, class Row>
-__device__ __forceinline__ void fused_row_dispatch(int hwave, const Row &row, int dh, unsigned char *__restrict__ s,
+__device__ __forceinline__ void fused_row_dispatch(int hwave, const Row &row, int dh, uint32_t s,
                                                    Slots sl, uint32_t &parity)
 {
     constexpr bool exact = std::is_same<A, ArithF32>::value && std::is_same<Row, RowQC>::value;
@@ -352,7 +403,7 @@ __device__ __forceinline__ void fused_row_dispatch(int hwave, const Row &row, in
 // between the halves (lane ^ 32), which gives every lane O_i in the same
 // association as the streaming layer kernel.
 template <class A, int D, class Row>
-__device__ __forceinline__ void layered_quarter_row(const Row &row, int dq, unsigned char *__restrict__ s, Slots sl)
+__device__ __forceinline__ void layered_quarter_row(const Row &row, int dq, uint32_t s, Slots sl)
 {
     using T = typename A::T;
     typename A::Acc p[D];
@@ -397,7 +448,7 @@ __device__ __forceinline__ void layered_quarter_row(const Row &row, int dq, unsi
 
 template <class A, int D, int DB, class Row>
 __device__ __forceinline__ void layered_quarter_dispatch(int qwave, const Row &row, int dq,
-                                                         unsigned char *__restrict__ s, Slots sl)
+                                                         uint32_t s, Slots sl)
 {
     constexpr bool exact = std::is_same<A, ArithF32>::value && std::is_same<Row, RowQC>::value;
     if constexpr (!exact) {
@@ -427,7 +478,7 @@ __device__ __forceinline__ void quarter_span(int32_t d, int part, int32_t &k0, i
 // the smallest message).  Flooding folds the parity of the previous decision
 // into `parity` (as fused_half_row); layered writes L = q + r at once.
 template <class A, int D, bool LAYERED, class Row>
-__device__ __forceinline__ void ms_half_row(const Row &row, int k0, int dh, unsigned char *__restrict__ s, Slots sl,
+__device__ __forceinline__ void ms_half_row(const Row &row, int k0, int dh, uint32_t s, Slots sl,
                                             uint32_t &parity, typename A::T scale, typename A::T offset)
 {
     using T = typename A::T;
@@ -480,7 +531,7 @@ __device__ __forceinline__ void ms_half_row(const Row &row, int k0, int dh, unsi
 // read offset 0.  edge(k) is the byte offset of the column's k-th message.
 template <class A, int D, bool SAFE0, bool FULL, class Edge>
 __device__ __forceinline__ typename A::T fused_col(const Edge &edge, int dv, typename A::T acc,
-                                                   const unsigned char *__restrict__ s)
+                                                   uint32_t s)
 {
     using T = typename A::T;
     static_assert(!SAFE0 || D <= kColSpare, "column body longer than the spare words cover");
@@ -496,7 +547,7 @@ __device__ __forceinline__ typename A::T fused_col(const Edge &edge, int dv, typ
 
 template <class A, int D, bool SAFE0, class Edge>
 __device__ __forceinline__ typename A::T fused_col_dispatch(int dwave, const Edge &edge, int dv, typename A::T acc,
-                                                            const unsigned char *__restrict__ s)
+                                                            uint32_t s)
 {
     using T = typename A::T;
     if constexpr (!std::is_same<A, ArithF32>::value) {
@@ -520,9 +571,9 @@ __device__ __forceinline__ typename A::T fused_col_dispatch(int dwave, const Edg
 
 // Places of one frame's data in LDS, for the launch.
 struct FrameView {
-    unsigned char *s;      // the frame's LDS (posteriors at offset 0)
-    uint32_t r0;           // byte offset of the messages
-    const int32_t *tab;    // the code's tables (raw QC tables, then the views below)
+    uint32_t s;               // the frame's LDS address (posteriors at offset 0)
+    uint32_t r0;              // byte offset of the messages
+    const Lds<int32_t> *tab;  // the code's tables (raw QC tables, then the views below)
     Slots slots;
 };
 
@@ -533,7 +584,7 @@ struct FrameView {
 template <class T>
 __device__ __forceinline__ void start_messages(const Code &c, const FrameView &fv)
 {
-    T *sR = reinterpret_cast<T *>(fv.s + fv.r0);
+    Lds<T> *sR = lds_at<T>(fv.s + fv.r0);
     for (int e = static_cast<int>(threadIdx.x); e < c.E; e += static_cast<int>(blockDim.x))
         sR[e] = T(0);
     lds_st<T>(fv.s, fv.slots.dslot, T(0));
@@ -553,20 +604,20 @@ enum Instance { kAnyJob = 0, kFloodQC = 1, kLayeredQC = 2, kMinSumQC = 3 };
 // (no min-sum or CSR rows compiled in); MSQ: every job is min-sum flooding on
 // a circulant view (no sum-product or CSR rows compiled in).
 template <class A, int DB, bool QCF = false, bool MSQ = false>
-__device__ __forceinline__ void decode_frame(const Code &c, const Job &job, int64_t f, const FrameView &fv)
+__device__ __forceinline__ int32_t decode_frame(const Code &c, const Job &job, int64_t f, const FrameView &fv, Vote &vote)
 {
     using T = typename A::T;
     constexpr uint32_t TS = sizeof(T);
     const int tid = static_cast<int>(threadIdx.x), NT = static_cast<int>(blockDim.x);
     const int32_t m = c.m, n = c.n, Z = c.Z;
     const T *llr = static_cast<const T *>(job.llr) + f * n;
-    unsigned char *s = fv.s;
-    T *sL = reinterpret_cast<T *>(s);
-    const int32_t *rbs = fv.tab;
-    const int32_t *cbs = fv.tab + (c.mb + 1) + 2 * c.nblocks;
-    const uint32_t *pack = reinterpret_cast<const uint32_t *>(fv.tab + c.words);
-    const int32_t *border = fv.tab + c.words + c.nblocks;
-    const uint32_t *cpack = reinterpret_cast<const uint32_t *>(border + c.mb);
+    const uint32_t s = fv.s;
+    Lds<T> *sL = lds_at<T>(s);
+    const Lds<int32_t> *rbs = fv.tab;
+    const Lds<int32_t> *cbs = fv.tab + (c.mb + 1) + 2 * c.nblocks;
+    const Lds<uint32_t> *pack = reinterpret_cast<const Lds<uint32_t> *>(fv.tab + c.words);
+    const Lds<int32_t> *border = fv.tab + c.words + c.nblocks;
+    const Lds<uint32_t> *cpack = reinterpret_cast<const Lds<uint32_t> *>(border + c.mb);
     const uint32_t z_t = TS * static_cast<uint32_t>(Z);
 
     for (int j = tid; j < n; j += NT)
@@ -630,7 +681,7 @@ __device__ __forceinline__ void decode_frame(const Code &c, const Job &job, int6
         // The syndrome of x^(t-1) is formed only under early stop (min-sum
         // rows form it always, unused without).
         if (es) {
-            if (!__syncthreads_or(static_cast<int>(parity))) {  // a codeword: stop at t-1, keep L^(t-1)
+            if (!vote.any(parity)) {  // a codeword: stop at t-1, keep L^(t-1)
                 it = t - 1;
                 break;
             }
@@ -656,16 +707,7 @@ __device__ __forceinline__ void decode_frame(const Code &c, const Job &job, int6
         }
         __syncthreads();
     }
-    uint8_t *bits = job.bits + f * n;
-    T *post = job.post ? static_cast<T *>(job.post) + f * n : nullptr;
-    for (int j = tid; j < n; j += NT) {
-        const T v = sL[j];
-        bits[j] = static_cast<uint8_t>(v < T(0));
-        if (post)
-            post[j] = it == 0 ? llr[j] : v * T(A::kOut);
-    }
-    if (tid == 0)
-        job.iters[f] = it;
+    return it;
 }
 
 // One frame under the layered schedule: check rows are visited in ascending
@@ -677,7 +719,8 @@ __device__ __forceinline__ void decode_frame(const Code &c, const Job &job, int6
 // QCL: every job of the launch is sum-product layered on a circulant view
 // (no min-sum or CSR rows compiled in).
 template <class A, int DB, bool QCL = false>
-__device__ __forceinline__ void decode_frame_layered(const Code &c, const Job &job, int64_t f, const FrameView &fv)
+__device__ __forceinline__ int32_t decode_frame_layered(const Code &c, const Job &job, int64_t f,
+                                                        const FrameView &fv, Vote &vote)
 {
     using T = typename A::T;
     constexpr uint32_t TS = sizeof(T);
@@ -685,10 +728,10 @@ __device__ __forceinline__ void decode_frame_layered(const Code &c, const Job &j
     const int lane = tid & 63, half = lane >> 5, wave = tid >> 6, nwaves = NT >> 6;
     const int32_t m = c.m, n = c.n, Z = c.Z;
     const T *llr = static_cast<const T *>(job.llr) + f * n;
-    unsigned char *s = fv.s;
-    T *sL = reinterpret_cast<T *>(s);
-    const int32_t *rbs = fv.tab;
-    const uint32_t *pack = reinterpret_cast<const uint32_t *>(fv.tab + c.words);
+    const uint32_t s = fv.s;
+    Lds<T> *sL = lds_at<T>(s);
+    const Lds<int32_t> *rbs = fv.tab;
+    const Lds<uint32_t> *pack = reinterpret_cast<const Lds<uint32_t> *>(fv.tab + c.words);
     const uint32_t z_t = TS * static_cast<uint32_t>(Z);
 
     for (int j = tid; j < n; j += NT)
@@ -734,7 +777,7 @@ __device__ __forceinline__ void decode_frame_layered(const Code &c, const Job &j
             }
             bad |= par ^ pair_swap(par);
         }
-        return __syncthreads_or(static_cast<int>(bad));
+        return vote.any(bad);
     };
 
     const bool es = (job.flags & LDPC_EARLY_STOP) != 0;
@@ -806,6 +849,19 @@ __device__ __forceinline__ void decode_frame_layered(const Code &c, const Job &j
             }
         }
     }
+    return it;
+}
+
+// Bits, iteration count and posterior of a decoded frame (stopped after `it`
+// iterations; one that ran none reports the caller's LLRs bit-exactly).
+template <class A>
+__device__ __forceinline__ void write_frame(const Code &c, const Job &job, int64_t f, int32_t it, const FrameView &fv)
+{
+    using T = typename A::T;
+    const int tid = static_cast<int>(threadIdx.x), NT = static_cast<int>(blockDim.x);
+    const int32_t n = c.n;
+    const Lds<T> *sL = lds_at<T>(fv.s);
+    const T *llr = static_cast<const T *>(job.llr) + f * n;
     uint8_t *bits = job.bits + f * n;
     T *post = job.post ? static_cast<T *>(job.post) + f * n : nullptr;
     for (int j = tid; j < n; j += NT) {
@@ -823,7 +879,7 @@ __device__ __forceinline__ void decode_frame_layered(const Code &c, const Job &j
 // offsets from a frame's base) and the spare zero words.  Ends with a
 // workgroup barrier.
 template <uint32_t TS>
-__device__ __forceinline__ void load_tables(const Code &c, int32_t *__restrict__ sTab, uint32_t r0)
+__device__ __forceinline__ void load_tables(const Code &c, Lds<int32_t> *sTab, uint32_t r0)
 {
     for (int w = threadIdx.x; w < c.words; w += blockDim.x)
         sTab[w] = c.tab[w];
@@ -855,8 +911,8 @@ __device__ __forceinline__ void load_tables(const Code &c, int32_t *__restrict__
 
 // fused_half_row for frames at s0 and s1 (see there).
 template <class A, int D, class Row>
-__device__ __forceinline__ void fused_half_row2(const Row &row, int dh, unsigned char *__restrict__ s0,
-                                                unsigned char *__restrict__ s1, Slots sl, uint32_t &parity0,
+__device__ __forceinline__ void fused_half_row2(const Row &row, int dh, uint32_t s0,
+                                                uint32_t s1, Slots sl, uint32_t &parity0,
                                                 uint32_t &parity1)
 {
     using T = typename A::T;
@@ -914,8 +970,8 @@ __device__ __forceinline__ void fused_half_row2(const Row &row, int dh, unsigned
 }
 
 template <class A, int D, int DB, class Row>
-__device__ __forceinline__ void fused_row_dispatch2(int hwave, const Row &row, int dh, unsigned char *__restrict__ s0,
-                                                    unsigned char *__restrict__ s1, Slots sl, uint32_t &parity0,
+__device__ __forceinline__ void fused_row_dispatch2(int hwave, const Row &row, int dh, uint32_t s0,
+                                                    uint32_t s1, Slots sl, uint32_t &parity0,
                                                     uint32_t &parity1)
 {
     constexpr bool exact = std::is_same<Row, RowQC>::value;
@@ -934,7 +990,7 @@ __device__ __forceinline__ void fused_row_dispatch2(int hwave, const Row &row, i
 // fused_col for frames at s0 and s1.
 template <class A, int D, bool SAFE0, class Edge>
 __device__ __forceinline__ void fused_col2(const Edge &edge, int dv, typename A::T &acc0, typename A::T &acc1,
-                                           const unsigned char *__restrict__ s0, const unsigned char *__restrict__ s1)
+                                           uint32_t s0, uint32_t s1)
 {
     using T = typename A::T;
     static_assert(!SAFE0 || D <= kColSpare, "column body longer than the spare words cover");
@@ -954,8 +1010,8 @@ __device__ __forceinline__ void fused_col2(const Edge &edge, int dv, typename A:
 
 template <class A, int D, bool SAFE0, class Edge>
 __device__ __forceinline__ void fused_col_dispatch2(int dwave, const Edge &edge, int dv, typename A::T &acc0,
-                                                    typename A::T &acc1, const unsigned char *__restrict__ s0,
-                                                    const unsigned char *__restrict__ s1)
+                                                    typename A::T &acc1, uint32_t s0,
+                                                    uint32_t s1)
 {
     using T = typename A::T;
     if constexpr (SAFE0 && D <= kColSpare) {
@@ -978,7 +1034,7 @@ __device__ __forceinline__ void fused_col_dispatch2(int dwave, const Edge &edge,
 // skipped) and leaves the loop's work to the other frame.
 template <class A, int DB>
 __device__ __forceinline__ void decode_frame_pair(const Code &c, const Job &job, int64_t f0, bool has1,
-                                                  const FrameView &fv0, const FrameView &fv1)
+                                                  const FrameView &fv0, const FrameView &fv1, Vote &vote)
 {
     using T = typename A::T;
     constexpr uint32_t TS = sizeof(T);
@@ -986,13 +1042,13 @@ __device__ __forceinline__ void decode_frame_pair(const Code &c, const Job &job,
     const int32_t m = c.m, n = c.n, Z = c.Z;
     const T *llr0 = static_cast<const T *>(job.llr) + f0 * n;
     const T *llr1 = has1 ? llr0 + n : llr0;
-    unsigned char *s0 = fv0.s, *s1 = fv1.s;
-    T *sL0 = reinterpret_cast<T *>(s0), *sL1 = reinterpret_cast<T *>(s1);
-    const int32_t *rbs = fv0.tab;
-    const int32_t *cbs = fv0.tab + (c.mb + 1) + 2 * c.nblocks;
-    const uint32_t *pack = reinterpret_cast<const uint32_t *>(fv0.tab + c.words);
-    const int32_t *border = fv0.tab + c.words + c.nblocks;
-    const uint32_t *cpack = reinterpret_cast<const uint32_t *>(border + c.mb);
+    const uint32_t s0 = fv0.s, s1 = fv1.s;
+    Lds<T> *sL0 = lds_at<T>(s0), *sL1 = lds_at<T>(s1);
+    const Lds<int32_t> *rbs = fv0.tab;
+    const Lds<int32_t> *cbs = fv0.tab + (c.mb + 1) + 2 * c.nblocks;
+    const Lds<uint32_t> *pack = reinterpret_cast<const Lds<uint32_t> *>(fv0.tab + c.words);
+    const Lds<int32_t> *border = fv0.tab + c.words + c.nblocks;
+    const Lds<uint32_t> *cpack = reinterpret_cast<const Lds<uint32_t> *>(border + c.mb);
     const uint32_t z_t = TS * static_cast<uint32_t>(Z);
 
     for (int j = tid; j < n; j += NT) {
@@ -1031,8 +1087,8 @@ __device__ __forceinline__ void decode_frame_pair(const Code &c, const Job &job,
                 fused_row_dispatch2<A, 1, DB / 2>(hwave, row, dh, s0, s1, fv0.slots, parity0, parity1);
             }
         }
-        const int unsat0 = __syncthreads_or(static_cast<int>(parity0));
-        const int unsat1 = __syncthreads_or(static_cast<int>(parity1));
+        const int unsat0 = vote.any(parity0);
+        const int unsat1 = vote.any(parity1);
         if (es) {  // as decode_frame, per frame: x^(t-1) a codeword -> stop at t-1, keep L^(t-1)
             if (run0 && !unsat0) {
                 it0 = t - 1;
@@ -1087,94 +1143,114 @@ __device__ __forceinline__ void decode_frame_pair(const Code &c, const Job &job,
     }
 }
 
-// Persistent batch kernel over frame pairs: flooding sum-product jobs only,
-// item i of a job being its frames 2i and 2i + 1.  Two frames' LDS (qc1944:
-// 152 KB) allow one 512-thread workgroup per CU, so the bodies may use 256
-// VGPRs (2 waves per SIMD).
+// Workgroup setup shared by the kernels: the +inf word of each frame's region
+// and the flag words (published by the barriers of load_tables).
+template <class T>
+__device__ __forceinline__ Lds<int32_t> *start_workgroup(const FrameLayout &lay, uint32_t nmax, int frames)
+{
+    Lds<int32_t> *flags = lds_at<int32_t>(lay.t0) - kFlagWords;
+    if (threadIdx.x < kFlagWords)
+        flags[threadIdx.x] = 0;
+    if (threadIdx.x == 0)
+        for (int k = 0; k < frames; ++k)
+            lds_at<T>(static_cast<uint32_t>(k) * lay.span)[nmax] = T(__builtin_huge_val());
+    return flags;
+}
+
+// A launch's items are handed out in one of two ways.  Up to as many items as
+// the device holds workgroups at once (counter null): one workgroup each, and
+// the launch, whose job table arrives by value, is the whole call (a kernel
+// that first wrote the table and a counter to memory cost a 64-frame batch 10
+// of its 75 us).  More items: resident workgroups that draw their next item
+// from *counter, which starts at 0.  There the hardware's own dispatch of one
+// workgroup per item is slower where frames run different numbers of
+// iterations, since it deals the items to the XCDs in turn whatever their
+// load (4096 layered frames of n = 1944 with early stop: 1463 against 1358
+// us; a static stride over the items: 2045 us).
+// Workgroup b's first item is b; the next is counted from the grid's end on.
+// Called by all threads; `drawn` is thread 0's draw, issued before the frame's
+// outputs are written, so that the writes cover its latency.
+__device__ __forceinline__ uint32_t draw_item(uint32_t *counter)
+{
+    return counter != nullptr && threadIdx.x == 0 ? atomicAdd(counter, 1u) : 0u;
+}
+__device__ __forceinline__ int32_t next_item(const uint32_t *counter, uint32_t drawn, int32_t nitems,
+                                             Lds<int32_t> *flags)
+{
+    if (counter == nullptr)
+        return nitems;
+    if (threadIdx.x == 0)
+        flags[kItemFlag] = static_cast<int32_t>(min(drawn + gridDim.x, static_cast<uint32_t>(nitems)));
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(flags[kItemFlag]);
+}
+
+// Batch kernel over frame pairs: flooding sum-product jobs only, item i of a
+// job being its frames 2i and 2i + 1.  Two frames' LDS (qc1944: 152 KB) allow
+// one 512-thread workgroup per CU, so the bodies may use 256 VGPRs (2 waves
+// per SIMD).
 template <class A, int DB>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k_fused_pair(const Batch *__restrict__ batch, unsigned long long *counter)
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k_fused_pair(const Batch b, uint32_t *counter)
 {
     using T = typename A::T;
     constexpr uint32_t TS = sizeof(T);
-    extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ long long s_item;
-    const Batch &b = *batch;
     const FrameLayout lay = frame_layout(b.emax, b.nmax, 0, 0, 0, TS, 2);
-    int32_t *sTab = reinterpret_cast<int32_t *>(smem + lay.t0);
+    Lds<int32_t> *sTab = lds_at<int32_t>(lay.t0);
     const uint32_t nmax = static_cast<uint32_t>(b.nmax);
     const Slots slots{TS * (nmax + 1 + threadIdx.x), TS * nmax};
-    const FrameView fv0{smem, lay.r0, sTab, slots}, fv1{smem + lay.span, lay.r0, sTab, slots};
-    if (threadIdx.x == 0) {  // published by the first barrier of the item loop
-        reinterpret_cast<T *>(fv0.s)[nmax] = T(__builtin_huge_val());
-        reinterpret_cast<T *>(fv1.s)[nmax] = T(__builtin_huge_val());
-    }
+    const FrameView fv0{0u, lay.r0, sTab, slots}, fv1{lay.span, lay.r0, sTab, slots};
+    Lds<int32_t> *flags = start_workgroup<T>(lay, nmax, 2);
+    Vote vote{flags};
     int cur_code = -1;
-    for (;;) {
-        if (threadIdx.x == 0)
-            s_item = static_cast<long long>(atomicAdd(counter, 1ull));
-        __syncthreads();
-        const int64_t item = s_item;
-        __syncthreads();
-        if (item >= b.nitems)
-            break;
-        int j = 0;
-        while (j + 1 < b.njobs && b.jobs[j + 1].item_begin <= item)
-            ++j;
+    for (int32_t item = static_cast<int32_t>(blockIdx.x); item < b.nitems;) {
+        const int32_t j = job_of_item(b, item);
         const Job &job = b.jobs[j];
         const Code &c = b.codes[job.code];
         if (job.code != cur_code) {
             cur_code = job.code;
             load_tables<TS>(c, sTab, lay.r0);
         }
-        const int64_t f0 = 2 * (item - job.item_begin);
-        decode_frame_pair<A, DB>(c, job, f0, f0 + 1 < job.frames, fv0, fv1);
-        __syncthreads();
+        const int64_t f0 = 2 * static_cast<int64_t>(item - b.begin[j]);
+        decode_frame_pair<A, DB>(c, job, f0, f0 + 1 < job.frames, fv0, fv1, vote);
+        item = next_item(counter, draw_item(counter), b.nitems, flags);
     }
 }
 
-// Persistent batch kernel: workgroups take (job, frame) items from *counter.
-// 512-thread workgroups, two per CU for n = 1944 (LDS bound): FP32 bodies are
-// held to 128 VGPRs so both fit (4 waves per SIMD); FP64 bodies get 256.
+// Batch kernel.  512-thread workgroups, two per CU for n = 1944 (LDS bound):
+// FP32 bodies are held to 128 VGPRs so both fit (4 waves per SIMD); FP64
+// bodies get 256.
 template <class A>
 constexpr int kFusedWavesPerEU = std::is_same<A, ArithF32>::value ? 4 : 2;
 
 template <class A, int DB, int INST = kAnyJob>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(kFusedWavesPerEU<A>))) void k_fused(const Batch *__restrict__ batch, unsigned long long *counter)
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(kFusedWavesPerEU<A>))) void k_fused(const Batch b, uint32_t *counter)
 {
     using T = typename A::T;
     constexpr uint32_t TS = sizeof(T);
-    extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ long long s_item;
-    const Batch &b = *batch;
     const FrameLayout lay = frame_layout(b.emax, b.nmax, 0, 0, 0, TS);
-    int32_t *sTab = reinterpret_cast<int32_t *>(smem + lay.t0);
+    Lds<int32_t> *sTab = lds_at<int32_t>(lay.t0);
     const uint32_t nmax = static_cast<uint32_t>(b.nmax);
-    const FrameView fv{smem, lay.r0, sTab, Slots{TS * (nmax + 1 + threadIdx.x), TS * nmax}};
-    if (threadIdx.x == 0)  // published by the first barrier of the item loop
-        reinterpret_cast<T *>(smem)[nmax] = T(__builtin_huge_val());
+    const FrameView fv{0u, lay.r0, sTab, Slots{TS * (nmax + 1 + threadIdx.x), TS * nmax}};
+    Lds<int32_t> *flags = start_workgroup<T>(lay, nmax, 1);
+    Vote vote{flags};
     int cur_code = -1;
-    for (;;) {
-        if (threadIdx.x == 0)
-            s_item = static_cast<long long>(atomicAdd(counter, 1ull));
-        __syncthreads();
-        const int64_t item = s_item;
-        __syncthreads();
-        if (item >= b.nitems)
-            break;
-        int j = 0;
-        while (j + 1 < b.njobs && b.jobs[j + 1].item_begin <= item)
-            ++j;
+    for (int32_t item = static_cast<int32_t>(blockIdx.x); item < b.nitems;) {
+        const int32_t j = job_of_item(b, item);
         const Job &job = b.jobs[j];
         const Code &c = b.codes[job.code];
         if (job.code != cur_code) {
             cur_code = job.code;
             load_tables<TS>(c, sTab, lay.r0);
         }
+        const int64_t f = item - b.begin[j];
+        int32_t it;
         if (INST == kLayeredQC || (INST == kAnyJob && (job.flags & LDPC_LAYERED)))
-            decode_frame_layered<A, DB, INST == kLayeredQC>(c, job, item - job.item_begin, fv);
+            it = decode_frame_layered<A, DB, INST == kLayeredQC>(c, job, f, fv, vote);
         else
-            decode_frame<A, DB, INST == kFloodQC, INST == kMinSumQC>(c, job, item - job.item_begin, fv);
-        __syncthreads();
+            it = decode_frame<A, DB, INST == kFloodQC, INST == kMinSumQC>(c, job, f, fv, vote);
+        const uint32_t drawn = draw_item(counter);
+        write_frame<A>(c, job, f, it, fv);
+        item = next_item(counter, drawn, b.nitems, flags);
     }
 }
 
@@ -1271,58 +1347,64 @@ inline ldpc_status launch_shape(const void *fn, size_t lds, int threads, int &pe
 
 }  // namespace fused
 
+// Sets a launch's item counter to 0.
+void launch_zero_counter(uint32_t *counter, hipStream_t s, bool profile);
+
 // Launcher of the fused kernel for codes of row degree <= DB (one
 // translation unit per dtype and bucket).
-// The caller has already written the batch table to d_batch and reset *counter.
 // fpw: frames per workgroup, 1 (k_fused) or 2 (k_fused_pair, FP32 flooding
 // sum-product jobs only; the batch's items are then frame pairs).
+// counter: a device word of the launch's own (its items' queue when they
+// exceed the resident workgroups).
 // profile = false keeps the launch out of ldpc_profile_* timing (whose event
 // pool may create events).
 template <class A, int DB>
-ldpc_status launch_fused_bucket(const fused::Batch &batch, fused::Batch *d_batch, unsigned long long *counter,
-                                size_t lds_bytes, int threads, int fpw, hipStream_t s, bool profile);
+ldpc_status launch_fused_bucket(const fused::Batch &batch, uint32_t *counter, size_t lds_bytes, int threads, int fpw,
+                                hipStream_t s, bool profile);
 
 template <class K>
-ldpc_status launch_fused_kernel(K kern, const fused::Batch &batch, fused::Batch *d_batch, unsigned long long *counter,
-                                size_t lds_bytes, int threads, hipStream_t s, bool profile)
+ldpc_status launch_fused_kernel(K kern, const fused::Batch &batch, uint32_t *counter, size_t lds_bytes, int threads,
+                                hipStream_t s, bool profile)
 {
     int per_cu = 0, cus = 0;
     const ldpc_status shape_rc =
         fused::launch_shape(reinterpret_cast<const void *>(kern), lds_bytes, threads, per_cu, cus);
     if (shape_rc != LDPC_OK)
         return shape_rc;
-    const int64_t grid = std::min<int64_t>(batch.nitems, static_cast<int64_t>(per_cu) * cus);
+    const int32_t resident = per_cu * cus;
+    if (batch.nitems <= resident)
+        counter = nullptr;  // one workgroup per item
+    else
+        launch_zero_counter(counter, s, profile);
     ProfScope ps(LDPC_KERNEL_FUSED, s, profile);
-    LDPC_LAUNCH(ps, kern, dim3(static_cast<unsigned>(grid)), dim3(threads), static_cast<uint32_t>(lds_bytes), s,
-                d_batch, counter);
+    LDPC_LAUNCH(ps, kern, dim3(static_cast<unsigned>(std::min(batch.nitems, resident))), dim3(threads),
+                static_cast<uint32_t>(lds_bytes), s, batch, counter);
     return hipGetLastError() == hipSuccess ? LDPC_OK : LDPC_EDEVICE;
 }
 
 #define LDPC_DEFINE_FUSED_BUCKET(A_, DB_)                                                                        \
     template <>                                                                                                  \
-    ldpc_status launch_fused_bucket<A_, DB_>(const fused::Batch &batch, fused::Batch *d_batch,                  \
-                                             unsigned long long *counter, size_t lds_bytes, int threads,        \
-                                             int fpw, hipStream_t s, bool profile)                               \
+    ldpc_status launch_fused_bucket<A_, DB_>(const fused::Batch &batch, uint32_t *counter, size_t lds_bytes,     \
+                                             int threads, int fpw, hipStream_t s, bool profile)                  \
     {                                                                                                            \
         if constexpr (std::is_same<A_, ArithF32>::value) {                                                       \
             if (fpw == 2)                                                                                        \
-                return launch_fused_kernel(fused::k_fused_pair<A_, DB_>, batch, d_batch, counter, lds_bytes,    \
-                                           threads, s, profile);                                                 \
+                return launch_fused_kernel(fused::k_fused_pair<A_, DB_>, batch, counter, lds_bytes, threads, s,  \
+                                           profile);                                                             \
             const fused::Instance inst_ = fpw == 1 ? fused::batch_instance(batch) : fused::kAnyJob;              \
             if (inst_ == fused::kFloodQC)                                                                        \
-                return launch_fused_kernel(fused::k_fused<A_, DB_, fused::kFloodQC>, batch, d_batch, counter,   \
-                                           lds_bytes, threads, s, profile);                                      \
+                return launch_fused_kernel(fused::k_fused<A_, DB_, fused::kFloodQC>, batch, counter, lds_bytes,  \
+                                           threads, s, profile);                                                 \
             if (inst_ == fused::kLayeredQC)                                                                      \
-                return launch_fused_kernel(fused::k_fused<A_, DB_, fused::kLayeredQC>, batch, d_batch, counter, \
+                return launch_fused_kernel(fused::k_fused<A_, DB_, fused::kLayeredQC>, batch, counter,           \
                                            lds_bytes, threads, s, profile);                                      \
             if (inst_ == fused::kMinSumQC)                                                                       \
-                return launch_fused_kernel(fused::k_fused<A_, DB_, fused::kMinSumQC>, batch, d_batch, counter,  \
-                                           lds_bytes, threads, s, profile);                                      \
+                return launch_fused_kernel(fused::k_fused<A_, DB_, fused::kMinSumQC>, batch, counter, lds_bytes, \
+                                           threads, s, profile);                                                 \
         }                                                                                                        \
         if (fpw != 1)                                                                                            \
             return LDPC_EUNSUPPORTED;                                                                            \
-        return launch_fused_kernel(fused::k_fused<A_, DB_>, batch, d_batch, counter, lds_bytes, threads, s,     \
-                                   profile);                                                                     \
+        return launch_fused_kernel(fused::k_fused<A_, DB_>, batch, counter, lds_bytes, threads, s, profile);     \
     }
 
 }  // namespace ldpc
