@@ -35,7 +35,7 @@ def parse():
     ap.add_argument("--steps", type=int, default=50)
     ap.add_argument("--warmup", type=int, default=20, help="untimed steps first: the GPU clock ramps up over the first ~10 ms of load")
     ap.add_argument("--path", choices=("plain", "batch", "layered"), default="plain",
-                    help="plain: per-iteration kernels (ldpc_decode); batch: ldpc_decode_batch; "
+                    help="plain: ldpc_decode; batch: ldpc_decode_batch; "
                          "layered: ldpc_decode with the layered schedule (10 passes instead of iterations)")
     ap.add_argument("--cpu-seconds", type=float, default=12.0, help="target wall time of the CPU oracle sample")
     ap.add_argument("--no-cpu-baseline", action="store_true")
@@ -180,12 +180,12 @@ def main():
     # Roofline of the dominant kernel.  Algorithmic bytes of one check-node
     # launch over F frames: read r (4E, not on the first iteration), write r
     # (4E), read the posterior once per variable (4n).
-    if args.path == "plain":
+    if args.path == "plain" and prof["check"][1]:
         name, (kms, kcount) = "check", prof["check"]
         per_frame_first = 4 * E + 4 * n
         per_frame_later = 8 * E + 4 * n
         bytes_per_launch = F * (per_frame_first + (T - 1) * per_frame_later) / T
-    elif args.path == "layered":
+    elif args.path == "layered" and prof["check"][1]:
         # one launch per layer; per edge and frame a layer reads r and L and
         # writes both (16 bytes; 12 on the first pass, which reads no r);
         # averaged over the launches of one decode
@@ -200,14 +200,14 @@ def main():
     avg_ms = kms / max(kcount, 1)
     achieved = bytes_per_launch / (avg_ms * 1e-3) / 1e9 if kcount else None
     traffic = None
-    if args.path == "plain" and check_source_hash() == CHECK_TRAFFIC["source_sha256"]:
+    if name == "check" and check_source_hash() == CHECK_TRAFFIC["source_sha256"]:
         traffic = CHECK_TRAFFIC["bytes_per_launch"]
     roofline = {"bound": "hbm", "kernel": name, "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": (achieved / HBM_PEAK_GBS) if achieved else None, "traffic": traffic,
                 "traffic_unit": "bytes per launch", "traffic_profile": CHECK_TRAFFIC["profile"] if traffic else None,
                 "launch_ms": avg_ms, "launches": kcount, "bytes_per_launch": bytes_per_launch,
                 "timed_launches": f"HIP events on every launch of every {args.profile_every}th timed step"}
-    if args.path == "plain" and kcount and check_source_hash() == CHECK_VALU["source_sha256"]:
+    if name == "check" and kcount and check_source_hash() == CHECK_VALU["source_sha256"]:
         insts = CHECK_VALU["insts_per_launch"]
         roofline["valu"] = {"achieved": insts / (avg_ms * 1e-3) / 1e9, "peak": VALU_ISSUE_PEAK / 1e9,
                             "unit": "G wavefront instructions/s", "frac": insts / (avg_ms * 1e-3) / VALU_ISSUE_PEAK,

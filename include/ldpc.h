@@ -156,8 +156,11 @@ ldpc_status ldpc_workspace_bytes(ldpc_code code, ldpc_dtype dtype, int32_t frame
                                  size_t *bytes);
 
 /*
- * Decode `frames` frames with per-iteration kernel launches (the plain
- * path, messages streamed through device memory): flooding runs one
+ * Decode `frames` frames of one code.  A code that fits the frame-resident
+ * kernel (ldpc_batch_fits_fused) is decoded by one launch of it, as a job of
+ * ldpc_decode_batch, where that is the faster route.  Otherwise the call runs
+ * per-iteration kernel launches (the plain path, messages streamed through
+ * device memory; the same outputs bit for bit): flooding runs one
  * check-node and one variable-node kernel per iteration (Section II,
  * Algorithm 1: Loop 2, then Loops 3 and 4; the launch boundary is the
  * two-phase barrier); layered (LDPC_LAYERED; Algorithm 2) one kernel per

@@ -415,6 +415,44 @@ ldpc_status launch_group(const ldpc_job *jobs, const Group &g, char *ws, int thr
 
 }  // namespace
 
+// Whether one frame-resident launch decodes a job of ldpc_decode faster than
+// the streaming kernels (both measured on MI355X, 10 iterations, us; frames 1,
+// 256, 1024).  It does wherever launches or FP64 arithmetic dominate: FP64
+// (qc n = 648: 130, 146, 548 against 335, 472, 1101), the layered schedule
+// (qc n = 1944: 166, 180, 492 against 446, 533, 734), and FP32 flooding while
+// a frame is at most four rounds of a 512-thread workgroup's half rows, m <=
+// 1024 (qc n = 1944: 99, 108, 300 against 102, 188, 429).  Beyond that few
+// frames leave the device idle (qc n = 3840: 175, 191, 718 against 125, 273,
+// 761).  CSR rows differ in degree from lane to lane and run padded, so there
+// the streaming kernels keep rows of many degrees (n = 1999, degrees 2 to 29:
+// 192, 205, 522 against 107, 200, 487) and short rows win to one round, m <=
+// 256 (n = 504, degree 6: 23, 25, 56 against 65, 81, 92).
+static bool fused_faster(const ldpc_job &j, ldpc_dtype dt)
+{
+    const ldpc_code_s *c = j.code;
+    if (dt == LDPC_F64 || (j.flags & LDPC_LAYERED))
+        return true;
+    return c->is_qc ? c->m <= 1024 : c->m <= 256 && c->max_row_deg <= 8;
+}
+
+bool fused_decode(const ldpc_job &job, ldpc_dtype dt, void *ws, hipStream_t stream, ldpc_status *rc)
+{
+    const FusedFit fit = fused_fit(job.code, dt, lds_limit());
+    if (!fit.ok || !fused_faster(job, dt))
+        return false;
+    const LaunchCfg cfg = cfg_for(&job, 1, dt);
+    Group g;
+    g.tsize = dt == LDPC_F64 ? sizeof(double) : sizeof(float);
+    g.jobs[g.njobs++] = 0;
+    g.add_code(job.code);
+    g.bucket = fit.bucket;
+    char *w = static_cast<char *>(ws);
+    const int threads = job_threads(job, dt, cfg.threads);
+    *rc = dt == LDPC_F64 ? launch_group<ArithF64>(&job, g, w, threads, stream, true)
+                         : launch_group<ArithF32>(&job, g, w, threads, stream, true);
+    return true;
+}
+
 size_t fused_group_bytes() { return kGroupBytes; }
 
 void launch_zero_counter(uint32_t *counter, hipStream_t s, bool profile)

@@ -489,6 +489,10 @@ try {
         return LDPC_EINVAL;
     if (!ldpc::code_on_current_device(code))
         return LDPC_EINVAL;
+    const ldpc_job job{code, frames, max_iter, flags, llr, bits, iters, posterior, ms_scale, ms_offset};
+    ldpc_status rc = LDPC_OK;
+    if (ldpc::fused_decode(job, dtype, workspace, static_cast<hipStream_t>(stream), &rc))
+        return rc;
     return ldpc::stream_decode(code, dtype, frames, max_iter, flags, llr, bits, iters, posterior, workspace,
                                static_cast<hipStream_t>(stream), ms_scale, ms_offset);
 } catch (...) {

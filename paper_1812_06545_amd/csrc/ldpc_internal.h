@@ -149,6 +149,12 @@ ldpc_status launch_link_copy16(void *dst, const void *src, size_t bytes, int32_t
 // and work counter).  A batch of J jobs needs at most J such launches.
 size_t fused_group_bytes();
 
+// ldpc_decode's frames as one frame-resident launch, if the code fits that
+// kernel: true, with the call's status in *rc (nothing is left to do), or
+// false, and the streaming path takes the call.  ws: at least 4 bytes of
+// device memory of the call's own.
+bool fused_decode(const ldpc_job &job, ldpc_dtype dt, void *ws, hipStream_t stream, ldpc_status *rc);
+
 // Streaming (per-iteration) path.
 size_t stream_workspace_bytes(const ldpc_code_s *c, ldpc_dtype dt, int32_t frames, int32_t max_iter);
 // ms_scale / ms_offset: the min-sum magnitude correction (used with

@@ -1,0 +1,71 @@
+"""ldpc_decode's two routes, frame-resident and streaming, give the same bits.
+
+A code small enough for the frame-resident kernel is stacked K times along
+the diagonal, K large enough that the stacked code's messages exceed a
+workgroup's LDS: the small code's decode takes the frame-resident kernel, the
+stacked one's the streaming kernels, and each copy's rows, columns and
+message orders are the small code's.  So every copy's outputs must equal the
+small decode's bit for bit (no tolerance: both routes evaluate each message
+with the same operations in the same order).  With early stop every copy
+holds the same frame, so the stacked frame stops where the small one does.
+Frame counts straddle the 64-frame chunks of the streaming layout.
+"""
+import numpy as np
+import pytest
+
+from workloads import codes
+
+pytestmark = pytest.mark.gpu
+
+LDS_WORDS = 160 * 1024 // 4
+
+
+@pytest.fixture(scope="module")
+def L():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1812_06545_amd as lib
+    return lib
+
+
+def _stack(code, K):
+    rows = [int(e) * code.edges for e in range(K)]
+    row_ptr = np.concatenate([code.row_ptr[:-1].astype(np.int64) + r for r in rows] + [[K * code.edges]])
+    col_idx = np.concatenate([code.col_idx.astype(np.int64) + k * code.n for k in range(K)])
+    return codes.Code(K * code.m, K * code.n, row_ptr.astype(np.int32), col_idx.astype(np.int32))
+
+
+CODES = {
+    "qc_z27": lambda: codes.qc_code(12, 24, 27, 31),
+    "qc_z81_r56": lambda: codes.qc_code(4, 24, 81, 32),
+    "gallager": lambda: codes.gallager_regular(240, 3, 6, 33),
+    "rows_2_29": lambda: codes.random_rows(120, 311, 2, 29, 34),
+    "rows_dense_col": lambda: codes.random_rows(70, 190, 1, 16, 35, dense_col=True),
+}
+
+
+@pytest.mark.parametrize("rule", ["spa", "minsum"])
+@pytest.mark.parametrize("layered", [False, True])
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("name", list(CODES))
+def test_routes_agree(L, name, dtype, layered, rule):
+    import torch
+    code = CODES[name]()
+    K = LDS_WORDS // code.edges + 1
+    small, big = L.Code.from_workload(code), L.Code.from_workload(_stack(code, K))
+    td = torch.float32 if dtype == "f32" else torch.float64
+    assert L.ldpc_batch_fits_fused(small, td)[0] and not L.ldpc_batch_fits_fused(big, td)[0]
+    kw = dict(layered=layered, rule=rule, ms_scale=0.8125, ms_offset=0.25)
+    rng = np.random.default_rng(36)
+    for frames, es, iters in ((3, False, 3), (70, True, 7)):
+        print(f"[gpu] routes {name} {dtype} layered={layered} {rule} frames={frames} es={es}", flush=True)
+        x = rng.normal(2.0, 2.2, size=(frames * (1 if es else K), code.n)).astype(np.float32)
+        t = torch.from_numpy(x).cuda().to(td)
+        bits, its, post = L.decode(small, t, iters, early_stop=es, **kw)
+        stacked = t.repeat(1, K) if es else t.reshape(frames, K * code.n)
+        b2, i2, p2 = L.decode(big, stacked.contiguous(), iters, early_stop=es, **kw)
+        if es:
+            assert torch.equal(its, i2)
+            bits, post = bits.repeat(1, K), post.repeat(1, K)
+        assert torch.equal(b2.reshape(bits.shape), bits) and torch.equal(p2.reshape(post.shape), post)
