@@ -158,7 +158,7 @@ ldpc_status ldpc_workspace_bytes(ldpc_code code, ldpc_dtype dtype, int32_t frame
 /*
  * Decode `frames` frames of one code.  A code that fits the frame-resident
  * kernel (ldpc_batch_fits_fused) is decoded by one launch of it, as a job of
- * ldpc_decode_batch, where that is the faster route.  Otherwise the call runs
+ * ldpc_decode_batch.  Otherwise the call runs
  * per-iteration kernel launches (the plain path, messages streamed through
  * device memory; the same outputs bit for bit): flooding runs one
  * check-node and one variable-node kernel per iteration (Section II,
@@ -387,7 +387,8 @@ void ldpc_server_destroy(ldpc_server server);
 /*
  * Workgroup size (a multiple of 64, at most 512) of the fused frame-resident
  * kernel used by ldpc_decode_batch (Section III-A: the threads that decode
- * one frame); default 512.  EINVAL for other values.  Process-wide default
+ * one frame); default 512, which leaves the choice to each launch (128 to
+ * 1024, by its codes and frame counts).  EINVAL for other values.  Process-wide default
  * for jobs whose code has no tuned size (ldpc_autotune_batch records one per
  * code; ldpc_tuning_clear forgets them); affects speed only, never results.
  */
@@ -396,9 +397,8 @@ ldpc_status ldpc_batch_set_threads(int32_t threads);
 /*
  * Frames per workgroup of the fused kernel used by ldpc_decode_batch for FP32
  * flooding sum-product jobs whose code fits two frames in one workgroup's LDS:
- * 1 (default) or 2.  With 2, every thread runs its rows and columns for two
- * frames of a job at once (Section III-A: frames decoded side by side),
- * sharing the offsets and table reads of each edge slot; other jobs keep 1.
+ * 1 (default) or 2.  With 2, a workgroup takes two frames of a job at a time
+ * (Section III-A) and decodes one after the other; other jobs keep 1.
  * Process-wide default (tuned shapes override it); affects speed only, never
  * results.  EINVAL for other values.
  */
@@ -417,9 +417,11 @@ ldpc_status ldpc_batch_launch_config(const ldpc_job *jobs, int32_t njobs, ldpc_d
                                      int32_t *frames_per_group, int32_t *tuned);
 
 /*
- * Workgroup size each job would run with in the fused kernel
+ * Workgroup size each job is given in the fused kernel
  * (threads[njobs], caller-allocated; 0 for a job with no frames or one that
- * runs on the plain path).  Jobs of different sizes run as separate fused
+ * runs on the plain path).  512 leaves the choice to the launch, which picks
+ * a size from 128 to 1024 threads by its codes and frame counts; the others
+ * are taken as they are.  Jobs of different sizes run as separate fused
  * launches on the same stream.  Errors as ldpc_decode_batch's argument
  * checks; EINVAL if threads is NULL with njobs > 0.  (Library bookkeeping of
  * the autotuner, Section III-A's mapping of frames onto the GPU.)
@@ -470,7 +472,7 @@ void ldpc_tuning_clear(void);
  * kernel (Section III-A: one frame per workgroup) on the current device (row degree <= 32, n < 65536 and one frame's
  * messages within one workgroup's LDS).  LDPC_OK if so, LDPC_EUNSUPPORTED if
  * ldpc_decode_batch would route the code through the plain path; *lds_bytes
- * (may be NULL) receives the LDS one frame needs.
+ * (may be NULL) receives the LDS that this rule counts for one frame.
  */
 ldpc_status ldpc_batch_fits_fused(ldpc_code code, ldpc_dtype dtype, size_t *lds_bytes);
 

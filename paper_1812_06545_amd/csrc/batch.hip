@@ -19,8 +19,9 @@
 namespace ldpc {
 namespace {
 
-// Launch configuration of the fused kernel: workgroup size and frames per
-// workgroup (1, or 2 for FP32 flooding sum-product jobs).
+// Launch configuration of the fused kernel: workgroup size (512: the size that
+// fused::workgroup_threads picks) and frames per work item (1, or 2, one after
+// the other, for FP32 flooding sum-product jobs).
 struct LaunchCfg {
     int threads = 512;
     int fpw = 1;
@@ -138,15 +139,28 @@ size_t lds_limit()
     return static_cast<size_t>(bytes);
 }
 
-// Whether the fused kernel uses the circulant view of a QC code in a dtype
-// of tsize bytes: its row tables pack tsize * j * Z and tsize * s into 16-bit
-// fields, and it divides row and column indices by Z with a multiply-high,
-// exact while index * Z < 2^32 (Z >= 2).  Other codes use the CSR view.
+// Whether a QC code is admitted to the fused kernel in a dtype of tsize bytes:
+// the bounds of an earlier layout that packed byte offsets into 16-bit fields.
 bool fused_qc_view(const ldpc_code_s *c, size_t tsize)
 {
     return c->is_qc && c->Z >= 2 && tsize * static_cast<size_t>(c->n) <= 65535 &&
            tsize * static_cast<size_t>(c->Z) <= 65535 &&
            static_cast<uint64_t>(std::max(c->m, c->n)) * static_cast<uint64_t>(c->Z) < (1ull << 32);
+}
+
+// LDS bytes that a workgroup is taken to need for `frames` frames of E
+// messages and n posteriors, a word per thread, and the tables of a circulant
+// code: the rule by which codes are admitted to the frame-resident kernel and
+// packed into launches, and the figure that ldpc_batch_fits_fused reports.
+// A launch's own need (fused::lds_bytes) is less in CSR order, and the padded
+// order is used where it fits.
+size_t fit_bytes(int64_t E, int32_t n, int32_t words, int32_t nblocks, int32_t mb, size_t tsize, int frames = 1)
+{
+    const size_t r0 = align_up((static_cast<size_t>(n) + 1 + 512) * tsize, 16);
+    const size_t span = align_up(r0 + static_cast<size_t>(E) * tsize, 16);
+    return span * static_cast<size_t>(frames) +
+           (static_cast<size_t>(words) + 2 * static_cast<size_t>(nblocks) + static_cast<size_t>(mb) + 16) *
+               sizeof(int32_t);
 }
 
 struct FusedFit {
@@ -165,11 +179,9 @@ FusedFit fused_fit(const ldpc_code_s *c, ldpc_dtype dt, size_t limit)
         r.bucket = d <= 8 ? 8 : d <= 16 ? 16 : d <= 32 ? 32 : 0;
     const size_t tsize = dt == LDPC_F64 ? sizeof(double) : sizeof(float);
     const bool qc = fused_qc_view(c, tsize);
-    // A QC code's fused slot tables list its rows by block-row degree, which
-    // only the circulant view follows: without it the code takes the plain path.
-    if (r.bucket == 0 || c->n >= 65536 || (c->is_qc && !qc))
+    if (r.bucket == 0 || c->fused.row_tab == nullptr || c->n >= 65536 || (c->is_qc && !qc))
         return r;
-    r.lds = fused::frame_lds_bytes(c->E, c->n, qc ? c->qc_words : 0, qc ? c->nblocks : 0, qc ? c->mb : 0, tsize);
+    r.lds = fit_bytes(c->E, c->n, qc ? c->qc_words : 0, qc ? c->nblocks : 0, qc ? c->mb : 0, tsize);
     r.ok = r.lds <= limit;
     return r;
 }
@@ -187,7 +199,7 @@ struct Group {
     int64_t emax = 0;
     int32_t nmax = 0, words = 0, nblocks = 0, mb = 0;
     size_t tsize = 4;
-    size_t lds() const { return fused::frame_lds_bytes(emax, nmax, words, nblocks, mb, tsize, fpw); }
+    size_t lds() const { return fit_bytes(emax, nmax, words, nblocks, mb, tsize, fpw); }
     int code_index(const ldpc_code_s *c) const
     {
         for (int32_t k = 0; k < ncodes; ++k)
@@ -219,7 +231,7 @@ int job_fpw(const ldpc_job &j, ldpc_dtype dt, int fpw_pref, size_t limit)
         return 1;
     const ldpc_code_s *c = j.code;
     const bool qc = fused_qc_view(c, sizeof(float));
-    const size_t two = fused::frame_lds_bytes(c->E, c->n, qc ? c->qc_words : 0, qc ? c->nblocks : 0,
+    const size_t two = fit_bytes(c->E, c->n, qc ? c->qc_words : 0, qc ? c->nblocks : 0,
                                               qc ? c->mb : 0, sizeof(float), 2);
     return two <= limit ? 2 : 1;
 }
@@ -329,32 +341,27 @@ size_t batch_bytes(const ldpc_job *jobs, int ngroups, const int32_t *plain, int3
     return static_cast<size_t>(ngroups) * kGroupBytes + stream;
 }
 
-fused::Code code_entry(const ldpc_code_s *c, size_t tsize)
+// The code's tables for messages of tsize bytes: in the padded slot order if a
+// frame then fits the device's LDS, else in CSR order.
+fused::Code code_entry(const ldpc_code_s *c, size_t tsize, size_t limit)
 {
-    const bool qc = fused_qc_view(c, tsize);
+    const FusedTables &t = c->fused;
+    const bool padded = fused::lds_bytes(c->n, t.slot_words, tsize) <= limit;
     fused::Code e{};
     e.m = c->m;
     e.n = c->n;
     e.E = static_cast<int32_t>(c->E);
-    e.Z = qc ? c->Z : 1;
-    e.nblocks = qc ? c->nblocks : 0;
-    e.mb = qc ? c->mb : 0;
-    e.nb = qc ? c->nb : 0;
-    e.qc = qc ? 1 : 0;
-    e.words = qc ? c->qc_words : 0;
-    e.zmagic = qc ? static_cast<uint32_t>(((1ull << 32) + static_cast<uint64_t>(c->Z) - 1) / static_cast<uint64_t>(c->Z))
-                  : 0u;
-    e.tab = c->qc_tab;
-    e.row_ptr = c->row_ptr;
-    e.col_idx = c->col_idx;
-    e.col_ptr = c->col_ptr;
-    e.col_edge = c->col_edge;
-    e.brow_order = c->brow_order;
-    e.row_gmax = c->row_gmax;
-    e.col_gmax = c->col_gmax;
-    e.layer_ptr = c->d_layer_ptr;
+    e.row_groups = t.row_groups;
     e.nlayers = static_cast<int32_t>(c->layer_dmax.size());
-    e.half_rows = qc ? c->half_rows : nullptr;
+    e.r_words = padded ? t.slot_words : e.E;
+    e.row_grp = padded ? t.row_grp : t.row_grp_x;
+    e.row_tab = padded ? t.row_tab : t.row_tab_x;
+    e.row_pos = padded ? nullptr : t.row_pos_x;
+    e.col_grp = t.col_grp;
+    e.col_tab = padded ? t.col_tab : t.col_tab_x;
+    e.lay_ptr = t.lay_ptr;
+    e.lay_grp = t.lay_grp;
+    e.lay_tab = t.lay_tab;
     return e;
 }
 
@@ -366,16 +373,9 @@ ldpc_status launch_group(const ldpc_job *jobs, const Group &g, char *ws, int thr
     fused::Batch b{};
     b.njobs = g.njobs;
     b.ncodes = g.ncodes;
-    int32_t nblocks_max = 0;
-    for (int32_t k = 0; k < g.ncodes; ++k) {
-        const ldpc_code_s *c = g.codes[k];
-        b.codes[k] = code_entry(c, sizeof(typename A::T));
-        b.emax = std::max<int32_t>(b.emax, static_cast<int32_t>(c->E));
-        b.nmax = std::max(b.nmax, c->n);
-        b.words_max = std::max(b.words_max, b.codes[k].words);
-        b.mb_max = std::max(b.mb_max, b.codes[k].mb);
-        nblocks_max = std::max(nblocks_max, b.codes[k].nblocks);
-    }
+    const size_t limit = lds_limit();
+    for (int32_t k = 0; k < g.ncodes; ++k)
+        b.codes[k] = code_entry(g.codes[k], sizeof(typename A::T), limit);
     int32_t items = 0;  // at most kMaxJobs x LDPC_MAX_FRAMES, below 2^29
     const int fpw = g.fpw;
     for (int32_t k = 0; k < fused::kMaxJobs; ++k) {
@@ -399,46 +399,25 @@ ldpc_status launch_group(const ldpc_job *jobs, const Group &g, char *ws, int thr
         items += (j.frames + fpw - 1) / fpw;  // one item per frame, or per pair of frames
     }
     b.nitems = items;
-    const size_t lds = fused::frame_lds_bytes(b.emax, b.nmax, b.words_max, nblocks_max, b.mb_max,
-                                              sizeof(typename A::T), fpw);
+    b.frames_per_item = fpw;
     auto *counter = reinterpret_cast<uint32_t *>(ws);
     switch (g.bucket) {
-    case 8: return launch_fused_bucket<A, 8>(b, counter, lds, threads, fpw, s, profile);
-    case 16: return launch_fused_bucket<A, 16>(b, counter, lds, threads, fpw, s, profile);
+    case 8: return launch_fused_bucket<A, 8>(b, counter, threads, s, profile);
+    case 16: return launch_fused_bucket<A, 16>(b, counter, threads, s, profile);
     case 24:
         if constexpr (std::is_same<A, ArithF32>::value)
-            return launch_fused_bucket<A, 24>(b, counter, lds, threads, fpw, s, profile);
-        return launch_fused_bucket<A, 32>(b, counter, lds, threads, fpw, s, profile);
-    default: return launch_fused_bucket<A, 32>(b, counter, lds, threads, fpw, s, profile);
+            return launch_fused_bucket<A, 24>(b, counter, threads, s, profile);
+        return launch_fused_bucket<A, 32>(b, counter, threads, s, profile);
+    default: return launch_fused_bucket<A, 32>(b, counter, threads, s, profile);
     }
 }
 
 }  // namespace
 
-// Whether one frame-resident launch decodes a job of ldpc_decode faster than
-// the streaming kernels (both measured on MI355X, 10 iterations, us; frames 1,
-// 256, 1024).  It does wherever launches or FP64 arithmetic dominate: FP64
-// (qc n = 648: 130, 146, 548 against 335, 472, 1101), the layered schedule
-// (qc n = 1944: 166, 180, 492 against 446, 533, 734), and FP32 flooding while
-// a frame is at most four rounds of a 512-thread workgroup's half rows, m <=
-// 1024 (qc n = 1944: 99, 108, 300 against 102, 188, 429).  Beyond that few
-// frames leave the device idle (qc n = 3840: 175, 191, 718 against 125, 273,
-// 761).  CSR rows differ in degree from lane to lane and run padded, so there
-// the streaming kernels keep rows of many degrees (n = 1999, degrees 2 to 29:
-// 192, 205, 522 against 107, 200, 487) and short rows win to one round, m <=
-// 256 (n = 504, degree 6: 23, 25, 56 against 65, 81, 92).
-static bool fused_faster(const ldpc_job &j, ldpc_dtype dt)
-{
-    const ldpc_code_s *c = j.code;
-    if (dt == LDPC_F64 || (j.flags & LDPC_LAYERED))
-        return true;
-    return c->is_qc ? c->m <= 1024 : c->m <= 256 && c->max_row_deg <= 8;
-}
-
 bool fused_decode(const ldpc_job &job, ldpc_dtype dt, void *ws, hipStream_t stream, ldpc_status *rc)
 {
     const FusedFit fit = fused_fit(job.code, dt, lds_limit());
-    if (!fit.ok || !fused_faster(job, dt))
+    if (!fit.ok)
         return false;
     const LaunchCfg cfg = cfg_for(&job, 1, dt);
     Group g;

@@ -72,61 +72,6 @@ ldpc_status build_host_layout(int32_t m, int32_t n, const int32_t *row_ptr, cons
     return LDPC_OK;
 }
 
-// Slot tables of the fused kernel (see ldpc_code_s).  brow_order is empty
-// for codes without a circulant-block structure.
-void slot_tables(const HostLayout &h, const std::vector<int32_t> &row_blk_start, int32_t Z,
-                 std::vector<int32_t> &brow_order, std::vector<int32_t> &row_gmax, std::vector<int32_t> &col_gmax)
-{
-    std::vector<int32_t> row_deg(h.m);
-    if (!row_blk_start.empty()) {
-        const int32_t mb = static_cast<int32_t>(row_blk_start.size()) - 1;
-        brow_order.resize(mb);
-        for (int32_t i = 0; i < mb; ++i)
-            brow_order[i] = i;
-        std::stable_sort(brow_order.begin(), brow_order.end(), [&](int32_t a, int32_t b) {
-            return row_blk_start[a + 1] - row_blk_start[a] > row_blk_start[b + 1] - row_blk_start[b];
-        });
-        for (int32_t si = 0; si < mb; ++si)
-            for (int32_t r = 0; r < Z; ++r)
-                row_deg[si * Z + r] = row_blk_start[brow_order[si] + 1] - row_blk_start[brow_order[si]];
-    } else {
-        for (int32_t i = 0; i < h.m; ++i)
-            row_deg[i] = h.row_ptr[i + 1] - h.row_ptr[i];
-    }
-    row_gmax.assign((h.m + 31) / 32, 0);
-    for (int32_t i = 0; i < h.m; ++i)
-        row_gmax[i / 32] = std::max(row_gmax[i / 32], row_deg[i]);
-    col_gmax.assign((h.n + 63) / 64, 0);
-    for (int32_t j = 0; j < h.n; ++j)
-        col_gmax[j / 64] = std::max(col_gmax[j / 64], h.col_ptr[j + 1] - h.col_ptr[j]);
-}
-
-// Half-row words of the fused kernel's circulant view (see ldpc_code_s):
-// row slot sr is row r = sr mod Z of block-row brow_order[sr / Z], whose
-// blocks are b0 .. b0 + d - 1; its first half holds ceil(d / 2) blocks from
-// b0, its second the rest.  Empty when there is no circulant view or a
-// field would overflow (13 bits of block index, 6 of length, 13 of row).
-std::vector<int32_t> half_row_words(const std::vector<int32_t> &row_blk_start, const std::vector<int32_t> &brow_order,
-                                    int32_t Z, int32_t m)
-{
-    std::vector<int32_t> out;
-    if (row_blk_start.empty() || brow_order.empty() || Z < 1 || Z >= (1 << 13) || row_blk_start.back() >= (1 << 13))
-        return out;
-    out.resize(2 * static_cast<size_t>(m));
-    for (int32_t sr = 0; sr < m; ++sr) {
-        const int32_t i = brow_order[sr / Z], r = sr % Z;
-        const int32_t b0 = row_blk_start[i], d = row_blk_start[i + 1] - b0, h = (d + 1) / 2;
-        if (h >= (1 << 6))
-            return {};
-        for (int32_t half = 0; half < 2; ++half) {
-            const uint32_t k0 = half ? h : 0, dh = half ? d - h : h;
-            const uint32_t w = (static_cast<uint32_t>(b0) + k0) | dh << 13 | static_cast<uint32_t>(r) << 19;
-            out[2 * static_cast<size_t>(sr) + half] = static_cast<int32_t>(w);
-        }
-    }
-    return out;
-}
-
 // Greedy layers over the rows in ascending order: a row opens a new layer
 // when it shares a variable with a row of the current one.  Visiting the
 // layers in order, each as a parallel step, equals visiting the rows one at a
@@ -186,31 +131,204 @@ uint64_t shape_hash(const HostLayout &h, int32_t Z)
     return x;
 }
 
-ldpc_status upload(const HostLayout &h, const std::vector<int32_t> *qc_tab, const std::vector<int32_t> &row_blk_start,
-                   int32_t Z, ldpc_code_s *c)
+// Host image of the device allocation.  Tables are sized before they are
+// filled: a code's handle is made once, but a program waits for it.
+struct TableImage {
+    std::vector<int32_t> words;
+    // `count` words of `fill` on a 16-byte boundary (quads are 16-byte loads).
+    size_t take(size_t count, int32_t fill)
+    {
+        const size_t at = (words.size() + 3) / 4 * 4;
+        words.resize(at, 0);
+        words.resize(at + count, fill);
+        return at;
+    }
+};
+
+constexpr int64_t kLdsBytes = 160 * 1024;  // one workgroup's, gfx950
+
+// Splits of a row of degree d: halves, or (layered) quarters.
+void part_span(int32_t d, int part, int parts, int32_t &k0, int32_t &len)
+{
+    const int32_t h = (d + 1) / 2, q1 = (h + 1) / 2, q3 = h + (d - h + 1) / 2;
+    const int32_t cut2[3] = {0, h, d}, cut4[5] = {0, q1, h, q3, d};
+    const int32_t *cut = parts == 2 ? cut2 : cut4;
+    k0 = cut[part];
+    len = cut[part + 1] - cut[part];
+}
+
+struct FusedOffsets {
+    bool built = false, explicit_too = false;
+    int32_t row_groups = 0, slot_words = 0;
+    size_t row_grp = 0, row_tab = 0, col_grp = 0, col_tab = 0;
+    size_t row_grp_x = 0, row_tab_x = 0, row_pos_x = 0, col_tab_x = 0;
+    size_t lay_ptr = 0, lay_grp = 0, lay_tab = 0;
+};
+
+// The tables described at FusedTables, appended to `im`.  Codes whose messages
+// cannot fit a workgroup in FP32, or whose rows are longer than the kernel's
+// bodies, get none.
+FusedOffsets fused_tables(const HostLayout &h, const std::vector<int32_t> &layer_ptr, TableImage &im)
+{
+    FusedOffsets o;
+    const int64_t E = static_cast<int64_t>(h.col_idx.size());
+    if (h.max_row_deg > 32 || 4 * (E + h.n) > kLdsBytes)
+        return o;
+    o.built = true;
+    const int32_t first = ldpc::fused_first_message(h.n), inf = 4 * h.n, minus_zero = 4 * (h.n + 1),
+                  junk = 4 * (h.n + 2);
+    auto degree = [&](int32_t i) { return h.row_ptr[i + 1] - h.row_ptr[i]; };
+    // rows by descending degree, stable; `filled` of them have an edge
+    std::vector<int32_t> order(h.m), rank(34, 0);
+    for (int32_t i = 0; i < h.m; ++i)
+        ++rank[33 - degree(i)];
+    for (int32_t d = 1; d < 34; ++d)
+        rank[d] += rank[d - 1];
+    const int32_t filled = rank[32];
+    for (int32_t i = h.m - 1; i >= 0; --i)
+        order[--rank[33 - degree(i)]] = i;
+    o.row_groups = (filled + 31) / 32;
+
+    std::vector<int32_t> slot_of(E);  // padded order: an edge's word among the messages
+    auto rows = [&](bool x, size_t &grp_at, size_t &tab_at, size_t *pos_at) {
+        size_t quad_rows = 0;
+        for (int32_t g = 0; g < o.row_groups; ++g)
+            quad_rows += x ? 4 : ((degree(order[32 * g]) + 1) / 2 + 3) / 4;
+        grp_at = im.take(2 * static_cast<size_t>(o.row_groups), 0);
+        tab_at = im.take(quad_rows * 256, inf);
+        if (x)
+            *pos_at = im.take(quad_rows * 256, junk);
+        int32_t *grp = im.words.data() + grp_at, *tab = im.words.data() + tab_at;
+        int32_t *pos = x ? im.words.data() + *pos_at : nullptr;
+        int32_t slots = 0, quad_row = 0;
+        for (int32_t g = 0; g < o.row_groups; ++g) {
+            const int32_t longest = (degree(order[32 * g]) + 1) / 2;
+            grp[2 * g] = longest << 16 | slots;
+            grp[2 * g + 1] = quad_row;
+            for (int32_t lane = 0; lane < 64; ++lane) {
+                const int32_t sr = 32 * g + (lane & 31);
+                if (sr >= filled)
+                    continue;
+                int32_t k0, len;
+                part_span(degree(order[sr]), lane >> 5, 2, k0, len);
+                const int32_t e0 = h.row_ptr[order[sr]] + k0;
+                const size_t base = static_cast<size_t>(quad_row) * 256 + static_cast<size_t>(lane) * 4;
+                for (int32_t k = 0; k < len; ++k) {
+                    const size_t at = base + static_cast<size_t>(k >> 2) * 256 + (k & 3);
+                    tab[at] = 4 * h.col_idx[e0 + k];
+                    if (x)
+                        pos[at] = 4 * (first + e0 + k);
+                    else
+                        slot_of[e0 + k] = (slots + k) * 64 + lane;
+                }
+            }
+            slots += longest;
+            quad_row += x ? 4 : (longest + 3) / 4;
+        }
+        return slots * 64;
+    };
+    auto columns = [&](bool x, size_t *grp_at, size_t &tab_at) {
+        const int32_t groups = (h.n + 63) / 64;
+        std::vector<int32_t> longest(groups, 0);
+        size_t quad_rows = 0;
+        for (int32_t g = 0; g < groups; ++g) {
+            for (int32_t j = 64 * g; j < std::min(h.n, 64 * g + 64); ++j)
+                longest[g] = std::max(longest[g], h.col_ptr[j + 1] - h.col_ptr[j]);
+            quad_rows += (longest[g] + 3) / 4;
+        }
+        if (grp_at)
+            *grp_at = im.take(2 * static_cast<size_t>(groups), 0);
+        tab_at = im.take(quad_rows * 256, minus_zero);
+        int32_t *grp = grp_at ? im.words.data() + *grp_at : nullptr, *tab = im.words.data() + tab_at;
+        int32_t quad_row = 0;
+        for (int32_t g = 0; g < groups; ++g) {
+            if (grp) {
+                grp[2 * g] = longest[g];
+                grp[2 * g + 1] = quad_row;
+            }
+            for (int32_t j = 64 * g; j < std::min(h.n, 64 * g + 64); ++j) {
+                const int32_t *edge = h.col_edge.data() + h.col_ptr[j];
+                const size_t base = static_cast<size_t>(quad_row) * 256 + static_cast<size_t>(j & 63) * 4;
+                for (int32_t k = 0; k < h.col_ptr[j + 1] - h.col_ptr[j]; ++k)
+                    tab[base + static_cast<size_t>(k >> 2) * 256 + (k & 3)] =
+                        4 * (first + (x ? edge[k] : slot_of[edge[k]]));
+            }
+            quad_row += (longest[g] + 3) / 4;
+        }
+    };
+    o.slot_words = rows(false, o.row_grp, o.row_tab, nullptr);
+    columns(false, &o.col_grp, o.col_tab);
+    // a type whose frames fit in CSR order but not in the padded order
+    for (const int64_t ts : {4, 8})
+        o.explicit_too |= ts * (first + o.slot_words) + 32 > kLdsBytes && ts * (first + E) <= kLdsBytes;
+    if (o.explicit_too) {
+        rows(true, o.row_grp_x, o.row_tab_x, &o.row_pos_x);
+        columns(true, nullptr, o.col_tab_x);
+    }
+
+    auto longest_quarter = [&](int32_t r0, int32_t rows16) {
+        int32_t longest = 0;
+        for (int32_t r = r0; r < r0 + rows16; ++r)
+            longest = std::max(longest, ((degree(r) + 1) / 2 + 1) / 2);
+        return longest;
+    };
+    const size_t layers = layer_ptr.size() - 1;
+    size_t groups = 0, words = 0;
+    for (size_t l = 0; l < layers; ++l)
+        for (int32_t r0 = layer_ptr[l]; r0 < layer_ptr[l + 1]; r0 += 16) {
+            const int32_t rows16 = std::min(16, layer_ptr[l + 1] - r0);
+            words += static_cast<size_t>((longest_quarter(r0, rows16) + 3) / 4) * 32 * rows16;
+            ++groups;
+        }
+    o.lay_ptr = im.take(layers + 1, 0);
+    o.lay_grp = im.take(2 * groups, 0);
+    o.lay_tab = im.take(words, inf);
+    int32_t *ptr = im.words.data() + o.lay_ptr, *grp = im.words.data() + o.lay_grp;
+    int32_t *tab = im.words.data() + o.lay_tab;
+    size_t g = 0, base = 0;
+    for (size_t l = 0; l < layers; ++l) {
+        ptr[l] = static_cast<int32_t>(g);
+        for (int32_t r0 = layer_ptr[l]; r0 < layer_ptr[l + 1]; r0 += 16, ++g) {
+            const int32_t rows16 = std::min(16, layer_ptr[l + 1] - r0), longest = longest_quarter(r0, rows16);
+            const size_t half = static_cast<size_t>((longest + 3) / 4) * 16 * rows16;
+            grp[2 * g] = longest << 8 | rows16;
+            grp[2 * g + 1] = static_cast<int32_t>(base / 4);
+            std::fill(tab + base + half, tab + base + 2 * half, junk);
+            for (int32_t r = 0; r < rows16; ++r)
+                for (int part = 0; part < 4; ++part) {
+                    int32_t k0, len;
+                    part_span(degree(r0 + r), part, 4, k0, len);
+                    const int32_t e0 = h.row_ptr[r0 + r] + k0;
+                    for (int32_t k = 0; k < len; ++k) {
+                        const size_t at = base + (static_cast<size_t>(k >> 2) * 4 * rows16 + part * rows16 + r) * 4 +
+                                          (k & 3);
+                        tab[at] = 4 * h.col_idx[e0 + k];
+                        tab[at + half] = 4 * (first + e0 + k);
+                    }
+                }
+            base += 2 * half;
+        }
+    }
+    ptr[layers] = static_cast<int32_t>(g);
+    return o;
+}
+
+ldpc_status upload(const HostLayout &h, int32_t Z, ldpc_code_s *c)
 {
     layer_tables(h, c->layer_ptr, c->layer_dmax);
-    std::vector<int32_t> brow_order, row_gmax, col_gmax;
-    slot_tables(h, row_blk_start, Z, brow_order, row_gmax, col_gmax);
-    const std::vector<int32_t> halves = half_row_words(row_blk_start, brow_order, Z, h.m);
-    const size_t words = h.row_ptr.size() + h.col_idx.size() + h.col_ptr.size() + h.col_edge.size() +
-                         (qc_tab ? qc_tab->size() : 0) + brow_order.size() + row_gmax.size() + col_gmax.size() +
-                         c->layer_ptr.size() + halves.size();
-    std::vector<int32_t> blob;
-    blob.reserve(words);
+    TableImage im;
+    im.words.reserve(10 * h.col_idx.size() + 4 * h.row_ptr.size() + 4 * h.col_ptr.size() + 4096);
+    const FusedOffsets fo = fused_tables(h, c->layer_ptr, im);
     auto put = [&](const std::vector<int32_t> &v) {
-        const size_t off = blob.size();
-        blob.insert(blob.end(), v.begin(), v.end());
+        const size_t off = im.words.size();
+        im.words.insert(im.words.end(), v.begin(), v.end());
         return off;
     };
     const size_t o_rp = put(h.row_ptr), o_ci = put(h.col_idx), o_cp = put(h.col_ptr), o_ce = put(h.col_edge);
-    const size_t o_qc = qc_tab ? put(*qc_tab) : 0;
-    const size_t o_bo = put(brow_order), o_rg = put(row_gmax), o_cg = put(col_gmax), o_lp = put(c->layer_ptr);
-    const size_t o_hr = put(halves);
     void *d = nullptr;
-    if (hipMalloc(&d, std::max<size_t>(blob.size(), 1) * sizeof(int32_t)) != hipSuccess)
+    if (hipMalloc(&d, std::max<size_t>(im.words.size(), 1) * sizeof(int32_t)) != hipSuccess)
         return LDPC_ENOMEM;
-    if (hipMemcpy(d, blob.data(), blob.size() * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess) {
+    if (hipMemcpy(d, im.words.data(), im.words.size() * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess) {
         (void)hipFree(d);
         return LDPC_EDEVICE;
     }
@@ -220,12 +338,24 @@ ldpc_status upload(const HostLayout &h, const std::vector<int32_t> *qc_tab, cons
     c->col_idx = base + o_ci;
     c->col_ptr = base + o_cp;
     c->col_edge = base + o_ce;
-    c->qc_tab = qc_tab ? base + o_qc : nullptr;
-    c->brow_order = brow_order.empty() ? nullptr : base + o_bo;
-    c->row_gmax = base + o_rg;
-    c->col_gmax = base + o_cg;
-    c->d_layer_ptr = base + o_lp;
-    c->half_rows = halves.empty() ? nullptr : reinterpret_cast<const uint32_t *>(base + o_hr);
+    if (fo.built) {
+        ldpc::FusedTables &t = c->fused;
+        t.row_groups = fo.row_groups;
+        t.slot_words = fo.slot_words;
+        t.row_grp = base + fo.row_grp;
+        t.row_tab = base + fo.row_tab;
+        t.col_grp = base + fo.col_grp;
+        t.col_tab = base + fo.col_tab;
+        if (fo.explicit_too) {
+            t.row_grp_x = base + fo.row_grp_x;
+            t.row_tab_x = base + fo.row_tab_x;
+            t.row_pos_x = base + fo.row_pos_x;
+            t.col_tab_x = base + fo.col_tab_x;
+        }
+        t.lay_ptr = base + fo.lay_ptr;
+        t.lay_grp = base + fo.lay_grp;
+        t.lay_tab = base + fo.lay_tab;
+    }
     c->m = h.m;
     c->n = h.n;
     c->E = static_cast<int64_t>(h.col_idx.size());
@@ -272,7 +402,7 @@ try {
         delete c;
         return LDPC_EDEVICE;
     }
-    st = upload(h, nullptr, {}, 0, c);
+    st = upload(h, 0, c);
     if (st != LDPC_OK) {
         delete c;
         return st;
@@ -317,25 +447,6 @@ try {
     ldpc_status st = build_host_layout(m, n, row_ptr.data(), col_idx.data(), h);
     if (st != LDPC_OK)
         return st;
-    std::vector<int32_t> col_blk_start(nb + 1, 0), col_blk;
-    int32_t max_bcol = 0, max_brow = 0;
-    for (int32_t j = 0; j < nb; ++j) {
-        for (int32_t i = 0; i < mb; ++i)
-            for (int32_t b = row_blk_start[i]; b < row_blk_start[i + 1]; ++b)
-                if (blk_col[b] == j)
-                    col_blk.push_back(b);
-        col_blk_start[j + 1] = static_cast<int32_t>(col_blk.size());
-        max_bcol = std::max(max_bcol, col_blk_start[j + 1] - col_blk_start[j]);
-    }
-    for (int32_t i = 0; i < mb; ++i)
-        max_brow = std::max(max_brow, row_blk_start[i + 1] - row_blk_start[i]);
-    std::vector<int32_t> tab;
-    tab.insert(tab.end(), row_blk_start.begin(), row_blk_start.end());
-    tab.insert(tab.end(), blk_col.begin(), blk_col.end());
-    tab.insert(tab.end(), blk_shift.begin(), blk_shift.end());
-    tab.insert(tab.end(), col_blk_start.begin(), col_blk_start.end());
-    tab.insert(tab.end(), col_blk.begin(), col_blk.end());
-
     auto *c = new (std::nothrow) ldpc_code_s();
     if (!c)
         return LDPC_ENOMEM;
@@ -343,7 +454,7 @@ try {
         delete c;
         return LDPC_EDEVICE;
     }
-    st = upload(h, &tab, row_blk_start, Z, c);
+    st = upload(h, Z, c);
     if (st != LDPC_OK) {
         delete c;
         return st;
@@ -353,10 +464,7 @@ try {
     c->nb = nb;
     c->Z = Z;
     c->nblocks = nblocks;
-    c->max_brow_deg = max_brow;
-    c->max_bcol_deg = max_bcol;
-    c->qc_words = static_cast<int32_t>(tab.size());
-    c->h_qc_tab = std::move(tab);
+    c->qc_words = (mb + 1) + 3 * nblocks + (nb + 1);
     *out = c;
     return LDPC_OK;
 } catch (...) {

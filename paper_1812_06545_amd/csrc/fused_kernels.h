@@ -7,31 +7,41 @@
 // check-node and variable-node phases becomes a workgroup barrier, because
 // the frames are independent (the frame-level parallelism of Section III-A)
 // and one workgroup owns a whole frame.  HBM traffic per frame is the channel
-// LLRs (read once per iteration, from L2 after the first) and the outputs.
+// LLRs (read once per iteration, from L2 after the first) and the outputs; the
+// code's address tables stream from L2.
 //
 // One launch decodes a batch of jobs of different codes, lengths and rates, in
 // items of one (job, frame) each; a frame that stops early frees its workgroup
 // for the next item.
 //
-// Thread mapping: check rows are visited in slot order (for QC codes
-// block-rows sorted by decreasing degree).  A wavefront's 64 rows may differ
-// in degree; the wave runs the straight-line body of its largest degree and
-// pads shorter rows with dummy edges carrying q = +inf, whose term is exactly
-// the identity of the row's combination and whose sign is +, so every real
-// message is computed with exactly the operations and rounding of the plain
-// path (bit-identical results).
+// Lanes and tables.  Every code runs from address tables that its handle
+// carries (FusedTables, code.cpp), so that no kernel derives an address:
+//   flooding   a group is 32 check rows of like degree (rows sorted by
+//              descending degree); lane l takes the first half of row l mod 32
+//              for l < 32, the second half for l >= 32.  Slot k of every lane
+//              has its posterior's LDS address in the table, four slots to a
+//              16-byte load.  The messages lie in the same order, slot by slot
+//              and lane by lane, so a message's address is the group's plus a
+//              constant, and no two lanes meet in an LDS bank.
+//   columns    a group is 64 variables; the table holds the addresses of each
+//              one's messages in ascending row order.
+//   layered    a group is up to 16 rows of one layer; lanes l, l + 16, l + 32
+//              and l + 48 take a row's quarters.  Messages lie in CSR order and
+//              have table addresses too, since a layer may hold few rows and
+//              the padded order would not be bounded.
+// A lane with fewer slots than its group's longest is padded with dummies:
+// their posterior is a word holding +inf, whose term is exactly the identity
+// of the row's combination and whose sign is +, so every real message is
+// computed with exactly the operations and rounding of the plain path
+// (bit-identical results); a column's dummies add a word holding -0, which
+// changes no sum.
 //
-// LDS per workgroup (FrameLayout; all accesses by byte offset from its
-// start): the posterior L of every variable, a word holding +inf, one
-// dummy-edge slot per thread, r for every edge, and the code's tables
-// (circulant codes: row and column views, and spare zero words after the
-// column view so that a column body may read past its own entries).
-//
-// Circulant codes keep their messages in a rotated layout: the message of
-// row r of block b, whose shift is s_b, sits at b*Z + ((r + s_b) mod Z),
-// the offset of the edge's column inside its block-column.  A row then
-// finds its message and its posterior from one offset, and a column finds
-// the messages of its blocks without any modular arithmetic.
+// What this layout is for: the flooding kernel is bound by VALU issue.  With
+// addresses formed from the circulants' shifts in the kernel (one table word
+// per block in LDS) a slot cost 7 of its 44 instructions, a column's message
+// 3, and the parked terms two LDS accesses; codes without circulants read
+// their indices uncoalesced, a cache line per lane.  The tables cost 4 bytes
+// of L2 traffic per edge and phase, about 3 TB/s over the device.
 #pragma once
 
 #include <algorithm>
@@ -49,15 +59,13 @@ namespace fused {
 constexpr int kMaxCodes = 16;
 constexpr int kMaxJobs = 24;
 
-// Kernel-argument copy of a code's device layout.
+// Kernel-argument copy of a code's tables (device pointers; see FusedTables).
 struct Code {
-    int32_t m, n, E, Z, nblocks;
-    int32_t mb, nb, qc, words;  // qc: use the circulant view (words: QC table words, 0 otherwise)
-    uint32_t zmagic;            // ceil(2^32 / Z): x / Z = mulhi(x, zmagic) for x * Z < 2^32 (qc only, Z >= 2)
-    const int32_t *tab, *row_ptr, *col_idx, *col_ptr, *col_edge, *brow_order, *row_gmax, *col_gmax;
-    const int32_t *layer_ptr;  // layered schedule, CSR view: layer l = rows [layer_ptr[l], layer_ptr[l+1])
-    int32_t nlayers;
-    const uint32_t *half_rows;  // circulant view: word 2 sr + h = half h of row slot sr (or null)
+    int32_t n, E;
+    int32_t row_groups, nlayers;
+    int32_t r_words;  // message words of a flooding frame (E with an explicit order)
+    int32_t m;
+    const int32_t *row_grp, *row_tab, *row_pos, *col_grp, *col_tab, *lay_ptr, *lay_grp, *lay_tab;
 };
 
 struct Job {
@@ -70,18 +78,18 @@ struct Job {
     void *post;
 };
 
-// One launch's jobs, passed to the kernel by value.  Item i (a frame, or in
-// the pair kernel two) belongs to the last job j with begin[j] <= i; the
+// One launch's jobs, passed to the kernel by value.  Item i (a frame, or
+// frames_per_item of them) belongs to the last job j with begin[j] <= i; the
 // entries past njobs hold INT32_MAX.
 struct Batch {
     int32_t njobs, ncodes;
-    int32_t nitems;
-    int32_t emax, nmax, words_max, mb_max;
+    int32_t nitems, frames_per_item;
+    uint32_t flags_at;  // LDS address of the workgroup's flag words
     int32_t begin[kMaxJobs];
     Code codes[kMaxCodes];
     Job jobs[kMaxJobs];
 };
-static_assert(sizeof(Batch) <= 4096, "a launch's kernel arguments are limited to 4 KiB");
+static_assert(sizeof(Batch) <= 4080, "a launch's kernel arguments are limited to 4 KiB");
 
 __device__ __forceinline__ int32_t job_of_item(const Batch &b, int32_t item)
 {
@@ -92,51 +100,25 @@ __device__ __forceinline__ int32_t job_of_item(const Batch &b, int32_t item)
     return j;
 }
 
-// One message-sized LDS word per thread (up to 512) after the +inf word: the
-// target of dummy-edge stores, so that a half row's stores need no
-// exec-mask branch and its loads can all be issued first.
-constexpr int kDummySlots = 512;
-// Zero words after the circulant column table: a column body of length D
-// reads table slots k0 .. k0 + D - 1 whatever the column's degree, which for
-// the last block-columns runs up to D - 1 words past the table's end.  A zero
-// word decodes to an offset inside the posteriors, a valid LDS address.
-// Exact column bodies go up to degree 16.
-constexpr int kColSpare = 16;
+// Workgroups have up to kMaxThreads threads in FP32 and kBaseThreads in FP64,
+// whose bodies need the registers of two wavefronts per SIMD.  kBaseThreads is
+// also the size the callers' settings end at; a launch left at it takes the
+// size workgroup_threads() picks.
+constexpr int kBaseThreads = 512, kMaxThreads = 1024;
 
-__host__ __device__ inline uint32_t align16(size_t x) { return static_cast<uint32_t>((x + 15) / 16 * 16); }
+// LDS of a workgroup, in words of the message type: the posteriors, then at
+// n + kInfWord .. the constants dummies use, then from first_message(n) the
+// messages; the flag words follow the launch's largest frame.  All of it is
+// dynamic and starts at address 0 (the kernels have no static LDS).  The
+// tables hold byte addresses of 4-byte words.
+constexpr int kInfWord = 0, kMinusZeroWord = 1, kJunkWord = 2;  // junk: a dummy's message (any finite value)
+constexpr int kFlagWords = 4, kItemFlag = 3;                    // three vote words, then the workgroup's next item
 
-// Byte layout of a workgroup's LDS for `frames` frames (1, or 2 for the
-// pair kernel) of the launch's largest n and E.  Frame k's region starts at
-// k * span; inside it (offsets from its start):
-//   [0, n)              posteriors L (message-sized words)
-//   n                   +inf: dummy edges read their posterior there
-//   n + 1 + t           dummy slot of thread t
-//   r0 ..               messages r, one word per edge
-// The workgroup's flags (kFlagWords int32 words, Vote below) follow the last
-// frame, at t0 - 4 kFlagWords, and the code's tables (int32 words) them, at t0.
-// All of a workgroup's LDS is dynamic and starts at address 0 (the kernels
-// have no static LDS), so the offsets above are LDS addresses.
-constexpr int kFlagWords = 4, kItemFlag = 3;  // three vote words, then the workgroup's next item
-struct FrameLayout {
-    uint32_t r0, span, t0;
-    size_t bytes;
-};
-__host__ __device__ inline FrameLayout frame_layout(int64_t E, int32_t n, int32_t words, int32_t nblocks, int32_t mb,
-                                                    size_t tsize, int frames = 1)
+// Bytes for the flag words and a frame of n variables and `r_words` messages.
+inline size_t lds_bytes(int32_t n, int64_t r_words, size_t tsize)
 {
-    FrameLayout f;
-    f.r0 = align16((static_cast<size_t>(n) + 1 + kDummySlots) * tsize);
-    f.span = align16(f.r0 + static_cast<size_t>(E) * tsize);
-    f.t0 = f.span * static_cast<uint32_t>(frames) + kFlagWords * static_cast<uint32_t>(sizeof(int32_t));
-    f.bytes = f.t0 + static_cast<size_t>(words + 2 * nblocks + mb + kColSpare) * sizeof(int32_t);
-    return f;
-}
-
-// LDS bytes a workgroup needs for `frames` frames of this code.
-__host__ __device__ inline size_t frame_lds_bytes(int64_t E, int32_t n, int32_t words, int32_t nblocks, int32_t mb,
-                                                  size_t tsize, int frames = 1)
-{
-    return frame_layout(E, n, words, nblocks, mb, tsize, frames).bytes;
+    return align_up((static_cast<size_t>(fused_first_message(n)) + static_cast<size_t>(r_words)) * tsize, 16) +
+           kFlagWords * sizeof(int32_t);
 }
 
 // LDS is addressed by integers: a workgroup's LDS starts at address 0, and an
@@ -149,35 +131,33 @@ __device__ __forceinline__ Lds<T> *lds_at(uint32_t addr)
 {
     return (Lds<T> *)addr;
 }
-// Loads and stores of LDS words by byte offset from the frame's base.
 template <class T>
-__device__ __forceinline__ T lds_ld(uint32_t base, uint32_t off)
+__device__ __forceinline__ T lds_ld(uint32_t addr)
 {
-    return *lds_at<T>(base + off);
+    return *lds_at<T>(addr);
 }
 template <class T>
-__device__ __forceinline__ void lds_st(uint32_t base, uint32_t off, T v)
+__device__ __forceinline__ void lds_st(uint32_t addr, T v)
 {
-    *lds_at<T>(base + off) = v;
+    *lds_at<T>(addr) = v;
 }
 
 // Workgroup-wide OR at a barrier, through an LDS word per use: any(v) is
-// nonzero on every thread if v was on some thread.  Three words take turns.
-// After the barrier of use u thread 0 clears the word of use u + 2: every
-// thread has read it (for use u - 1) before that barrier, and use u + 2 sets
-// it after the barrier of use u + 1, which thread 0 reaches after the clear.
-// One barrier and one LDS word per use, where __syncthreads_or takes several
-// barriers and 272 bytes of static LDS (which moved every address below by a
-// constant, one more addition per edge).
+// nonzero on every thread if v (uniform in each wavefront) was on some
+// wavefront.  Three words take turns.  After the barrier of use u thread 0
+// clears the word of use u + 2: every thread has read it (for use u - 1)
+// before that barrier, and use u + 2 sets it after the barrier of use u + 1,
+// which thread 0 reaches after the clear.  One barrier and one LDS word per
+// use, where __syncthreads_or takes several barriers and static LDS.
 struct Vote {
     Lds<int32_t> *w;  // three words, zero at the start
     uint32_t k = 0;   // uses so far, mod 3
-    __device__ __forceinline__ int32_t any(uint32_t v)
+    __device__ __forceinline__ int32_t any(bool v)
     {
-        if (__any(static_cast<int>(v)) && (threadIdx.x & 63) == 0)
+        if (v && (threadIdx.x & 63) == 0)
             w[k] = 1;
         __syncthreads();
-        const int32_t r = w[k];
+        const int32_t r = __builtin_amdgcn_readfirstlane(w[k]);
         if (threadIdx.x == 0)
             w[k == 0 ? 2 : k - 1] = 0;
         k = k == 2 ? 0 : k + 1;
@@ -185,682 +165,502 @@ struct Vote {
     }
 };
 
-__device__ __forceinline__ int32_t div_z(int32_t x, uint32_t zmagic)
+// Value of the partner lane (lane ^ 32: the other half of the row) and of the
+// sibling lane (lane ^ 16: the other quarter of the half), by the lane-group
+// swaps: after a swap of x with itself one result holds x's even lane groups
+// in every group, the other its odd ones.
+template <int M>
+__device__ __forceinline__ uint32_t lane_swap(uint32_t v)
 {
-    return static_cast<int32_t>(__umulhi(static_cast<uint32_t>(x), zmagic));
-}
-
-// Byte offsets of the messages and posteriors of one half row.
-//   QC:  slot k of a half row starting at block b0 + k0:
-//        c = tsize * ((r + s) mod Z) for that block's shift s,
-//        message b * Z * tsize + c (rotated layout), posterior j * Z * tsize + c
-//   CSR: slot k is edge e0 + k0 + k (CSR order), posterior col_idx[e]
-struct RowQC {
-    // The row table in LDS is followed by at least kColSpare readable words
-    // (the block-row order, the column table and its spare words), so
-    // offsets(k) may be read for any k < kColSpare past a row's blocks: the
-    // offsets are then some values, which the caller discards.
-    static constexpr bool kReadPast = true;
-    uint32_t r_t;          // tsize * r
-    uint32_t z_t;          // tsize * Z
-    uint32_t base;         // r0 + tsize * Z * (first block of this half)
-    const Lds<uint32_t> *pack;  // from this half's first block: (tsize * j * Z) | (tsize * s) << 16
-    __device__ __forceinline__ void offsets(int k, uint32_t &ri, uint32_t &ci) const
-    {
-        const uint32_t w = pack[k];
-        const uint32_t c = r_t + (w >> 16);                             // in [0, 2 z_t): min picks c or c - z_t
-        const uint32_t cm = __builtin_elementwise_min(c, c - z_t);
-        ci = (w & 0xffffu) + cm;
-        ri = base + static_cast<uint32_t>(k) * z_t + cm;
-    }
-};
-
-template <int TS>
-struct RowCSR {
-    static constexpr bool kReadPast = false;  // col_idx ends with the last row
-    uint32_t base;        // r0 + TS * (e0 + k0)
-    const int32_t *cols;  // global: col_idx + e0 + k0
-    __device__ __forceinline__ void offsets(int k, uint32_t &ri, uint32_t &ci) const
-    {
-        ri = base + static_cast<uint32_t>(k * TS);
-        ci = static_cast<uint32_t>(cols[k] * TS);
-    }
-};
-
-// Offsets of slot k of a half row: the real edge's, or, for a slot past its
-// edges (a dummy), this thread's dummy slot and the +inf word.  Where the row
-// view allows it the table is read unconditionally, so the load needs no
-// exec-mask branch.
-template <class Row>
-__device__ __forceinline__ void slot_offsets(const Row &row, int k, bool real, uint32_t dslot, uint32_t inf_off,
-                                             uint32_t &ri, uint32_t &ci)
-{
-    if constexpr (Row::kReadPast) {
-        static_assert(kColSpare >= 16, "half rows up to 16 slots read past the row table");
-        uint32_t a, b;
-        row.offsets(k, a, b);
-        ri = real ? a : dslot;
-        ci = real ? b : inf_off;
+    static_assert(M == 16 || M == 32, "lane groups of 16 or 32");
+    const bool odd = (threadIdx.x & M) != 0;
+    if constexpr (M == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        return odd ? r[0] : r[1];
     } else {
-        if (real) {
-            row.offsets(k, ri, ci);
-        } else {
-            ri = dslot;
-            ci = inf_off;
-        }
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        return odd ? r[0] : r[1];
     }
 }
+template <int M>
+__device__ __forceinline__ float lane_swap(float v)
+{
+    return __uint_as_float(lane_swap<M>(__float_as_uint(v)));
+}
+template <int M>
+__device__ __forceinline__ double lane_swap(double v)
+{
+    const uint64_t u = static_cast<uint64_t>(__double_as_longlong(v));
+    const uint64_t lo = lane_swap<M>(static_cast<uint32_t>(u)), hi = lane_swap<M>(static_cast<uint32_t>(u >> 32));
+    return __longlong_as_double(static_cast<long long>(hi << 32 | lo));
+}
+template <int M>
+__device__ __forceinline__ ArithF32::Acc lane_swap(const ArithF32::Acc &v)
+{
+    return ArithF32::Acc{lane_swap<M>(v.P), lane_swap<M>(v.Q)};
+}
+template <int M>
+__device__ __forceinline__ ArithF64::Acc lane_swap(const ArithF64::Acc &v)
+{
+    return ArithF64::Acc{lane_swap<M>(v.P), lane_swap<M>(v.Q)};
+}
 
-// Per-thread places every half row of a frame shares: this thread's dummy
-// slot and the +inf word (byte offsets).
-struct Slots {
-    uint32_t dslot, inf_off;
+// Slots 4i .. 4i + 3 of a lane.
+typedef int32_t Quad __attribute__((ext_vector_type(4)));
+constexpr int quads(int d) { return (d + 3) / 4; }
+
+// Table addresses of D slots, from this lane's first quad, quads `stride` apart.
+template <class T, int D>
+struct Addresses {
+    Quad q[quads(D)];
+    __device__ __forceinline__ void load(const Quad *tab, int stride)
+    {
+#pragma unroll
+        for (int i = 0; i < quads(D); ++i)
+            q[i] = tab[i * stride];
+    }
+    __device__ __forceinline__ uint32_t operator[](int k) const
+    {
+        return static_cast<uint32_t>(q[k / 4][k % 4]) * static_cast<uint32_t>(sizeof(T) / 4);
+    }
 };
 
-// Value of the partner lane (lane ^ 32): the other half of the same row.
-// Rows are laid out so that lanes 0..31 of a wavefront hold the first halves
-// of 32 consecutive rows and lanes 32..63 their second halves.
-__device__ __forceinline__ uint32_t pair_swap(uint32_t v)
+// Where a flooding lane's messages lie: slot by slot (ra: slot 0's address),
+// or, where the padded order did not fit, at table addresses.
+template <class T, int D, bool POS>
+struct Messages {
+    uint32_t ra;
+    Addresses<T, POS ? D : 1> pos;
+    __device__ __forceinline__ uint32_t operator[](int k) const
+    {
+        if constexpr (POS)
+            return pos[k];
+        else
+            return ra + static_cast<uint32_t>(k * 64 * static_cast<int>(sizeof(T)));
+    }
+};
+
+// Parity of a row whose two halves lie 32 lanes apart, over the wavefront:
+// some row is odd.
+__device__ __forceinline__ bool some_odd(uint64_t half_parity)
 {
-    return static_cast<uint32_t>(__shfl_xor(static_cast<int>(v), 32));
-}
-__device__ __forceinline__ float pair_swap(float v) { return __shfl_xor(v, 32); }
-__device__ __forceinline__ double pair_swap(double v) { return __shfl_xor(v, 32); }
-__device__ __forceinline__ ArithF32::Acc pair_swap(const ArithF32::Acc &v)
-{
-    return ArithF32::Acc{pair_swap(v.P), pair_swap(v.Q)};
-}
-__device__ __forceinline__ ArithF64::Acc pair_swap(const ArithF64::Acc &v)
-{
-    return ArithF64::Acc{pair_swap(v.P), pair_swap(v.Q)};
+    return (static_cast<uint32_t>(half_parity) ^ static_cast<uint32_t>(half_parity >> 32)) != 0u;
 }
 
-// Value of lane ^ 16: the sibling quarter of a layered row, whose four
-// quarters sit in lanes l, l + 16, l + 32 and l + 48 (l < 16).
-__device__ __forceinline__ uint32_t quad_swap(uint32_t v)
-{
-    return static_cast<uint32_t>(__shfl_xor(static_cast<int>(v), 16));
-}
-__device__ __forceinline__ ArithF32::Acc quad_swap(const ArithF32::Acc &v)
-{
-    return ArithF32::Acc{__shfl_xor(v.P, 16), __shfl_xor(v.Q, 16)};
-}
-__device__ __forceinline__ ArithF64::Acc quad_swap(const ArithF64::Acc &v)
-{
-    return ArithF64::Acc{__shfl_xor(v.P, 16), __shfl_xor(v.Q, 16)};
-}
-
-// One half of a check row, run-time length dh <= D, as the straight-line
-// body of length D: this lane owns dh edges of the row (the first half, or
-// the second), its partner lane the other half.  Slots j >= dh are
-// dummies: they enter as q = +inf, whose terms are the exact identity of the
-// combination (t = 1, u = 0) with a + sign; they
-// read the +inf posterior word and this thread's dummy slot, and write only
-// to the dummy slot.  All of the half row's offsets and loads are issued
-// before its arithmetic.  The forward pass parks (part of) a_k in the edge's
-// own r slot (free once q_k is formed, owned by this lane alone) instead of
-// a register array; after the partner's half combination and sign are
-// exchanged, the backward pass reads a_k back and overwrites the slot with
-// the new message.
-// TAIL: the caller has checked that every lane of the wave has dh >= D - 1,
-// so only the last slot can be a dummy.
-template <class A, int D, bool PAR, bool TAIL, class Row>
-__device__ __forceinline__ void fused_half_row(const Row &row, int dh, uint32_t s, Slots sl,
-                                               uint32_t &parity)
+// One half of a check row of each lane, D slots.  All loads are issued before
+// the arithmetic.  PAR: `odd` is set if a row of the wavefront is unsatisfied
+// by the decision [L < 0] that the gathered posteriors hold (one comparison
+// per slot; the parities are lane masks in scalar registers).
+template <class A, int D, bool PAR, bool POS>
+__device__ __forceinline__ void half_row(const Quad *tab, const Messages<typename A::T, D, POS> &msg, bool &odd)
 {
     using T = typename A::T;
-    typename A::Acc p[D];
-    typename A::Keep kp[D];
-    typename A::Acc acc = A::identity();
-    uint32_t sign = 0, par = 0;
-    uint32_t ri[D], ci[D];
-#pragma unroll
-    for (int j = 0; j < D; ++j)
-        slot_offsets(row, j, (TAIL && j < D - 1) || j < dh, sl.dslot, sl.inf_off, ri[j], ci[j]);
+    Addresses<T, D> ci;
+    ci.load(tab, 64);
     T lv[D], rv[D];
 #pragma unroll
-    for (int j = 0; j < D; ++j) {
-        lv[j] = lds_ld<T>(s, ci[j]);
-        rv[j] = lds_ld<T>(s, ri[j]);
-    }
-    // A dummy edge reads l = +inf; its slot holds a finite value (a parked
-    // term or a clamped message) written by this thread in an earlier
-    // iteration, so q = +inf and the edge adds nothing to the parity.
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-        const T l = lv[j];
-        if constexpr (PAR)
-            par ^= static_cast<uint32_t>(l < T(0));
-        const T q = l - rv[j];
-        typename A::Term a_k;
-        check_forward<A>(q, a_k, p[j], acc, sign);
-        kp[j] = A::keep(a_k);
-        lds_st<T>(s, ri[j], A::park(a_k));
-    }
-    const typename A::Acc s_other = pair_swap(acc);
-    const uint32_t sign_total = sign ^ pair_swap(sign);
-    if constexpr (PAR)
-        parity |= par ^ pair_swap(par);  // a lane may hold several rows: any unsatisfied row counts
-    typename A::Acc sx = A::seed(s_other);
-    // Every parked value is read before the first message is stored: a
-    // dummy's slot then still holds the parked dummy term (kDummyParked,
-    // written by the forward pass), which needs no per-slot select.
-    T pv[D];
+    for (int j = 0; j < D; ++j)
+        rv[j] = lds_ld<T>(msg[j]);
 #pragma unroll
     for (int j = 0; j < D; ++j)
-        pv[j] = lds_ld<T>(s, ri[j]);
+        lv[j] = lds_ld<T>(ci[j]);
+    typename A::Term a[D];
+    typename A::Acc p[D];
+    typename A::Acc acc = A::identity();
+    uint32_t sign = 0;
+    uint64_t par = 0;
 #pragma unroll
-    for (int j = D - 1; j >= 0; --j) {
-        const T parked = pv[j];
-        const typename A::Term a_k = A::unpark(parked, kp[j]);
-        const T r = check_backward<A>(a_k, p[j], sx, sign_total);
-        lds_st<T>(s, ri[j], r);
+    for (int j = 0; j < D; ++j) {
+        if constexpr (PAR)
+            par ^= __ballot(lv[j] < T(0));
+        check_forward<A>(lv[j] - rv[j], a[j], p[j], acc, sign);
+    }
+    typename A::Acc sx = A::seed(lane_swap<32>(acc));
+    const uint32_t sign_total = sign ^ lane_swap<32>(sign);
+    if constexpr (PAR)
+        odd |= some_odd(par);
+#pragma unroll
+    for (int j = D - 1; j >= 0; --j)
+        lds_st<T>(msg[j], check_backward<A>(a[j], p[j], sx, sign_total));
+}
+
+// Minimum state of part of a row: its two smallest magnitudes and the parity
+// of its negative messages.  Which edge holds the smallest needs no index: an
+// edge whose magnitude equals m1 takes m2, and if another edge equals it too,
+// m2 is that value.  NaN magnitudes count as +inf (the comparisons of
+// min_add pass them over).
+template <class T>
+struct Min2 {
+    T m1, m2;
+    uint32_t neg;
+};
+__device__ __forceinline__ float min_of(float a, float b) { return __builtin_fminf(a, b); }
+__device__ __forceinline__ float max_of(float a, float b) { return __builtin_fmaxf(a, b); }
+__device__ __forceinline__ double min_of(double a, double b) { return __builtin_fmin(a, b); }
+__device__ __forceinline__ double max_of(double a, double b) { return __builtin_fmax(a, b); }
+// The second smallest of m1 <= m2 and a (no NaN among them).
+__device__ __forceinline__ float second_of(float m1, float m2, float a)
+{
+    return __builtin_amdgcn_fmed3f(m1, m2, a);
+}
+__device__ __forceinline__ double second_of(double m1, double m2, double a) { return min_of(m2, max_of(m1, a)); }
+template <int M, class T>
+__device__ __forceinline__ void min_merge(Min2<T> &s)
+{
+    const T o1 = lane_swap<M>(s.m1), o2 = lane_swap<M>(s.m2);
+    s.neg ^= lane_swap<M>(s.neg);
+    s.m2 = min_of(max_of(s.m1, o1), min_of(s.m2, o2));
+    s.m1 = min_of(s.m1, o1);
+}
+
+// Messages of D slots of a min-sum row under min_message's rule, spread over
+// two lanes (QUARTERS: four), from q: the correction and the clamp are applied
+// to the row's two minima, and each edge selects one.
+template <class A, int D, bool QUARTERS, class Store>
+__device__ __forceinline__ void min_row(const typename A::T (&q)[D], typename A::T scale, typename A::T offset,
+                                        const Store &store)
+{
+    using T = typename A::T;
+    const T inf = T(__builtin_huge_val());
+    Min2<T> s{inf, inf, 0u};
+    T a[D];
+#pragma unroll
+    for (int j = 0; j < D; ++j) {
+        a[j] = min_of(fabs(q[j]), inf);  // NaN: inf
+        s.m2 = second_of(s.m1, s.m2, a[j]);
+        s.m1 = min_of(s.m1, a[j]);
+        s.neg ^= static_cast<uint32_t>(q[j] < T(0));
+    }
+    if constexpr (QUARTERS)
+        min_merge<16>(s);
+    min_merge<32>(s);
+    auto corrected = [&](T m) {
+        T mag = scale * m - offset;
+        mag = mag > T(0) ? mag : T(0);
+        return mag < T(A::kRmax) ? mag : T(A::kRmax);
+    };
+    const T r1 = corrected(s.m1), r2 = corrected(s.m2);
+#pragma unroll
+    for (int j = 0; j < D; ++j) {
+        const T mag = a[j] == s.m1 ? r2 : r1;
+        const bool neg = (s.neg != 0u) != (q[j] < T(0));
+        store(j, neg ? -mag : mag);
     }
 }
 
-// An exact-length body.  For jobs without early stop (no syndrome), when the
-// wave's half rows are all D or D - 1 long (a wave within one block-row, or
-// across two of close degrees: the common case), one whose slots need no
-// dummy select but the last.  (With the syndrome the same body measured
-// slower on most codes, so early-stop jobs keep the general one.)
-template <class A, int D, bool PAR, class Row>
-__device__ __forceinline__ void fused_row_exact(const Row &row, int dh, uint32_t s, Slots sl,
-                                                uint32_t &parity)
+// half_row under the min-sum rule.
+template <class A, int D, bool PAR, bool POS>
+__device__ __forceinline__ void ms_half_row(const Quad *tab, const Messages<typename A::T, D, POS> &msg, bool &odd,
+                                            typename A::T scale, typename A::T offset)
 {
-    if constexpr (!PAR && D > 1) {
-        if (__all(dh >= D - 1)) {
-            fused_half_row<A, D, PAR, true>(row, dh, s, sl, parity);
+    using T = typename A::T;
+    Addresses<T, D> ci;
+    ci.load(tab, 64);
+    T lv[D], q[D];
+#pragma unroll
+    for (int j = 0; j < D; ++j)
+        q[j] = lds_ld<T>(msg[j]);
+#pragma unroll
+    for (int j = 0; j < D; ++j)
+        lv[j] = lds_ld<T>(ci[j]);
+    uint64_t par = 0;
+#pragma unroll
+    for (int j = 0; j < D; ++j) {
+        if constexpr (PAR)
+            par ^= __ballot(lv[j] < T(0));
+        q[j] = lv[j] - q[j];
+    }
+    if constexpr (PAR)
+        odd |= some_odd(par);
+    min_row<A, D, false>(q, scale, offset, [&](int j, T r) { lds_st<T>(msg[j], r); });
+}
+
+// One quarter of a layered row of each lane (Section II, Algorithm 2, with the
+// layered combination order of spa_math.h), D slots: the quarter combinations
+// are exchanged in two steps, with the sibling quarter and then between the
+// halves, which gives every lane O_i in the same association as the streaming
+// layer kernel; new posteriors are stored at once.  `stride`: quads of one
+// slot quad of the group (4 lanes per row).
+template <class A, int D>
+__device__ __forceinline__ void layered_quarter(const Quad *tab, int stride, bool ms, typename A::T scale,
+                                                typename A::T offset)
+{
+    using T = typename A::T;
+    Addresses<T, D> ci, ri;
+    ci.load(tab, stride);
+    ri.load(tab + quads(D) * stride, stride);
+    T q[D], rv[D];
+#pragma unroll
+    for (int j = 0; j < D; ++j) {
+        q[j] = lds_ld<T>(ci[j]);
+        rv[j] = lds_ld<T>(ri[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < D; ++j)
+        q[j] = q[j] - rv[j];  // +inf for a dummy
+    if (ms) {
+        min_row<A, D, true>(q, scale, offset, [&](int j, T r) {
+            lds_st<T>(ri[j], r);
+            lds_st<T>(ci[j], q[j] + r);
+        });
+        return;
+    }
+    typename A::Term a[D];
+    typename A::Acc p[D];
+    typename A::Acc acc = A::identity();
+    uint32_t sign = 0;
+#pragma unroll
+    for (int j = 0; j < D; ++j)
+        check_forward<A>(q[j], a[j], p[j], acc, sign);
+    const typename A::Acc c_sib = lane_swap<16>(acc);
+    const typename A::Acc c_other = lane_swap<32>(A::merge(acc, c_sib));  // the other half's combination
+    typename A::Acc sx = A::seed(A::merge(c_sib, c_other));
+    const uint32_t sign_half = sign ^ lane_swap<16>(sign);
+    const uint32_t sign_total = sign_half ^ lane_swap<32>(sign_half);
+#pragma unroll
+    for (int j = D - 1; j >= 0; --j) {
+        const T r = check_backward<A>(a[j], p[j], sx, sign_total);
+        lds_st<T>(ri[j], r);
+        lds_st<T>(ci[j], q[j] + r);
+    }
+}
+
+// Exact-length bodies for D in [D, DB], by the group's longest part.
+template <class A, int D, int DB, bool PAR, bool POS, bool MS>
+__device__ __forceinline__ void half_row_dispatch(int d, const Quad *tab, const Quad *pos, uint32_t ra, bool &odd,
+                                                  typename A::T scale, typename A::T offset)
+{
+    if constexpr (D < DB) {
+        if (d != D) {
+            half_row_dispatch<A, D + 1, DB, PAR, POS, MS>(d, tab, pos, ra, odd, scale, offset);
             return;
         }
     }
-    fused_half_row<A, D, PAR, false>(row, dh, s, sl, parity);
+    Messages<typename A::T, D, POS> msg;
+    msg.ra = ra;
+    if constexpr (POS)
+        msg.pos.load(pos, 64);
+    if constexpr (MS)
+        ms_half_row<A, D, PAR, POS>(tab, msg, odd, scale, offset);
+    else
+        half_row<A, D, PAR, POS>(tab, msg, odd);
 }
 
-// Body selection by the wave's largest half length: exact-length bodies for
-// FP32 circulant codes, the hot case; one padded body of length DB for FP64
-// and for CSR codes (fewer instantiations, same results).
-template <class A, int D, int DB, bool PAR, class Row>
-__device__ __forceinline__ void fused_row_dispatch(int hwave, const Row &row, int dh, uint32_t s,
-                                                   Slots sl, uint32_t &parity)
+template <class A, int D, int DB>
+__device__ __forceinline__ void layered_dispatch(int d, const Quad *tab, int stride, bool ms, typename A::T scale,
+                                                 typename A::T offset)
 {
-    constexpr bool exact = std::is_same<A, ArithF32>::value && std::is_same<Row, RowQC>::value;
-    if constexpr (!exact) {
-        fused_half_row<A, DB, PAR, false>(row, dh, s, sl, parity);
-    } else if constexpr (D < DB) {
-        if (hwave == D)
-            fused_row_exact<A, D, PAR>(row, dh, s, sl, parity);
-        else
-            fused_row_dispatch<A, D + 1, DB, PAR>(hwave, row, dh, s, sl, parity);
-    } else {
-        fused_row_exact<A, DB, PAR>(row, dh, s, sl, parity);
+    if constexpr (D < DB) {
+        if (d != D) {
+            layered_dispatch<A, D + 1, DB>(d, tab, stride, ms, scale, offset);
+            return;
+        }
     }
+    layered_quarter<A, D>(tab, stride, ms, scale, offset);
 }
 
-// One quarter of a layered check row (Section II, Algorithm 2, with the
-// layered combination order of spa_math.h): as layered_half_row, over this
-// lane's quarter (run-time length dq <= D); the quarter combinations are
-// exchanged in two steps, with the sibling quarter (lane ^ 16) and then
-// between the halves (lane ^ 32), which gives every lane O_i in the same
-// association as the streaming layer kernel.
-template <class A, int D, class Row>
-__device__ __forceinline__ void layered_quarter_row(const Row &row, int dq, uint32_t s, Slots sl)
+// acc plus a column's messages in ascending row order, D slots (dummies add -0).
+template <class A, int D>
+__device__ __forceinline__ typename A::T column_sum(const Quad *tab, typename A::T acc)
 {
     using T = typename A::T;
-    typename A::Acc p[D];
-    typename A::Keep kp[D];
-    typename A::Acc acc = A::identity();
-    uint32_t sign = 0;
-    uint32_t ri[D], ci[D];
+    if constexpr (D > 0) {
+        Addresses<T, D> ad;
+        ad.load(tab, 64);
+        T rv[D];
 #pragma unroll
-    for (int j = 0; j < D; ++j)
-        slot_offsets(row, j, j < dq, sl.dslot, sl.inf_off, ri[j], ci[j]);
-    T lv[D], rv[D];
+        for (int k = 0; k < D; ++k)
+            rv[k] = lds_ld<T>(ad[k]);
 #pragma unroll
-    for (int j = 0; j < D; ++j) {
-        lv[j] = lds_ld<T>(s, ci[j]);
-        rv[j] = lds_ld<T>(s, ri[j]);
+        for (int k = 0; k < D; ++k)
+            acc += rv[k];
     }
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-        const T q = lv[j] - rv[j];  // +inf for a dummy
-        typename A::Term a_k;
-        check_forward<A>(q, a_k, p[j], acc, sign);
-        kp[j] = A::keep(a_k);
-        lds_st<T>(s, ri[j], A::park(a_k));
-        lds_st<T>(s, ci[j], q);
-    }
-    const typename A::Acc c_sib = quad_swap(acc);
-    const typename A::Acc c_other = pair_swap(A::merge(acc, c_sib));  // the other half's combination
-    typename A::Acc sx = A::seed(A::merge(c_sib, c_other));
-    const uint32_t sign_half = sign ^ quad_swap(sign);
-    const uint32_t sign_total = sign_half ^ pair_swap(sign_half);
-#pragma unroll
-    for (int j = D - 1; j >= 0; --j) {
-        const bool real = j < dq;
-        const T parked = lds_ld<T>(s, ri[j]);  // a dummy's slot is valid; its value may be a later dummy's message
-        const typename A::Term a_k = A::unpark(real ? parked : T(A::kDummyParked), kp[j]);
-        const T r = check_backward<A>(a_k, p[j], sx, sign_total);
-        const T q = lds_ld<T>(s, ci[j]);
-        lds_st<T>(s, ri[j], r);
-        lds_st<T>(s, ci[j], q + r);
-    }
-}
-
-template <class A, int D, int DB, class Row>
-__device__ __forceinline__ void layered_quarter_dispatch(int qwave, const Row &row, int dq,
-                                                         uint32_t s, Slots sl)
-{
-    constexpr bool exact = std::is_same<A, ArithF32>::value && std::is_same<Row, RowQC>::value;
-    if constexpr (!exact) {
-        layered_quarter_row<A, DB>(row, dq, s, sl);
-    } else if constexpr (D < DB) {
-        if (qwave == D)
-            layered_quarter_row<A, D>(row, dq, s, sl);
-        else
-            layered_quarter_dispatch<A, D + 1, DB>(qwave, row, dq, s, sl);
-    } else {
-        layered_quarter_row<A, DB>(row, dq, s, sl);
-    }
-}
-
-// This lane's quarter of a row of degree d: its first position k0 and length.
-__device__ __forceinline__ void quarter_span(int32_t d, int part, int32_t &k0, int32_t &dq)
-{
-    const Quarters Q = quarters(d);
-    k0 = part == 0 ? 0 : part == 1 ? Q.q1 : part == 2 ? Q.h : Q.q3;
-    dq = (part == 0 ? Q.q1 : part == 1 ? Q.h : part == 2 ? Q.q3 : d) - k0;
-}
-
-// One half of a check row under the min-sum rule, flooding or (LAYERED)
-// layered, padded body of length D: each lane keeps the running minimum
-// state of its half, the partner lanes merge theirs, and every real edge gets
-// one select.  k0 is the half's first position in the row (positions identify
-// the smallest message).  Flooding folds the parity of the previous decision
-// into `parity` (as fused_half_row); layered writes L = q + r at once.
-template <class A, int D, bool LAYERED, class Row>
-__device__ __forceinline__ void ms_half_row(const Row &row, int k0, int dh, uint32_t s, Slots sl,
-                                            uint32_t &parity, typename A::T scale, typename A::T offset)
-{
-    using T = typename A::T;
-    T q[D];
-    MinState<T> st;
-    min_init(st);
-    uint32_t par = 0;
-    // dummy edges enter as q = +inf, which leaves the minimum state
-    // unchanged, and store their messages in this thread's dummy slot; they
-    // read (and, layered, write back) the +inf posterior word, as in
-    // fused_half_row: a min-sum message is clamped too, so the dummy slot
-    // always holds a finite value
-    uint32_t ri[D], ci[D];
-#pragma unroll
-    for (int j = 0; j < D; ++j)
-        slot_offsets(row, j, j < dh, sl.dslot, sl.inf_off, ri[j], ci[j]);
-    T lv[D], rv[D];
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-        lv[j] = lds_ld<T>(s, ci[j]);
-        rv[j] = lds_ld<T>(s, ri[j]);
-    }
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-        if (!LAYERED)
-            par ^= static_cast<uint32_t>(lv[j] < T(0));
-        q[j] = lv[j] - rv[j];
-        min_add(st, q[j], k0 + j);
-    }
-    const T o_m1 = pair_swap(st.m1), o_m2 = pair_swap(st.m2);
-    const int32_t o_idx = static_cast<int32_t>(pair_swap(static_cast<uint32_t>(st.idx)));
-    const uint32_t o_neg = pair_swap(st.neg);
-    min_merge(st, o_m1, o_m2, o_idx, o_neg);
-    if (!LAYERED)
-        parity |= par ^ pair_swap(par);
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-        const T r = min_message<A>(st, q[j], k0 + j, scale, offset);
-        lds_st<T>(s, ri[j], r);
-        if (LAYERED)
-            lds_st<T>(s, ci[j], q[j] + r);
-    }
-}
-
-// Column sum L = Lch + sum of r in ascending row order, run-time degree dv <= D
-// (dummy edges read a valid word and are not added).  SAFE0: every table
-// slot up to D - 1 past the column's start is readable and decodes to a valid
-// offset (the circulant tables in LDS end with kColSpare zero words), so all
-// D slots are read unconditionally at constant offsets; otherwise dummies
-// read offset 0.  edge(k) is the byte offset of the column's k-th message.
-template <class A, int D, bool SAFE0, bool FULL, class Edge>
-__device__ __forceinline__ typename A::T fused_col(const Edge &edge, int dv, typename A::T acc,
-                                                   uint32_t s)
-{
-    using T = typename A::T;
-    static_assert(!SAFE0 || D <= kColSpare, "column body longer than the spare words cover");
-    T rv[D > 0 ? D : 1];
-#pragma unroll
-    for (int k = 0; k < D; ++k)
-        rv[k] = SAFE0 || FULL ? lds_ld<T>(s, edge(k)) : lds_ld<T>(s, k < dv ? edge(k) : 0u);
-#pragma unroll
-    for (int k = 0; k < D; ++k)
-        acc = FULL || k < dv ? acc + rv[k] : acc;
     return acc;
 }
-
-template <class A, int D, bool SAFE0, class Edge>
-__device__ __forceinline__ typename A::T fused_col_dispatch(int dwave, const Edge &edge, int dv, typename A::T acc,
-                                                            uint32_t s)
+constexpr int kColExact = 16;  // longer columns run in steps of four slots
+template <class A, int D>
+__device__ __forceinline__ typename A::T column_dispatch(int d, const Quad *tab, typename A::T acc)
 {
-    using T = typename A::T;
-    if constexpr (!std::is_same<A, ArithF32>::value) {
-        for (int k = 0; k < dv; ++k)
-            acc += lds_ld<T>(s, edge(k));
-        return acc;
-    } else if constexpr (D <= kColSpare) {
-        if (dwave == D) {
-            // FULL: every column of the wave has degree D (no slot to skip)
-            if (__all(dv == D))
-                return fused_col<A, D, SAFE0, true>(edge, dv, acc, s);
-            return fused_col<A, D, SAFE0, false>(edge, dv, acc, s);
-        }
-        return fused_col_dispatch<A, D + 1, SAFE0>(dwave, edge, dv, acc, s);
+    if constexpr (D <= kColExact) {
+        if (d == D)
+            return column_sum<A, D>(tab, acc);
+        return column_dispatch<A, D + 1>(d, tab, acc);
     } else {
-        for (int k = 0; k < dv; ++k)
-            acc += lds_ld<T>(s, edge(k));
+        for (int i = 0; i < quads(d); ++i)
+            acc = column_sum<A, 4>(tab + i * 64, acc);
         return acc;
     }
 }
 
-// Places of one frame's data in LDS, for the launch.
-struct FrameView {
-    uint32_t s;               // the frame's LDS address (posteriors at offset 0)
-    uint32_t r0;              // byte offset of the messages
-    const Lds<int32_t> *tab;  // the code's tables (raw QC tables, then the views below)
-    Slots slots;
-};
+// Kernel instances: one for any batch, and three compiled with one schedule
+// and rule only, in the padded message order, for batches whose jobs all allow
+// it (FP32).
+enum Instance { kAnyJob = 0, kFlood = 1, kLayered = 2, kMinSum = 3 };
 
-// Messages r start at 0 (before the first iteration, or pass, there are
-// none), and so does this thread's dummy slot: the first iteration then
-// forms q = L - 0 = L exactly, as the streaming kernels' first iteration,
-// with the same code as every later one.
-template <class T>
-__device__ __forceinline__ void start_messages(const Code &c, const FrameView &fv)
+// A frame's posteriors (the channel values), the dummies' constants and its
+// messages, which start at 0: the first iteration then forms q = L - 0 = L
+// exactly, as the streaming kernels' first iteration, with the same code as
+// every later one.
+template <class A>
+__device__ __forceinline__ void start_frame(const Code &c, const typename A::T *llr, int32_t r_words)
 {
-    Lds<T> *sR = lds_at<T>(fv.s + fv.r0);
-    for (int e = static_cast<int>(threadIdx.x); e < c.E; e += static_cast<int>(blockDim.x))
+    using T = typename A::T;
+    const int tid = static_cast<int>(threadIdx.x), NT = static_cast<int>(blockDim.x);
+    const int32_t n = c.n;
+    Lds<T> *sL = lds_at<T>(0);
+    for (int j = tid; j < n; j += NT)
+        sL[j] = llr[j] * T(A::kIn);
+    if (tid == 0) {
+        sL[n + kInfWord] = T(__builtin_huge_val());
+        sL[n + kMinusZeroWord] = T(-0.0);
+        sL[n + kJunkWord] = T(0);
+    }
+    Lds<T> *sR = sL + fused_first_message(n);
+    for (int e = tid; e < r_words; e += NT)
         sR[e] = T(0);
-    lds_st<T>(fv.s, fv.slots.dslot, T(0));
+    __syncthreads();
 }
 
-// QC table views in LDS (raw tables of `words` words first):
-//   [words, +nblocks)             row view: pack word of block b
-//   [.., +mb)                     brow_order
-//   [.., +nblocks)                column view: r0 + tsize * Z * b for block-column slot w
-//   [.., +kColSpare)              zero words
-// Kernel instances: one for any batch, and two compiled with one schedule's
-// sum-product rows on circulant views only (no min-sum, no CSR rows, no
-// other schedule), for batches whose jobs all allow it.
-enum Instance { kAnyJob = 0, kFloodQC = 1, kLayeredQC = 2, kMinSumQC = 3 };
-
-// QCF: every job of the launch is sum-product flooding on a circulant view
-// (no min-sum or CSR rows compiled in); MSQ: every job is min-sum flooding on
-// a circulant view (no sum-product or CSR rows compiled in).
-template <class A, int DB, bool QCF = false, bool MSQ = false>
-__device__ __forceinline__ int32_t decode_frame(const Code &c, const Job &job, int64_t f, const FrameView &fv, Vote &vote)
+// One frame on the flooding schedule; returns the iterations it ran.
+template <class A, int DB, Instance INST>
+__device__ __forceinline__ int32_t decode_frame(const Code &c, const Job &job, int64_t f, Vote &vote)
 {
     using T = typename A::T;
     constexpr uint32_t TS = sizeof(T);
-    const int tid = static_cast<int>(threadIdx.x), NT = static_cast<int>(blockDim.x);
-    const int32_t m = c.m, n = c.n, Z = c.Z;
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int lane = static_cast<int>(threadIdx.x & 63), nwaves = static_cast<int>(blockDim.x >> 6);
+    const int32_t n = c.n, col_groups = (n + 63) / 64;
     const T *llr = static_cast<const T *>(job.llr) + f * n;
-    const uint32_t s = fv.s;
-    Lds<T> *sL = lds_at<T>(s);
-    const Lds<int32_t> *rbs = fv.tab;
-    const Lds<int32_t> *cbs = fv.tab + (c.mb + 1) + 2 * c.nblocks;
-    const Lds<uint32_t> *pack = reinterpret_cast<const Lds<uint32_t> *>(fv.tab + c.words);
-    const Lds<int32_t> *border = fv.tab + c.words + c.nblocks;
-    const Lds<uint32_t> *cpack = reinterpret_cast<const Lds<uint32_t> *>(border + c.mb);
-    const uint32_t z_t = TS * static_cast<uint32_t>(Z);
-
-    for (int j = tid; j < n; j += NT)
-        sL[j] = llr[j] * T(A::kIn);
-    start_messages<T>(c, fv);
-    __syncthreads();
+    Lds<T> *sL = lds_at<T>(0);
+    const Quad *row_tab = reinterpret_cast<const Quad *>(c.row_tab) + lane;
+    const Quad *row_pos = reinterpret_cast<const Quad *>(c.row_pos) + lane;
+    const Quad *col_tab = reinterpret_cast<const Quad *>(c.col_tab) + lane;
+    const uint32_t r0 = TS * static_cast<uint32_t>(fused_first_message(n) + lane);
+    start_frame<A>(c, llr, c.r_words);
 
     const bool es = (job.flags & LDPC_EARLY_STOP) != 0;
-    const bool ms = MSQ || (!QCF && (job.flags & LDPC_MIN_SUM) != 0);
-    const T ms_scale = static_cast<T>(job.ms_scale), ms_offset = static_cast<T>(job.ms_offset * A::kIn);
-    int32_t it = job.max_iter;
+    const bool ms = INST == kMinSum || (INST == kAnyJob && (job.flags & LDPC_MIN_SUM) != 0);
+    const bool pos = INST == kAnyJob && c.row_pos != nullptr;
+    const T scale = static_cast<T>(job.ms_scale), offset = static_cast<T>(job.ms_offset * A::kIn);
     for (int32_t t = 1; t <= job.max_iter; ++t) {
-        uint32_t parity = 0;
-        // two lanes per check row: in each wavefront, lane l < 32 takes the
-        // first half of slot rb + l and lane l + 32 its second half
-        const int lane = tid & 63, half = lane >> 5;
-        for (int rb = (tid >> 6) * 32; rb < m; rb += (NT >> 6) * 32) {
-            const int dwave = c.row_gmax[__builtin_amdgcn_readfirstlane(rb) >> 5];
-            const int sr = rb + (lane & 31);
-            if (dwave == 0 || sr >= m)
+        bool odd = false;
+        for (int g = wave; g < c.row_groups; g += nwaves) {
+            // group word 0: message slots before the group (16 bits), its longest half; word 1: first quad
+            const int32_t w = c.row_grp[2 * g], first = c.row_grp[2 * g + 1];
+            const int d = w >> 16;
+            const uint32_t ra = r0 + TS * 64u * static_cast<uint32_t>(w & 0xffff);
+            const Quad *tab = row_tab + static_cast<int64_t>(first) * 64;
+            const Quad *pt = row_pos + static_cast<int64_t>(first) * 64;
+            if (d == 0)
                 continue;
-            const int hwave = (dwave + 1) >> 1;
-            if constexpr (QCF) {
-                // the half row's first block, length and row in one word
-                const uint32_t w = c.half_rows[2 * sr + half];
-                const uint32_t bk = w & 0x1fffu, r = w >> 19;
-                const int32_t dh = static_cast<int32_t>((w >> 13) & 63u);
-                const RowQC row{TS * r, z_t, fv.r0 + z_t * bk, pack + bk};
-                if (es)
-                    fused_row_dispatch<A, 1, DB / 2, true>(hwave, row, dh, s, fv.slots, parity);
-                else
-                    fused_row_dispatch<A, 1, DB / 2, false>(hwave, row, dh, s, fv.slots, parity);
-            } else if (c.qc) {
-                const int32_t si = div_z(sr, c.zmagic);
-                const int32_t r = sr - si * Z;
-                const int32_t i = border[si];
-                const int32_t b0 = rbs[i], d = rbs[i + 1] - b0, h = (d + 1) >> 1;
-                const int32_t k0 = half ? h : 0, dh = half ? d - h : h;
-                const RowQC row{TS * static_cast<uint32_t>(r), z_t, fv.r0 + z_t * static_cast<uint32_t>(b0 + k0),
-                                pack + b0 + k0};
-                if (ms)
-                    ms_half_row<A, DB / 2, false>(row, k0, dh, s, fv.slots, parity, ms_scale, ms_offset);
-                else if constexpr (!MSQ) {
-                    if (es)
-                        fused_row_dispatch<A, 1, DB / 2, true>(hwave, row, dh, s, fv.slots, parity);
+            if (ms) {
+                if constexpr (INST == kMinSum || INST == kAnyJob) {
+                    if (INST == kAnyJob && pos)
+                        half_row_dispatch<A, DB / 2, DB / 2, true, true, true>(d, tab, pt, ra, odd, scale, offset);
                     else
-                        fused_row_dispatch<A, 1, DB / 2, false>(hwave, row, dh, s, fv.slots, parity);
+                        half_row_dispatch<A, 1, DB / 2, true, false, true>(d, tab, pt, ra, odd, scale, offset);
                 }
-            } else if constexpr (!MSQ) {
-                const int32_t e0 = c.row_ptr[sr], d = c.row_ptr[sr + 1] - e0, h = (d + 1) >> 1;
-                const int32_t k0 = half ? h : 0, dh = half ? d - h : h;
-                const RowCSR<TS> row{fv.r0 + TS * static_cast<uint32_t>(e0 + k0), c.col_idx + e0 + k0};
-                if (ms)
-                    ms_half_row<A, DB / 2, false>(row, k0, dh, s, fv.slots, parity, ms_scale, ms_offset);
+            } else if constexpr (INST != kMinSum) {
+                if (INST == kAnyJob && pos)
+                    half_row_dispatch<A, DB / 2, DB / 2, true, true, false>(d, tab, pt, ra, odd, scale, offset);
                 else if (es)
-                    fused_row_dispatch<A, 1, DB / 2, true>(hwave, row, dh, s, fv.slots, parity);
+                    half_row_dispatch<A, 1, DB / 2, true, false, false>(d, tab, pt, ra, odd, scale, offset);
                 else
-                    fused_row_dispatch<A, 1, DB / 2, false>(hwave, row, dh, s, fv.slots, parity);
+                    half_row_dispatch<A, 1, DB / 2, false, false, false>(d, tab, pt, ra, odd, scale, offset);
             }
         }
-        // The syndrome of x^(t-1) is formed only under early stop (min-sum
-        // rows form it always, unused without).
+        // The syndrome of x^(t-1), formed by the rows just run.
         if (es) {
-            if (!vote.any(parity)) {  // a codeword: stop at t-1, keep L^(t-1)
-                it = t - 1;
-                break;
-            }
+            if (!vote.any(odd))  // a codeword: stop at t-1, keep L^(t-1)
+                return t - 1;
         } else {
             __syncthreads();
         }
-        for (int j = tid; j < n; j += NT) {
-            const int dwave = c.col_gmax[__builtin_amdgcn_readfirstlane(j) >> 6];
-            const T acc = llr[j] * T(A::kIn);
-            T v;
-            if (QCF || MSQ || c.qc) {
-                const int32_t bj = div_z(j, c.zmagic);
-                const uint32_t cc_t = TS * static_cast<uint32_t>(j - bj * Z);
-                const int32_t k0 = cbs[bj];
-                auto edge = [&](int k) { return cpack[k0 + k] + cc_t; };
-                v = fused_col_dispatch<A, 0, true>(dwave, edge, cbs[bj + 1] - k0, acc, s);
-            } else {
-                const int32_t k0 = c.col_ptr[j];
-                auto edge = [&](int k) { return fv.r0 + TS * static_cast<uint32_t>(c.col_edge[k0 + k]); };
-                v = fused_col_dispatch<A, 0, false>(dwave, edge, c.col_ptr[j + 1] - k0, acc, s);
-            }
-            sL[j] = v;
+        for (int g = wave; g < col_groups; g += nwaves) {
+            const int j = g * 64 + lane;
+            T acc = T(0);
+            if (j < n)
+                acc = llr[j] * T(A::kIn);
+            const int32_t d = c.col_grp[2 * g], first = c.col_grp[2 * g + 1];  // longest column, first quad
+            const T v = column_dispatch<A, 0>(d, col_tab + static_cast<int64_t>(first) * 64, acc);
+            if (j < n)
+                sL[j] = v;
         }
         __syncthreads();
     }
-    return it;
+    return job.max_iter;
 }
 
-// One frame under the layered schedule: check rows are visited in ascending
-// order, one layer at a time (QC codes: one block-row, Z rows; other codes:
-// the code's layer table), the rows of a layer in parallel with two lanes
-// each and a workgroup barrier between layers.  With early stop the syndrome
-// of [L < 0] is tested before the first pass and after every pass but the
-// last.  Each row's arithmetic is the plain layered path's, bit for bit.
-// QCL: every job of the launch is sum-product layered on a circulant view
-// (no min-sum or CSR rows compiled in).
-template <class A, int DB, bool QCL = false>
-__device__ __forceinline__ int32_t decode_frame_layered(const Code &c, const Job &job, int64_t f,
-                                                        const FrameView &fv, Vote &vote)
+// One frame on the layered schedule: the layers in order, the rows of a layer
+// in parallel with four lanes each and a workgroup barrier between layers.
+// With early stop the syndrome of [L < 0] is tested before the first pass and
+// after every pass but the last.  Each row's arithmetic is the plain layered
+// path's, bit for bit.  Returns the passes run.
+template <class A, int DB, Instance INST>
+__device__ __forceinline__ int32_t decode_frame_layered(const Code &c, const Job &job, int64_t f, Vote &vote)
 {
     using T = typename A::T;
-    constexpr uint32_t TS = sizeof(T);
-    const int tid = static_cast<int>(threadIdx.x), NT = static_cast<int>(blockDim.x);
-    const int lane = tid & 63, half = lane >> 5, wave = tid >> 6, nwaves = NT >> 6;
-    const int32_t m = c.m, n = c.n, Z = c.Z;
-    const T *llr = static_cast<const T *>(job.llr) + f * n;
-    const uint32_t s = fv.s;
-    Lds<T> *sL = lds_at<T>(s);
-    const Lds<int32_t> *rbs = fv.tab;
-    const Lds<uint32_t> *pack = reinterpret_cast<const Lds<uint32_t> *>(fv.tab + c.words);
-    const uint32_t z_t = TS * static_cast<uint32_t>(Z);
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int lane = static_cast<int>(threadIdx.x & 63), nwaves = static_cast<int>(blockDim.x >> 6);
+    const T *llr = static_cast<const T *>(job.llr) + f * c.n;
+    start_frame<A>(c, llr, c.E);
 
-    for (int j = tid; j < n; j += NT)
-        sL[j] = llr[j] * T(A::kIn);
-    start_messages<T>(c, fv);
-    __syncthreads();
-
-    // View of one half of row sr (natural order).
-    auto qc_half = [&](int32_t i, int32_t r, int32_t &d, int32_t &k0, int32_t &dh) {
-        const int32_t b0 = rbs[i];
-        d = rbs[i + 1] - b0;
-        const int32_t h = (d + 1) >> 1;
-        k0 = half ? h : 0;
-        dh = half ? d - h : h;
-        return RowQC{TS * static_cast<uint32_t>(r), z_t, fv.r0 + z_t * static_cast<uint32_t>(b0 + k0), pack + b0 + k0};
-    };
-
-    // 1 if some row is unsatisfied by [sL < 0]: each lane takes one half of a
-    // row, partner lanes combine their parities.  A wavefront stops at its
-    // first group of 32 rows holding an unsatisfied one (the answer is then
-    // known; in most passes that is the first group).
-    auto unsatisfied = [&]() -> int {
-        uint32_t bad = 0;
-        for (int rb = wave * 32; rb < m && !__any(static_cast<int>(bad)); rb += nwaves * 32) {
-            const int sr = rb + (lane & 31);
-            uint32_t par = 0;
-            if (sr < m) {
-                if (QCL || c.qc) {
-                    const int32_t si = div_z(sr, c.zmagic);
-                    int32_t d, k0, dh;
-                    const RowQC row = qc_half(si, sr - si * Z, d, k0, dh);
-                    for (int32_t k = 0; k < dh; ++k) {
-                        uint32_t ri, ci;
-                        row.offsets(k, ri, ci);
-                        par ^= static_cast<uint32_t>(lds_ld<T>(s, ci) < T(0));
-                    }
-                } else {
-                    const int32_t e0 = c.row_ptr[sr], d = c.row_ptr[sr + 1] - e0, h = (d + 1) >> 1;
-                    const int32_t k0 = half ? h : 0, dh = half ? d - h : h;
-                    for (int32_t k = 0; k < dh; ++k)
-                        par ^= static_cast<uint32_t>(sL[c.col_idx[e0 + k0 + k]] < T(0));
-                }
+    // Whether some row is unsatisfied by the decision [L < 0], from the
+    // flooding table.  A wavefront stops at its first group of 32 rows holding
+    // one (the answer is then known; in most passes that is the first group).
+    auto unsatisfied = [&]() -> int32_t {
+        bool odd = false;
+        for (int g = wave; g < c.row_groups && !odd; g += nwaves) {
+            const int32_t w = c.row_grp[2 * g], first = c.row_grp[2 * g + 1];
+            const Quad *tab = reinterpret_cast<const Quad *>(c.row_tab) + (static_cast<int64_t>(first) * 64 + lane);
+            uint64_t par = 0;
+            for (int i = 0; i < quads(w >> 16); ++i) {
+                Addresses<T, 4> ci;
+                ci.load(tab + i * 64, 64);
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    par ^= __ballot(lds_ld<T>(ci[k]) < T(0));
             }
-            bad |= par ^ pair_swap(par);
+            odd = some_odd(par);
         }
-        return vote.any(bad);
+        return vote.any(odd);
     };
 
     const bool es = (job.flags & LDPC_EARLY_STOP) != 0;
-    const bool ms = !QCL && (job.flags & LDPC_MIN_SUM) != 0;
-    const T ms_scale = static_cast<T>(job.ms_scale), ms_offset = static_cast<T>(job.ms_offset * A::kIn);
-    uint32_t no_parity = 0;
-    int32_t it = job.max_iter;
-    if (es && !unsatisfied()) {
-        it = 0;
-    } else {
-        for (int32_t t = 1; t <= job.max_iter; ++t) {
-            // min-sum rows: two lanes each (32 rows per wavefront); sum-product
-            // rows: four lanes each (16 rows per wavefront)
-            const int rows_per_wave = ms ? 32 : 16;
-            const int part = lane >> 4;
-            if (QCL || c.qc) {
-                for (int32_t i = 0; i < c.mb; ++i) {
-                    for (int rb = wave * rows_per_wave; rb < Z; rb += nwaves * rows_per_wave) {
-                        const int r = rb + (lane & (rows_per_wave - 1));
-                        if (r >= Z)
-                            continue;
-                        if (ms) {
-                            int32_t d, k0, dh;
-                            const RowQC row = qc_half(i, r, d, k0, dh);
-                            if (d > 0)
-                                ms_half_row<A, DB / 2, true>(row, k0, dh, s, fv.slots, no_parity, ms_scale,
-                                                             ms_offset);
-                        } else {
-                            const int32_t b0 = rbs[i], d = rbs[i + 1] - b0;
-                            if (d == 0)
-                                continue;
-                            int32_t k0, dq;
-                            quarter_span(d, part, k0, dq);
-                            const RowQC row{TS * static_cast<uint32_t>(r), z_t,
-                                            fv.r0 + z_t * static_cast<uint32_t>(b0 + k0), pack + b0 + k0};
-                            layered_quarter_dispatch<A, 1, DB / 4>(quarters(d).q1, row, dq, s, fv.slots);
-                        }
-                    }
-                    __syncthreads();
-                }
-            } else {
-                for (int32_t l = 0; l < c.nlayers; ++l) {
-                    const int32_t row0 = c.layer_ptr[l], rows = c.layer_ptr[l + 1] - row0;
-                    for (int rb = wave * rows_per_wave; rb < rows; rb += nwaves * rows_per_wave) {
-                        const int slot = rb + (lane & (rows_per_wave - 1));
-                        if (slot >= rows)
-                            continue;
-                        const int32_t e0 = c.row_ptr[row0 + slot], d = c.row_ptr[row0 + slot + 1] - e0;
-                        if (d == 0)
-                            continue;
-                        if (ms) {
-                            const int32_t h = (d + 1) >> 1;
-                            const int32_t k0 = half ? h : 0, dh = half ? d - h : h;
-                            const RowCSR<TS> row{fv.r0 + TS * static_cast<uint32_t>(e0 + k0), c.col_idx + e0 + k0};
-                            ms_half_row<A, DB / 2, true>(row, k0, dh, s, fv.slots, no_parity, ms_scale, ms_offset);
-                        } else {
-                            int32_t k0, dq;
-                            quarter_span(d, part, k0, dq);
-                            const RowCSR<TS> row{fv.r0 + TS * static_cast<uint32_t>(e0 + k0), c.col_idx + e0 + k0};
-                            layered_quarter_dispatch<A, 1, DB / 4>(quarters(d).q1, row, dq, s, fv.slots);
-                        }
-                    }
-                    __syncthreads();
-                }
+    const bool ms = INST == kAnyJob && (job.flags & LDPC_MIN_SUM) != 0;
+    const T scale = static_cast<T>(job.ms_scale), offset = static_cast<T>(job.ms_offset * A::kIn);
+    if (es && !unsatisfied())
+        return 0;
+    for (int32_t t = 1; t <= job.max_iter; ++t) {
+        int32_t end = c.lay_ptr[0];
+        for (int32_t l = 0; l < c.nlayers; ++l) {
+            const int32_t begin = end;
+            end = c.lay_ptr[l + 1];
+            for (int g = begin + wave; g < end; g += nwaves) {
+                const int32_t w = c.lay_grp[2 * g], first = c.lay_grp[2 * g + 1];
+                const int rows = w & 0xff, d = w >> 8;  // word 1: first quad
+                if ((lane & 15) < rows && d > 0)
+                    layered_dispatch<A, 1, DB / 4>(
+                        d, reinterpret_cast<const Quad *>(c.lay_tab) + (first + (lane >> 4) * rows + (lane & 15)),
+                        4 * rows, ms, scale, offset);
             }
-            if (es && t < job.max_iter && !unsatisfied()) {
-                it = t;
-                break;
-            }
+            __syncthreads();
         }
+        if (es && t < job.max_iter && !unsatisfied())
+            return t;
     }
-    return it;
+    return job.max_iter;
 }
 
 // Bits, iteration count and posterior of a decoded frame (stopped after `it`
 // iterations; one that ran none reports the caller's LLRs bit-exactly).
 template <class A>
-__device__ __forceinline__ void write_frame(const Code &c, const Job &job, int64_t f, int32_t it, const FrameView &fv)
+__device__ __forceinline__ void write_frame(const Code &c, const Job &job, int64_t f, int32_t it)
 {
     using T = typename A::T;
     const int tid = static_cast<int>(threadIdx.x), NT = static_cast<int>(blockDim.x);
     const int32_t n = c.n;
-    const Lds<T> *sL = lds_at<T>(fv.s);
+    const Lds<T> *sL = lds_at<T>(0);
     const T *llr = static_cast<const T *>(job.llr) + f * n;
     uint8_t *bits = job.bits + f * n;
     T *post = job.post ? static_cast<T *>(job.post) + f * n : nullptr;
@@ -872,289 +672,6 @@ __device__ __forceinline__ void write_frame(const Code &c, const Job &job, int64
     }
     if (tid == 0)
         job.iters[f] = it;
-}
-
-// The code's tables in LDS (see decode_frame): the raw QC tables, then the
-// row view (pack words), the block-row order, the column view (message
-// offsets from a frame's base) and the spare zero words.  Ends with a
-// workgroup barrier.
-template <uint32_t TS>
-__device__ __forceinline__ void load_tables(const Code &c, Lds<int32_t> *sTab, uint32_t r0)
-{
-    for (int w = threadIdx.x; w < c.words; w += blockDim.x)
-        sTab[w] = c.tab[w];
-    if (c.qc) {
-        const uint32_t Z = static_cast<uint32_t>(c.Z);
-        const int32_t *bcol = c.tab + (c.mb + 1);
-        const int32_t *bsh = bcol + c.nblocks;
-        for (int w = threadIdx.x; w < c.nblocks; w += blockDim.x)
-            sTab[c.words + w] = static_cast<int32_t>((TS * static_cast<uint32_t>(bcol[w]) * Z) |
-                                                     ((TS * static_cast<uint32_t>(bsh[w])) << 16));
-        for (int w = threadIdx.x; w < c.mb; w += blockDim.x)
-            sTab[c.words + c.nblocks + w] = c.brow_order[w];
-        // the column phase's view: block-column slot w holds block cb[w]
-        const int32_t *cb = bsh + c.nblocks + (c.nb + 1);
-        for (int w = threadIdx.x; w < c.nblocks; w += blockDim.x)
-            sTab[c.words + c.nblocks + c.mb + w] = static_cast<int32_t>(r0 + TS * Z * static_cast<uint32_t>(cb[w]));
-        if (threadIdx.x < kColSpare)  // readable words past the column table's end
-            sTab[c.words + 2 * c.nblocks + c.mb + threadIdx.x] = 0;
-    }
-    __syncthreads();
-}
-
-// ---------------------------------------------------------------------------
-// Two frames per workgroup (flooding, sum-product): every lane runs its half
-// rows and columns for two frames of one job at once, so the offsets, table
-// reads, dummy handling and loop bookkeeping of a slot serve both frames.
-// Each frame's arithmetic, in its own LDS region, is exactly the one-frame
-// kernel's (and so the plain path's), bit for bit.
-
-// fused_half_row for frames at s0 and s1 (see there).
-template <class A, int D, class Row>
-__device__ __forceinline__ void fused_half_row2(const Row &row, int dh, uint32_t s0,
-                                                uint32_t s1, Slots sl, uint32_t &parity0,
-                                                uint32_t &parity1)
-{
-    using T = typename A::T;
-    typename A::Acc p0[D], p1[D];
-    typename A::Keep kp0[D], kp1[D];
-    typename A::Acc acc0 = A::identity(), acc1 = A::identity();
-    uint32_t sign0 = 0, sign1 = 0, par0 = 0, par1 = 0;
-    uint32_t ri[D], ci[D];
-#pragma unroll
-    for (int j = 0; j < D; ++j)
-        slot_offsets(row, j, j < dh, sl.dslot, sl.inf_off, ri[j], ci[j]);
-    T lv0[D], rv0[D], lv1[D], rv1[D];
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-        lv0[j] = lds_ld<T>(s0, ci[j]);
-        rv0[j] = lds_ld<T>(s0, ri[j]);
-        lv1[j] = lds_ld<T>(s1, ci[j]);
-        rv1[j] = lds_ld<T>(s1, ri[j]);
-    }
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-        par0 ^= static_cast<uint32_t>(lv0[j] < T(0));
-        par1 ^= static_cast<uint32_t>(lv1[j] < T(0));
-        typename A::Term a0, a1;
-        check_forward<A>(lv0[j] - rv0[j], a0, p0[j], acc0, sign0);
-        check_forward<A>(lv1[j] - rv1[j], a1, p1[j], acc1, sign1);
-        kp0[j] = A::keep(a0);
-        kp1[j] = A::keep(a1);
-        lds_st<T>(s0, ri[j], A::park(a0));
-        lds_st<T>(s1, ri[j], A::park(a1));
-    }
-    const typename A::Acc o0 = pair_swap(acc0), o1 = pair_swap(acc1);
-    const uint32_t st0 = sign0 ^ pair_swap(sign0), st1 = sign1 ^ pair_swap(sign1);
-    parity0 |= par0 ^ pair_swap(par0);
-    parity1 |= par1 ^ pair_swap(par1);
-    typename A::Acc x0 = A::seed(o0), x1 = A::seed(o1);
-    // Every parked value is read before the first message is stored: a
-    // dummy's slot then still holds the parked dummy term (kDummyParked,
-    // written by the forward pass), which needs no per-slot select.
-    T v0[D], v1[D];
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-        v0[j] = lds_ld<T>(s0, ri[j]);
-        v1[j] = lds_ld<T>(s1, ri[j]);
-    }
-#pragma unroll
-    for (int j = D - 1; j >= 0; --j) {
-        const typename A::Term a0 = A::unpark(v0[j], kp0[j]);
-        const typename A::Term a1 = A::unpark(v1[j], kp1[j]);
-        const T r0 = check_backward<A>(a0, p0[j], x0, st0);
-        const T r1 = check_backward<A>(a1, p1[j], x1, st1);
-        lds_st<T>(s0, ri[j], r0);
-        lds_st<T>(s1, ri[j], r1);
-    }
-}
-
-template <class A, int D, int DB, class Row>
-__device__ __forceinline__ void fused_row_dispatch2(int hwave, const Row &row, int dh, uint32_t s0,
-                                                    uint32_t s1, Slots sl, uint32_t &parity0,
-                                                    uint32_t &parity1)
-{
-    constexpr bool exact = std::is_same<Row, RowQC>::value;
-    if constexpr (!exact) {
-        fused_half_row2<A, DB>(row, dh, s0, s1, sl, parity0, parity1);
-    } else if constexpr (D < DB) {
-        if (hwave == D)
-            fused_half_row2<A, D>(row, dh, s0, s1, sl, parity0, parity1);
-        else
-            fused_row_dispatch2<A, D + 1, DB>(hwave, row, dh, s0, s1, sl, parity0, parity1);
-    } else {
-        fused_half_row2<A, DB>(row, dh, s0, s1, sl, parity0, parity1);
-    }
-}
-
-// fused_col for frames at s0 and s1.
-template <class A, int D, bool SAFE0, class Edge>
-__device__ __forceinline__ void fused_col2(const Edge &edge, int dv, typename A::T &acc0, typename A::T &acc1,
-                                           uint32_t s0, uint32_t s1)
-{
-    using T = typename A::T;
-    static_assert(!SAFE0 || D <= kColSpare, "column body longer than the spare words cover");
-    T rv0[D > 0 ? D : 1], rv1[D > 0 ? D : 1];
-#pragma unroll
-    for (int k = 0; k < D; ++k) {
-        const uint32_t o = SAFE0 ? edge(k) : (k < dv ? edge(k) : 0u);
-        rv0[k] = lds_ld<T>(s0, o);
-        rv1[k] = lds_ld<T>(s1, o);
-    }
-#pragma unroll
-    for (int k = 0; k < D; ++k) {
-        acc0 = k < dv ? acc0 + rv0[k] : acc0;
-        acc1 = k < dv ? acc1 + rv1[k] : acc1;
-    }
-}
-
-template <class A, int D, bool SAFE0, class Edge>
-__device__ __forceinline__ void fused_col_dispatch2(int dwave, const Edge &edge, int dv, typename A::T &acc0,
-                                                    typename A::T &acc1, uint32_t s0,
-                                                    uint32_t s1)
-{
-    using T = typename A::T;
-    if constexpr (SAFE0 && D <= kColSpare) {
-        if (dwave == D)
-            return fused_col2<A, D, SAFE0>(edge, dv, acc0, acc1, s0, s1);
-        return fused_col_dispatch2<A, D + 1, SAFE0>(dwave, edge, dv, acc0, acc1, s0, s1);
-    } else {
-        for (int k = 0; k < dv; ++k) {
-            const uint32_t o = edge(k);
-            acc0 += lds_ld<T>(s0, o);
-            acc1 += lds_ld<T>(s1, o);
-        }
-    }
-}
-
-// Frames f0 and f0 + 1 of a flooding sum-product job (with has1 false only
-// frame f0: the second region then decodes a copy of it, whose results are
-// not written).  Early stop is per frame: a frame whose decision is a
-// codeword keeps its posteriors from then on (its column updates are
-// skipped) and leaves the loop's work to the other frame.
-template <class A, int DB>
-__device__ __forceinline__ void decode_frame_pair(const Code &c, const Job &job, int64_t f0, bool has1,
-                                                  const FrameView &fv0, const FrameView &fv1, Vote &vote)
-{
-    using T = typename A::T;
-    constexpr uint32_t TS = sizeof(T);
-    const int tid = static_cast<int>(threadIdx.x), NT = static_cast<int>(blockDim.x);
-    const int32_t m = c.m, n = c.n, Z = c.Z;
-    const T *llr0 = static_cast<const T *>(job.llr) + f0 * n;
-    const T *llr1 = has1 ? llr0 + n : llr0;
-    const uint32_t s0 = fv0.s, s1 = fv1.s;
-    Lds<T> *sL0 = lds_at<T>(s0), *sL1 = lds_at<T>(s1);
-    const Lds<int32_t> *rbs = fv0.tab;
-    const Lds<int32_t> *cbs = fv0.tab + (c.mb + 1) + 2 * c.nblocks;
-    const Lds<uint32_t> *pack = reinterpret_cast<const Lds<uint32_t> *>(fv0.tab + c.words);
-    const Lds<int32_t> *border = fv0.tab + c.words + c.nblocks;
-    const Lds<uint32_t> *cpack = reinterpret_cast<const Lds<uint32_t> *>(border + c.mb);
-    const uint32_t z_t = TS * static_cast<uint32_t>(Z);
-
-    for (int j = tid; j < n; j += NT) {
-        sL0[j] = llr0[j] * T(A::kIn);
-        sL1[j] = llr1[j] * T(A::kIn);
-    }
-    start_messages<T>(c, fv0);
-    start_messages<T>(c, fv1);
-    __syncthreads();
-
-    const bool es = (job.flags & LDPC_EARLY_STOP) != 0;
-    int32_t it0 = job.max_iter, it1 = job.max_iter;
-    bool run0 = true, run1 = true;
-    for (int32_t t = 1; t <= job.max_iter; ++t) {
-        uint32_t parity0 = 0, parity1 = 0;
-        const int lane = tid & 63, half = lane >> 5;
-        for (int rb = (tid >> 6) * 32; rb < m; rb += (NT >> 6) * 32) {
-            const int dwave = c.row_gmax[__builtin_amdgcn_readfirstlane(rb) >> 5];
-            const int sr = rb + (lane & 31);
-            if (dwave == 0 || sr >= m)
-                continue;
-            const int hwave = (dwave + 1) >> 1;
-            if (c.qc) {
-                const int32_t si = div_z(sr, c.zmagic);
-                const int32_t r = sr - si * Z;
-                const int32_t i = border[si];
-                const int32_t b0 = rbs[i], d = rbs[i + 1] - b0, h = (d + 1) >> 1;
-                const int32_t k0 = half ? h : 0, dh = half ? d - h : h;
-                const RowQC row{TS * static_cast<uint32_t>(r), z_t, fv0.r0 + z_t * static_cast<uint32_t>(b0 + k0),
-                                pack + b0 + k0};
-                fused_row_dispatch2<A, 1, DB / 2>(hwave, row, dh, s0, s1, fv0.slots, parity0, parity1);
-            } else {
-                const int32_t e0 = c.row_ptr[sr], d = c.row_ptr[sr + 1] - e0, h = (d + 1) >> 1;
-                const int32_t k0 = half ? h : 0, dh = half ? d - h : h;
-                const RowCSR<TS> row{fv0.r0 + TS * static_cast<uint32_t>(e0 + k0), c.col_idx + e0 + k0};
-                fused_row_dispatch2<A, 1, DB / 2>(hwave, row, dh, s0, s1, fv0.slots, parity0, parity1);
-            }
-        }
-        const int unsat0 = vote.any(parity0);
-        const int unsat1 = vote.any(parity1);
-        if (es) {  // as decode_frame, per frame: x^(t-1) a codeword -> stop at t-1, keep L^(t-1)
-            if (run0 && !unsat0) {
-                it0 = t - 1;
-                run0 = false;
-            }
-            if (run1 && !unsat1) {
-                it1 = t - 1;
-                run1 = false;
-            }
-            if (!run0 && !run1)
-                break;
-        }
-        for (int j = tid; j < n; j += NT) {
-            const int dwave = c.col_gmax[__builtin_amdgcn_readfirstlane(j) >> 6];
-            T v0 = llr0[j] * T(A::kIn), v1 = llr1[j] * T(A::kIn);
-            if (c.qc) {
-                const int32_t bj = div_z(j, c.zmagic);
-                const uint32_t cc_t = TS * static_cast<uint32_t>(j - bj * Z);
-                const int32_t k0 = cbs[bj];
-                auto edge = [&](int k) { return cpack[k0 + k] + cc_t; };
-                fused_col_dispatch2<A, 0, true>(dwave, edge, cbs[bj + 1] - k0, v0, v1, s0, s1);
-            } else {
-                const int32_t k0 = c.col_ptr[j];
-                auto edge = [&](int k) { return fv0.r0 + TS * static_cast<uint32_t>(c.col_edge[k0 + k]); };
-                fused_col_dispatch2<A, 0, false>(dwave, edge, c.col_ptr[j + 1] - k0, v0, v1, s0, s1);
-            }
-            if (run0)
-                sL0[j] = v0;
-            if (run1)
-                sL1[j] = v1;
-        }
-        __syncthreads();
-    }
-    uint8_t *bits = job.bits + f0 * n;
-    T *post = job.post ? static_cast<T *>(job.post) + f0 * n : nullptr;
-    for (int j = tid; j < n; j += NT) {
-        const T v = sL0[j];
-        bits[j] = static_cast<uint8_t>(v < T(0));
-        if (post)
-            post[j] = it0 == 0 ? llr0[j] : v * T(A::kOut);
-        if (has1) {
-            const T w = sL1[j];
-            bits[n + j] = static_cast<uint8_t>(w < T(0));
-            if (post)
-                post[n + j] = it1 == 0 ? llr1[j] : w * T(A::kOut);
-        }
-    }
-    if (tid == 0) {
-        job.iters[f0] = it0;
-        if (has1)
-            job.iters[f0 + 1] = it1;
-    }
-}
-
-// Workgroup setup shared by the kernels: the +inf word of each frame's region
-// and the flag words (published by the barriers of load_tables).
-template <class T>
-__device__ __forceinline__ Lds<int32_t> *start_workgroup(const FrameLayout &lay, uint32_t nmax, int frames)
-{
-    Lds<int32_t> *flags = lds_at<int32_t>(lay.t0) - kFlagWords;
-    if (threadIdx.x < kFlagWords)
-        flags[threadIdx.x] = 0;
-    if (threadIdx.x == 0)
-        for (int k = 0; k < frames; ++k)
-            lds_at<T>(static_cast<uint32_t>(k) * lay.span)[nmax] = T(__builtin_huge_val());
-    return flags;
 }
 
 // A launch's items are handed out in one of two ways.  Up to as many items as
@@ -1185,100 +702,56 @@ __device__ __forceinline__ int32_t next_item(const uint32_t *counter, uint32_t d
     return __builtin_amdgcn_readfirstlane(flags[kItemFlag]);
 }
 
-// Batch kernel over frame pairs: flooding sum-product jobs only, item i of a
-// job being its frames 2i and 2i + 1.  Two frames' LDS (qc1944: 152 KB) allow
-// one 512-thread workgroup per CU, so the bodies may use 256 VGPRs (2 waves
-// per SIMD).
-template <class A, int DB>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k_fused_pair(const Batch b, uint32_t *counter)
-{
-    using T = typename A::T;
-    constexpr uint32_t TS = sizeof(T);
-    const FrameLayout lay = frame_layout(b.emax, b.nmax, 0, 0, 0, TS, 2);
-    Lds<int32_t> *sTab = lds_at<int32_t>(lay.t0);
-    const uint32_t nmax = static_cast<uint32_t>(b.nmax);
-    const Slots slots{TS * (nmax + 1 + threadIdx.x), TS * nmax};
-    const FrameView fv0{0u, lay.r0, sTab, slots}, fv1{lay.span, lay.r0, sTab, slots};
-    Lds<int32_t> *flags = start_workgroup<T>(lay, nmax, 2);
-    Vote vote{flags};
-    int cur_code = -1;
-    for (int32_t item = static_cast<int32_t>(blockIdx.x); item < b.nitems;) {
-        const int32_t j = job_of_item(b, item);
-        const Job &job = b.jobs[j];
-        const Code &c = b.codes[job.code];
-        if (job.code != cur_code) {
-            cur_code = job.code;
-            load_tables<TS>(c, sTab, lay.r0);
-        }
-        const int64_t f0 = 2 * static_cast<int64_t>(item - b.begin[j]);
-        decode_frame_pair<A, DB>(c, job, f0, f0 + 1 < job.frames, fv0, fv1, vote);
-        item = next_item(counter, draw_item(counter), b.nitems, flags);
-    }
-}
-
-// Batch kernel.  512-thread workgroups, two per CU for n = 1944 (LDS bound):
-// FP32 bodies are held to 128 VGPRs so both fit (4 waves per SIMD); FP64
-// bodies get 256.
+// Batch kernel.  FP32 bodies are held to 128 VGPRs, so that a CU holds 16
+// wavefronts (4 per SIMD): two 512-thread workgroups for n = 1944, whose LDS
+// admits no third, or one of 1024.  FP64 bodies get 256 VGPRs.
 template <class A>
 constexpr int kFusedWavesPerEU = std::is_same<A, ArithF32>::value ? 4 : 2;
+template <class A>
+constexpr int kFusedMaxThreads = std::is_same<A, ArithF32>::value ? kMaxThreads : kBaseThreads;
 
-template <class A, int DB, int INST = kAnyJob>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(kFusedWavesPerEU<A>))) void k_fused(const Batch b, uint32_t *counter)
+template <class A, int DB, Instance INST = kAnyJob>
+__global__ __launch_bounds__(kFusedMaxThreads<A>) __attribute__((amdgpu_waves_per_eu(kFusedWavesPerEU<A>))) void k_fused(const Batch b, uint32_t *counter)
 {
-    using T = typename A::T;
-    constexpr uint32_t TS = sizeof(T);
-    const FrameLayout lay = frame_layout(b.emax, b.nmax, 0, 0, 0, TS);
-    Lds<int32_t> *sTab = lds_at<int32_t>(lay.t0);
-    const uint32_t nmax = static_cast<uint32_t>(b.nmax);
-    const FrameView fv{0u, lay.r0, sTab, Slots{TS * (nmax + 1 + threadIdx.x), TS * nmax}};
-    Lds<int32_t> *flags = start_workgroup<T>(lay, nmax, 1);
+    Lds<int32_t> *flags = lds_at<int32_t>(b.flags_at);
+    if (threadIdx.x < kFlagWords)
+        flags[threadIdx.x] = 0;  // published by the barrier of start_frame
     Vote vote{flags};
-    int cur_code = -1;
     for (int32_t item = static_cast<int32_t>(blockIdx.x); item < b.nitems;) {
         const int32_t j = job_of_item(b, item);
         const Job &job = b.jobs[j];
         const Code &c = b.codes[job.code];
-        if (job.code != cur_code) {
-            cur_code = job.code;
-            load_tables<TS>(c, sTab, lay.r0);
+        const int32_t f0 = (item - b.begin[j]) * b.frames_per_item;
+        uint32_t drawn = 0;
+        for (int32_t f = f0; f < f0 + b.frames_per_item && f < job.frames; ++f) {
+            if (f > f0)
+                __syncthreads();  // the last frame's posteriors have been read
+            int32_t it;
+            if (INST == kLayered || (INST == kAnyJob && (job.flags & LDPC_LAYERED)))
+                it = decode_frame_layered<A, DB, INST>(c, job, f, vote);
+            else
+                it = decode_frame<A, DB, INST>(c, job, f, vote);
+            if (f == f0)
+                drawn = draw_item(counter);
+            write_frame<A>(c, job, f, it);
         }
-        const int64_t f = item - b.begin[j];
-        int32_t it;
-        if (INST == kLayeredQC || (INST == kAnyJob && (job.flags & LDPC_LAYERED)))
-            it = decode_frame_layered<A, DB, INST == kLayeredQC>(c, job, f, fv, vote);
-        else
-            it = decode_frame<A, DB, INST == kFloodQC, INST == kMinSumQC>(c, job, f, fv, vote);
-        const uint32_t drawn = draw_item(counter);
-        write_frame<A>(c, job, f, it, fv);
         item = next_item(counter, drawn, b.nitems, flags);
     }
 }
 
-// The instance of k_fused that runs every job of the batch: kFloodQC or
-// kLayeredQC when all jobs are sum-product (no LDPC_MIN_SUM) on codes with a
-// circulant view and all take that schedule, kMinSumQC when all are min-sum
-// flooding on such codes, else kAnyJob.
+// The instance of k_fused that runs every job of the batch.
 inline Instance batch_instance(const Batch &b)
 {
-    if (b.njobs == 0)
-        return kAnyJob;
     for (int32_t k = 0; k < b.ncodes; ++k)
-        if (!b.codes[k].qc)
+        if (b.codes[k].row_pos != nullptr)
             return kAnyJob;
     const uint32_t first = b.jobs[0].flags & (LDPC_LAYERED | LDPC_MIN_SUM);
     for (int32_t k = 0; k < b.njobs; ++k)
         if ((b.jobs[k].flags & (LDPC_LAYERED | LDPC_MIN_SUM)) != first)
             return kAnyJob;
-    if (first == LDPC_MIN_SUM)
-        return kMinSumQC;
-    if (first != 0 && first != LDPC_LAYERED)
-        return kAnyJob;  // layered min-sum
-    if (first)
-        return kLayeredQC;
-    for (int32_t k = 0; k < b.ncodes; ++k)  // the flooding instance reads the half-row words
-        if (b.codes[k].half_rows == nullptr)
-            return kAnyJob;
-    return kFloodQC;
+    if (first == 0)
+        return kFlood;
+    return first == LDPC_LAYERED ? kLayered : first == LDPC_MIN_SUM ? kMinSum : kAnyJob;
 }
 
 }  // namespace fused
@@ -1347,25 +820,102 @@ inline ldpc_status launch_shape(const void *fn, size_t lds, int threads, int &pe
 
 }  // namespace fused
 
+namespace fused {
+
+// LDS bytes of a launch, up to and with its flag words.
+inline size_t batch_lds_bytes(const Batch &b, size_t tsize)
+{
+    size_t bytes = 0;
+    for (int32_t i = 0; i < b.njobs; ++i) {
+        const Code &c = b.codes[b.jobs[i].code];
+        bytes = std::max(bytes, lds_bytes(c.n, (b.jobs[i].flags & LDPC_LAYERED) ? c.E : c.r_words, tsize));
+    }
+    return bytes;
+}
+
+// Workgroup size of a one-frame launch whose caller left it at kBaseThreads.
+// A frame's iteration (a layered frame's pass) is a chain of rounds: a
+// wavefront takes 32 check rows at a time (16 of a layer's) and 64 columns.  The unit below is one 32-row group's VALU time on
+// a whole CU (0.20 us for rows of degree 17): a wavefront alone on its SIMD
+// takes 4 of them, and no round less than its latency, about 11 in FP32 and 5
+// in FP64, whose instructions hold the SIMD longer.  k frames on a CU take at
+// least the VALU time of all their rows.  The size with the least (passes
+// over the device) x (time of a frame) is taken; of equals the smallest,
+// which holds more frames at once, or in FP64 with early stop the largest,
+// which ends the long frames of the last pass sooner.  512 threads and this rule,
+// us per call of 10 iterations: one frame of qc n = 648 46.7 and 36.4, of n =
+// 1944 99.1 and 75.8; 64 frames of four codes in a plan 64.9 and 52.0; 1024
+// FP64 frames of n = 504 134 and 110.
+template <class K>
+ldpc_status workgroup_threads(K kern, const Batch &b, size_t tsize, size_t lds, int max_threads, int &threads)
+{
+    const int64_t round = tsize == sizeof(float) ? 11 : 5, col_round = 2;
+    bool stops = false;
+    int widest = 2;  // a layer's few rows leave wider workgroups' wavefronts idle at every barrier
+    for (int32_t i = 0; i < b.njobs; ++i) {
+        const Job &j = b.jobs[i];
+        const Code &c = b.codes[j.code];
+        stops |= (j.flags & LDPC_EARLY_STOP) != 0;
+        widest = std::max(widest, (j.flags & LDPC_LAYERED)
+                                      ? std::max((c.m / std::max(c.nlayers, 1) + 15) / 16, c.n / 256 + 1)
+                                      : max_threads / 64);
+    }
+    int64_t best = -1;
+    for (int w = 2; w * 64 <= max_threads && w <= widest; ++w) {
+        int per_cu = 0, cus = 0;
+        const ldpc_status rc = launch_shape(reinterpret_cast<const void *>(kern), lds, w * 64, per_cu, cus);
+        if (rc != LDPC_OK)
+            return rc;
+        const int64_t k = std::min<int64_t>(per_cu, (b.nitems + cus - 1) / cus);
+        int64_t work = 0;
+        for (int32_t i = 0; i < b.njobs; ++i) {
+            const Job &j = b.jobs[i];
+            const Code &c = b.codes[j.code];
+            const bool layered = (j.flags & LDPC_LAYERED) != 0;
+            const int64_t steps = layered ? std::max(c.nlayers, 1) : 1;
+            const int64_t rows = (c.m + steps - 1) / steps;
+            const int64_t per_wave = layered ? 16 : 32;
+            const int64_t g = (rows + per_wave - 1) / per_wave, cols = layered ? 0 : (c.n + 63) / 64;
+            const int64_t rest = (g % w + 3) / 4 * 4;
+            const int64_t latency = g / w * std::max<int64_t>(round, (w + 3) / 4 * 4) +
+                                    (rest > 0 ? std::max(round, rest) : 0) + (cols + w - 1) / w * col_round;
+            work += j.frames * steps * std::max(latency, k * g);
+        }
+        const int64_t t = work * ((b.nitems + k * cus - 1) / (k * cus));
+        if (best < 0 || t < best || (stops && tsize == sizeof(double) && t == best)) {
+            best = t;
+            threads = w * 64;
+        }
+    }
+    return LDPC_OK;
+}
+
+}  // namespace fused
+
 // Sets a launch's item counter to 0.
 void launch_zero_counter(uint32_t *counter, hipStream_t s, bool profile);
 
 // Launcher of the fused kernel for codes of row degree <= DB (one
 // translation unit per dtype and bucket).
-// fpw: frames per workgroup, 1 (k_fused) or 2 (k_fused_pair, FP32 flooding
-// sum-product jobs only; the batch's items are then frame pairs).
 // counter: a device word of the launch's own (its items' queue when they
 // exceed the resident workgroups).
 // profile = false keeps the launch out of ldpc_profile_* timing (whose event
 // pool may create events).
 template <class A, int DB>
-ldpc_status launch_fused_bucket(const fused::Batch &batch, uint32_t *counter, size_t lds_bytes, int threads, int fpw,
-                                hipStream_t s, bool profile);
+ldpc_status launch_fused_bucket(fused::Batch &batch, uint32_t *counter, int threads, hipStream_t s, bool profile);
 
-template <class K>
-ldpc_status launch_fused_kernel(K kern, const fused::Batch &batch, uint32_t *counter, size_t lds_bytes, int threads,
-                                hipStream_t s, bool profile)
+template <class A, class K>
+ldpc_status launch_fused_kernel(K kern, fused::Batch &batch, uint32_t *counter, int threads, hipStream_t s,
+                                bool profile)
 {
+    const size_t lds_bytes = fused::batch_lds_bytes(batch, sizeof(typename A::T));
+    batch.flags_at = static_cast<uint32_t>(lds_bytes - fused::kFlagWords * sizeof(int32_t));
+    if (threads == fused::kBaseThreads) {
+        const ldpc_status rc = fused::workgroup_threads(kern, batch, sizeof(typename A::T), lds_bytes,
+                                                        fused::kFusedMaxThreads<A>, threads);
+        if (rc != LDPC_OK)
+            return rc;
+    }
     int per_cu = 0, cus = 0;
     const ldpc_status shape_rc =
         fused::launch_shape(reinterpret_cast<const void *>(kern), lds_bytes, threads, per_cu, cus);
@@ -1384,27 +934,21 @@ ldpc_status launch_fused_kernel(K kern, const fused::Batch &batch, uint32_t *cou
 
 #define LDPC_DEFINE_FUSED_BUCKET(A_, DB_)                                                                        \
     template <>                                                                                                  \
-    ldpc_status launch_fused_bucket<A_, DB_>(const fused::Batch &batch, uint32_t *counter, size_t lds_bytes,     \
-                                             int threads, int fpw, hipStream_t s, bool profile)                  \
+    ldpc_status launch_fused_bucket<A_, DB_>(fused::Batch & batch, uint32_t *counter, int threads,               \
+                                             hipStream_t s, bool profile)                                        \
     {                                                                                                            \
+        const auto launch = [&](auto kern) {                                                                     \
+            return launch_fused_kernel<A_>(kern, batch, counter, threads, s, profile);                           \
+        };                                                                                                       \
         if constexpr (std::is_same<A_, ArithF32>::value) {                                                       \
-            if (fpw == 2)                                                                                        \
-                return launch_fused_kernel(fused::k_fused_pair<A_, DB_>, batch, counter, lds_bytes, threads, s,  \
-                                           profile);                                                             \
-            const fused::Instance inst_ = fpw == 1 ? fused::batch_instance(batch) : fused::kAnyJob;              \
-            if (inst_ == fused::kFloodQC)                                                                        \
-                return launch_fused_kernel(fused::k_fused<A_, DB_, fused::kFloodQC>, batch, counter, lds_bytes,  \
-                                           threads, s, profile);                                                 \
-            if (inst_ == fused::kLayeredQC)                                                                      \
-                return launch_fused_kernel(fused::k_fused<A_, DB_, fused::kLayeredQC>, batch, counter,           \
-                                           lds_bytes, threads, s, profile);                                      \
-            if (inst_ == fused::kMinSumQC)                                                                       \
-                return launch_fused_kernel(fused::k_fused<A_, DB_, fused::kMinSumQC>, batch, counter, lds_bytes, \
-                                           threads, s, profile);                                                 \
+            switch (fused::batch_instance(batch)) {                                                              \
+            case fused::kFlood: return launch(fused::k_fused<A_, DB_, fused::kFlood>);                           \
+            case fused::kLayered: return launch(fused::k_fused<A_, DB_, fused::kLayered>);                       \
+            case fused::kMinSum: return launch(fused::k_fused<A_, DB_, fused::kMinSum>);                         \
+            default: break;                                                                                      \
+            }                                                                                                    \
         }                                                                                                        \
-        if (fpw != 1)                                                                                            \
-            return LDPC_EUNSUPPORTED;                                                                            \
-        return launch_fused_kernel(fused::k_fused<A_, DB_>, batch, counter, lds_bytes, threads, s, profile);     \
+        return launch(fused::k_fused<A_, DB_>);                                                                  \
     }
 
 }  // namespace ldpc

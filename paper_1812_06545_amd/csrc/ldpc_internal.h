@@ -44,13 +44,53 @@ inline ldpc_status status_of_exception() noexcept
 
 }  // namespace ldpc
 
+namespace ldpc {
+
+// Word of a frame's LDS where its messages start, after n posteriors and the
+// dummies' constants (a multiple of 4).
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+inline int32_t fused_first_message(int32_t n)
+{
+    return (n + 3 + 3) / 4 * 4;
+}
+
+// Address tables of the frame-resident kernel, in device memory.  Addresses
+// are byte addresses of 4-byte words in a frame's LDS (fused_kernels.h gives
+// the words' places and the lanes' roles); a lane's slots 4i .. 4i + 3 form a
+// quad (16 bytes), and quads are indexed in 16-byte units.
+//   row order  rows by descending degree (stable); group g is rows 32g .. of it.
+//   row_grp    per group: (longest half) << 16 | message slots before the
+//              group; first quad row / 64.
+//   row_tab    [first + slot quad][64 lanes] posterior addresses.
+//   col_grp    per 64 columns: longest column; first quad row / 64.
+//   col_tab    [first + slot quad][64 lanes] message addresses in the padded
+//              slot order, in ascending row order of the column's edges.
+//   *_x        the same for messages in CSR order, with row_pos giving the
+//              messages' addresses beside row_tab's posteriors; every group has
+//              four quads.  Built only for codes whose padded order does not
+//              fit a workgroup's LDS in some type in which CSR order does.
+//   lay_ptr    per layer: its first group; then the group count.
+//   lay_grp    per group of up to 16 rows of a layer: (longest quarter) << 8 |
+//              rows; first quad.
+//   lay_tab    per group: [slot quad][4 parts][rows] posterior addresses, then
+//              the same of the messages in CSR order.
+struct FusedTables {
+    int32_t row_groups = 0;
+    int32_t slot_words = 0;  // message words of the padded slot order
+    const int32_t *row_grp = nullptr, *row_tab = nullptr, *col_grp = nullptr, *col_tab = nullptr;
+    const int32_t *row_grp_x = nullptr, *row_tab_x = nullptr, *row_pos_x = nullptr, *col_tab_x = nullptr;
+    const int32_t *lay_ptr = nullptr, *lay_grp = nullptr, *lay_tab = nullptr;
+};
+
+}  // namespace ldpc
+
 // A code handle: H in device memory, in two layouts.
 //   CSR/CSC (every code): edges numbered in CSR order (rows ascending,
 //   columns ascending inside a row); col_edge lists each column's edges in
 //   ascending row order.  Used by the per-iteration streaming kernels.
-//   Circulant-block tables (QC codes only): blocks numbered row-major over
-//   the base matrix; the edge of block b in check row i*Z + r is b*Z + r.
-//   Used by the fused frame-resident kernel.
+//   Address tables (FusedTables) for the frame-resident kernel.
 struct ldpc_code_s {
     int device = 0;
     int32_t m = 0, n = 0;
@@ -61,39 +101,17 @@ struct ldpc_code_s {
     const int32_t *col_idx = nullptr;   // E
     const int32_t *col_ptr = nullptr;   // n + 1
     const int32_t *col_edge = nullptr;  // E
-    // circulant-block tables (is_qc)
+    // circulant-block structure (is_qc)
     bool is_qc = false;
     int32_t mb = 0, nb = 0, Z = 0, nblocks = 0;
     int32_t max_brow_deg = 0, max_bcol_deg = 0;
-    // qc_tab layout (int32 words):
-    //   [0, mb]                 row_blk_start   (first block of block-row i; mb+1 entries)
-    //   [mb+1, +nblocks)        blk_col         (base column j of block b)
-    //   [.., +nblocks)          blk_shift       (shift s of block b)
-    //   [.., +nb+1)             col_blk_start   (nb+1 entries)
-    //   [.., +nblocks)          col_blk         (blocks of base column j, ascending block-row)
-    const int32_t *qc_tab = nullptr;
-    int32_t qc_words = 0;
-    std::vector<int32_t> h_qc_tab;
-    // Thread-slot tables of the fused kernel (every code).  Check rows are
-    // visited in "slot" order: for QC codes block-rows sorted by decreasing
-    // degree (rows of one block-row consecutive), otherwise natural order;
-    // brow_order[i] is the block-row in sorted position i (QC only).
-    // row_gmax[g]: largest row degree among slots 32g .. 32g+31 (one
-    // wavefront's rows: the fused kernel gives each row two lanes);
-    // col_gmax[g]: largest column degree among columns 64g .. 64g+63.
-    const int32_t *brow_order = nullptr;
-    const int32_t *row_gmax = nullptr;
-    const int32_t *col_gmax = nullptr;
-    // Half-row words of the fused kernel's circulant view (QC codes whose
-    // sizes fit the fields, else null): word 2 sr + h describes half h of
-    // row slot sr as (first block of the half) | (its length) << 13 |
-    // (the row's index within its block-row) << 19.
-    const uint32_t *half_rows = nullptr;
+    int32_t qc_words = 0;  // words of a table of the block structure: part of the frame-resident kernel's fit rule
+    // Address tables of the frame-resident kernel (codes that can fit it).
+    ldpc::FusedTables fused;
     // Layers of the layered schedule (host): maximal runs of consecutive rows,
     // in ascending order, in which no two rows share a variable.  Layer l is
     // rows [layer_ptr[l], layer_ptr[l+1]); layer_dmax[l] its largest degree.
     std::vector<int32_t> layer_ptr, layer_dmax;
-    const int32_t *d_layer_ptr = nullptr;  // device copy of layer_ptr
     // Hash of the code's shape (sizes, lifting size, row and column degree
     // histograms): the key of tuning choices, which depend on shape only.
     uint64_t shape_hash = 0;
@@ -150,7 +168,12 @@ ldpc_status launch_link_copy16(void *dst, const void *src, size_t bytes, int32_t
 size_t fused_group_bytes();
 
 // ldpc_decode's frames as one frame-resident launch, if the code fits that
-// kernel: true, with the call's status in *rc (nothing is left to do), or
+// kernel, which is the faster route at every size measured (MI355X, FP32, 10
+// iterations, us per call, frames 1 / 256 / 1024, streaming and frame-resident:
+// qc n = 648 88 / 119 / 186 and 34 / 38 / 100; qc n = 3840, one frame to a CU,
+// 125 / 273 / 761 and 120 / 134 / 507; n = 1999 of degrees 2 to 29 107 / 200 /
+// 487 and 77 / 86 / 260; layered qc n = 1944 446 / 533 / 734 and 172 / 182 /
+// 457; FP64 n = 504 131 / 156 / 304 and 27 / 31 / 99): true, with the call's status in *rc (nothing is left to do), or
 // false, and the streaming path takes the call.  ws: at least 4 bytes of
 // device memory of the call's own.
 bool fused_decode(const ldpc_job &job, ldpc_dtype dt, void *ws, hipStream_t stream, ldpc_status *rc);

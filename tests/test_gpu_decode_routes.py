@@ -36,12 +36,16 @@ def _stack(code, K):
     return codes.Code(K * code.m, K * code.n, row_ptr.astype(np.int32), col_idx.astype(np.int32))
 
 
+# `half`: the message is 8 bytes, so half as many fit.
 CODES = {
-    "qc_z27": lambda: codes.qc_code(12, 24, 27, 31),
-    "qc_z81_r56": lambda: codes.qc_code(4, 24, 81, 32),
-    "gallager": lambda: codes.gallager_regular(240, 3, 6, 33),
-    "rows_2_29": lambda: codes.random_rows(120, 311, 2, 29, 34),
-    "rows_dense_col": lambda: codes.random_rows(70, 190, 1, 16, 35, dense_col=True),
+    "qc_z27": lambda half: codes.qc_code(12, 24, 27, 31),
+    "qc_z81_r56": lambda half: codes.qc_code(4, 24, 81, 32),
+    "gallager": lambda half: codes.gallager_regular(240, 3, 6, 33),
+    "rows_2_29": lambda half: codes.random_rows(120, 311, 2, 29, 34),
+    "rows_31_32": lambda half: codes.random_rows(33, 130, 31, 32, 38),
+    "rows_dense_col": lambda half: codes.random_rows(70, 190, 1, 16, 35, dense_col=True),
+    # rows of degree 3 pad to 4: the messages fit a workgroup's LDS in CSR order only
+    "csr_order": lambda half: codes.random_rows(5400, 3000, 3, 3, 37) if half else codes.random_rows(10900, 6000, 3, 3, 37),
 }
 
 
@@ -51,7 +55,7 @@ CODES = {
 @pytest.mark.parametrize("name", list(CODES))
 def test_routes_agree(L, name, dtype, layered, rule):
     import torch
-    code = CODES[name]()
+    code = CODES[name](dtype == "f64")
     K = LDS_WORDS // code.edges + 1
     small, big = L.Code.from_workload(code), L.Code.from_workload(_stack(code, K))
     td = torch.float32 if dtype == "f32" else torch.float64
