@@ -111,7 +111,7 @@ __device__ __forceinline__ void check_row(const int32_t *__restrict__ cols, cons
     typename A::Term a[D];
     typename A::Acc p[D];
     typename A::Acc acc0 = A::identity(), acc1 = A::identity();
-    uint32_t sign = 0;
+    Lanes sign = 0;
 #pragma unroll
     for (int k = 0; k < D; ++k) {
         if (ES)
@@ -147,7 +147,7 @@ __device__ __forceinline__ void check_row_guarded(const int32_t *__restrict__ co
     typename A::Term a[DMAX];
     typename A::Acc p[DMAX];
     typename A::Acc acc0 = A::identity(), acc1 = A::identity();
-    uint32_t sign = 0;
+    Lanes sign = 0;
 #pragma unroll
     for (int k = 0; k < DMAX; ++k) {
         if (k < d) {

@@ -182,6 +182,13 @@ __device__ __forceinline__ uint32_t lane_swap(uint32_t v)
         return odd ? r[0] : r[1];
     }
 }
+// The same of a lane mask.
+template <int M>
+__device__ __forceinline__ Lanes lane_swap(Lanes m)
+{
+    constexpr Lanes even = M == 32 ? 0x00000000ffffffffull : 0x0000ffff0000ffffull;
+    return (m & even) << M | (m >> M & even);
+}
 template <int M>
 __device__ __forceinline__ float lane_swap(float v)
 {
@@ -267,7 +274,7 @@ __device__ __forceinline__ void half_row(const Quad *tab, const Messages<typenam
     typename A::Term a[D];
     typename A::Acc p[D];
     typename A::Acc acc = A::identity();
-    uint32_t sign = 0;
+    Lanes sign = 0;
     uint64_t par = 0;
 #pragma unroll
     for (int j = 0; j < D; ++j) {
@@ -276,7 +283,7 @@ __device__ __forceinline__ void half_row(const Quad *tab, const Messages<typenam
         check_forward<A>(lv[j] - rv[j], a[j], p[j], acc, sign);
     }
     typename A::Acc sx = A::seed(lane_swap<32>(acc));
-    const uint32_t sign_total = sign ^ lane_swap<32>(sign);
+    const Lanes sign_total = sign ^ lane_swap<32>(sign);
     if constexpr (PAR)
         odd |= some_odd(par);
 #pragma unroll
@@ -292,7 +299,7 @@ __device__ __forceinline__ void half_row(const Quad *tab, const Messages<typenam
 template <class T>
 struct Min2 {
     T m1, m2;
-    uint32_t neg;
+    Lanes neg;
 };
 __device__ __forceinline__ float min_of(float a, float b) { return __builtin_fminf(a, b); }
 __device__ __forceinline__ float max_of(float a, float b) { return __builtin_fmaxf(a, b); }
@@ -322,14 +329,16 @@ __device__ __forceinline__ void min_row(const typename A::T (&q)[D], typename A:
 {
     using T = typename A::T;
     const T inf = T(__builtin_huge_val());
-    Min2<T> s{inf, inf, 0u};
+    Min2<T> s{inf, inf, 0};
     T a[D];
+    Lanes neg[D];
 #pragma unroll
     for (int j = 0; j < D; ++j) {
         a[j] = min_of(fabs(q[j]), inf);  // NaN: inf
         s.m2 = second_of(s.m1, s.m2, a[j]);
         s.m1 = min_of(s.m1, a[j]);
-        s.neg ^= static_cast<uint32_t>(q[j] < T(0));
+        neg[j] = __ballot(q[j] < T(0));
+        s.neg ^= neg[j];
     }
     if constexpr (QUARTERS)
         min_merge<16>(s);
@@ -343,8 +352,7 @@ __device__ __forceinline__ void min_row(const typename A::T (&q)[D], typename A:
 #pragma unroll
     for (int j = 0; j < D; ++j) {
         const T mag = a[j] == s.m1 ? r2 : r1;
-        const bool neg = (s.neg != 0u) != (q[j] < T(0));
-        store(j, neg ? -mag : mag);
+        store(j, lane_of(s.neg ^ neg[j]) ? -mag : mag);
     }
 }
 
@@ -408,15 +416,15 @@ __device__ __forceinline__ void layered_quarter(const Quad *tab, int stride, boo
     typename A::Term a[D];
     typename A::Acc p[D];
     typename A::Acc acc = A::identity();
-    uint32_t sign = 0;
+    Lanes sign = 0;
 #pragma unroll
     for (int j = 0; j < D; ++j)
         check_forward<A>(q[j], a[j], p[j], acc, sign);
     const typename A::Acc c_sib = lane_swap<16>(acc);
     const typename A::Acc c_other = lane_swap<32>(A::merge(acc, c_sib));  // the other half's combination
     typename A::Acc sx = A::seed(A::merge(c_sib, c_other));
-    const uint32_t sign_half = sign ^ lane_swap<16>(sign);
-    const uint32_t sign_total = sign_half ^ lane_swap<32>(sign_half);
+    const Lanes sign_half = sign ^ lane_swap<16>(sign);
+    const Lanes sign_total = sign_half ^ lane_swap<32>(sign_half);
 #pragma unroll
     for (int j = D - 1; j >= 0; --j) {
         const T r = check_backward<A>(a[j], p[j], sx, sign_total);

@@ -55,7 +55,7 @@ __device__ __forceinline__ void layer_row(const int32_t *__restrict__ cols, type
     typename A::Term a[D];
     typename A::Acc p[D];
     typename A::Acc acc[4] = {A::identity(), A::identity(), A::identity(), A::identity()};
-    uint32_t sign = 0;
+    Lanes sign = 0;
 #pragma unroll
     for (int k = 0; k < D; ++k) {
         if (!FIRST)
@@ -97,7 +97,7 @@ __device__ __forceinline__ void layer_row_guarded(const int32_t *__restrict__ co
     // One running combination, closed into C[i] at each quarter boundary
     // (quarters may be empty: their combination is the identity).
     typename A::Acc C[4], cur = A::identity();
-    uint32_t sign = 0;
+    Lanes sign = 0;
 #pragma unroll
     for (int k = 0; k < DMAX; ++k) {
         if (k < d) {
@@ -221,7 +221,7 @@ __global__ __launch_bounds__(256) void k_layer_q(const int32_t *__restrict__ row
     using T = typename A::T;
     using Acc = typename A::Acc;
     __shared__ Acc sC[4][kChunk];
-    __shared__ uint32_t sS[4][kChunk];
+    __shared__ Lanes sS[4];
     const int part = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int lane = static_cast<int>(threadIdx.x & 63);
     int group, chunk;
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(256) void k_layer_q(const int32_t *__restrict__ row
     typename A::Term a[DQ];
     Acc p[DQ];
     Acc acc = A::identity();
-    uint32_t sign = 0;
+    Lanes sign = 0;
 #pragma unroll
     for (int k = 0; k < DQ; ++k) {
         if (k < dq) {
@@ -262,10 +262,13 @@ __global__ __launch_bounds__(256) void k_layer_q(const int32_t *__restrict__ row
         }
     }
     sC[part][lane] = acc;
-    sS[part][lane] = sign;
+    if (lane == 0)
+        sS[part] = sign;
     __syncthreads();
     const Acc C0 = sC[0][lane], C1 = sC[1][lane], C2 = sC[2][lane], C3 = sC[3][lane];
-    const uint32_t sign_total = sS[0][lane] ^ sS[1][lane] ^ sS[2][lane] ^ sS[3][lane];
+    const Lanes s4 = sS[0] ^ sS[1] ^ sS[2] ^ sS[3];  // the same in every lane
+    const Lanes sign_total = static_cast<Lanes>(__builtin_amdgcn_readfirstlane(static_cast<int>(s4 >> 32))) << 32 |
+                             static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(s4)));
     Acc other;
     if (part == 0)
         other = A::merge(C1, A::merge(C2, C3));

@@ -8,7 +8,7 @@
 // prefix and suffix combinations (never "total minus self" or a division,
 // which cancel or fail when one term dominates or is zero), through an
 // arithmetic type A that supplies:
-//     Term  term(q)        per-edge quantity, q's sign in its sign bit;
+//     Term  term(q)        per-edge quantity and q's sign;
 //     Acc   identity()     the empty combination;
 //     Acc   add(Acc, Term) combination grown by one edge;
 //     Acc   merge(Acc, Acc) combination of two disjoint edge sets;
@@ -45,6 +45,11 @@
 
 namespace ldpc {
 
+// A condition of every lane of the wavefront, as a mask in scalar registers.
+// (As a plain condition the compiler recomputes it in vector registers.)
+using Lanes = uint64_t;
+__device__ __forceinline__ bool lane_of(Lanes m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
 struct ArithF32 {
     using T = float;
     static constexpr float kIn = 1.44269504088896341f;   // natural LLR -> internal (log2 e)
@@ -52,11 +57,12 @@ struct ArithF32 {
     static constexpr float kRmax = 28.8539008177792681f; // R_MAX = 20 in internal units
 
     struct Term {
-        float t;  // tanh(|q| ln2 / 2), with q's sign bit
-        float u;  // 1 - |t|
+        float t;   // tanh(|q| ln2 / 2)
+        float u;   // 1 - t
+        Lanes neg;  // q's sign bit, of all lanes
     };
     struct Acc {
-        float P;  // product of the |t|
+        float P;  // product of the t
         float Q;  // 1 - P, formed from the u
     };
     // a (+) b = 1 - (1 - a)(1 - b) for a, b in [0, 1]
@@ -74,20 +80,29 @@ struct ArithF32 {
         // Everything is formed at half scale, d/2 and 2/(1 + e), which
         // scales by powers of two only (the same roundings) and saves the
         // doubling of e in u = 2e/(1 + e).
-        float p = __builtin_fmaf(-x, 0.5f * 1.33335581e-3f, 0.5f * 9.61812911e-3f);  // ln2^5/120, ln2^4/24
-        p = __builtin_fmaf(-x, p, 0.5f * 5.55041087e-2f);                             // ln2^3/6
+        float c5 = 0.5f * 1.33335581e-3f;  // ln2^5/120
+        // in a register: an instruction that holds the constant itself cannot
+        // take |q|, and x would cost an instruction of its own
+        asm("" : "+s"(c5));
+        float p = __builtin_fmaf(-x, c5, 0.5f * 9.61812911e-3f);  // ln2^4/24
+        p = __builtin_fmaf(-x, p, 0.5f * 5.55041087e-2f);            // ln2^3/6
         p = __builtin_fmaf(-x, p, 0.5f * 2.40226507e-1f);                             // ln2^2/2
         p = __builtin_fmaf(-x, p, 0.5f * 6.93147181e-1f);                             // ln2
-        const float dh = (x < 0.125f) ? x * p : __builtin_fmaf(e, -0.5f, 0.5f);     // d / 2
+        float series = x * p;
+        // a select, not a branch around one of its values: a row stays one block
+        // of code, whose edges' chains overlap
+        asm("" : "+v"(series));
+        const float dh = x < 0.125f ? series : __builtin_fmaf(e, -0.5f, 0.5f);  // d / 2
         const float ri2 = __builtin_amdgcn_rcpf(__builtin_fmaf(e, 0.5f, 0.5f));     // 2 / (1 + e)
         Term k;
-        k.t = mag_with_sign_of(dh * ri2, q);
+        k.t = dh * ri2;
         k.u = e * ri2;
+        k.neg = __ballot(__float_as_int(q) < 0);
         return k;
     }
     __device__ static __forceinline__ Acc add(Acc a, const Term &k)
     {
-        return Acc{a.P * __builtin_fabsf(k.t), oplus(a.Q, k.u)};
+        return Acc{a.P * k.t, oplus(a.Q, k.u)};
     }
     __device__ static __forceinline__ Acc merge(Acc a, Acc b) { return Acc{a.P * b.P, oplus(a.Q, b.Q)}; }
     __device__ static __forceinline__ Acc seed(Acc a) { return Acc{a.P + a.P, a.Q}; }
@@ -103,26 +118,6 @@ struct ArithF32 {
         const float c = __builtin_amdgcn_fmed3f((1.0f - w) + z, -0x1p-24f, 0x1p-24f);
         const float r = __builtin_fmaf(c, 1.44269504088896341f, __builtin_amdgcn_logf(w));
         return r < kRmax ? r : kRmax;
-    }
-    __device__ static __forceinline__ uint32_t term_sign(const Term &k) { return sign_bit(k.t); }
-
-    // The fused kernel parks a term's t in the edge's message slot and keeps u
-    // in a register; kDummyParked is the parked part of a dummy edge's term
-    // (q = +inf: t = 1, u = 0).
-    using Keep = float;
-    static constexpr float kDummyParked = 1.0f;
-    __device__ static __forceinline__ float park(const Term &k) { return k.t; }
-    __device__ static __forceinline__ Keep keep(const Term &k) { return k.u; }
-    __device__ static __forceinline__ Term unpark(float parked, Keep kept) { return Term{parked, kept}; }
-
-    __device__ static __forceinline__ uint32_t sign_bit(float v) { return __float_as_uint(v) >> 31; }
-    __device__ static __forceinline__ float with_sign(float mag, uint32_t neg)
-    {
-        return __uint_as_float(__float_as_uint(mag) | (neg << 31));
-    }
-    __device__ static __forceinline__ float mag_with_sign_of(float mag, float src)
-    {
-        return __uint_as_float(__float_as_uint(mag) | (__float_as_uint(src) & 0x80000000u));
     }
 };
 
@@ -146,11 +141,12 @@ struct ArithF64 {
     static constexpr double kRmax = 20.0;
 
     struct Term {
-        double t;  // tanh(|q| / 2), with q's sign bit
-        double u;  // 1 - |t|
+        double t;  // tanh(|q| / 2)
+        double u;  // 1 - t
+        Lanes neg;  // q's sign bit, of all lanes
     };
     struct Acc {
-        double P;  // product of the |t|
+        double P;  // product of the t
         double Q;  // 1 - P, formed from the u
     };
     __device__ static __forceinline__ double oplus(double a, double b) { return __builtin_fma(-a, b, a + b); }
@@ -226,13 +222,14 @@ struct ArithF64 {
         const double d = __builtin_fma(-two, m, 1.0 - two);
         const double ri = recip(1.0 + e);
         Term out;
-        out.t = mag_with_sign_of(d * ri, q);
+        out.t = d * ri;
         out.u = (e + e) * ri;
+        out.neg = __ballot(__double_as_longlong(q) < 0);
         return out;
     }
     __device__ static __forceinline__ Acc add(Acc a, const Term &k)
     {
-        return Acc{a.P * __builtin_fabs(k.t), oplus(a.Q, k.u)};
+        return Acc{a.P * k.t, oplus(a.Q, k.u)};
     }
     __device__ static __forceinline__ Acc merge(Acc a, Acc b) { return Acc{a.P * b.P, oplus(a.Q, b.Q)}; }
     __device__ static __forceinline__ Acc seed(Acc a) { return Acc{a.P + a.P, a.Q}; }
@@ -241,28 +238,6 @@ struct ArithF64 {
         // Q = 0 gives NaN, which the select turns into R_MAX.
         const double r = log1p_pos(x.P * recip(x.Q));
         return r < kRmax ? r : kRmax;
-    }
-    __device__ static __forceinline__ uint32_t term_sign(const Term &k) { return sign_bit(k.t); }
-
-    // As ArithF32: t is parked in the edge's message slot, u stays in a register.
-    using Keep = double;
-    static constexpr double kDummyParked = 1.0;
-    __device__ static __forceinline__ double park(const Term &k) { return k.t; }
-    __device__ static __forceinline__ Keep keep(const Term &k) { return k.u; }
-    __device__ static __forceinline__ Term unpark(double parked, Keep kept) { return Term{parked, kept}; }
-    __device__ static __forceinline__ uint32_t sign_bit(double v)
-    {
-        return static_cast<uint32_t>(static_cast<uint64_t>(__double_as_longlong(v)) >> 63);
-    }
-    __device__ static __forceinline__ double with_sign(double mag, uint32_t neg)
-    {
-        return __longlong_as_double(static_cast<long long>(static_cast<uint64_t>(__double_as_longlong(mag)) |
-                                                           (static_cast<uint64_t>(neg) << 63)));
-    }
-    __device__ static __forceinline__ double mag_with_sign_of(double mag, double src)
-    {
-        const uint64_t s = static_cast<uint64_t>(__double_as_longlong(src)) & 0x8000000000000000ull;
-        return __longlong_as_double(static_cast<long long>(static_cast<uint64_t>(__double_as_longlong(mag)) | s));
     }
 };
 
@@ -317,24 +292,30 @@ __device__ __forceinline__ void quarter_seeds(const typename A::Acc C[4], typena
 // half's running combination, which then grows by a_k.
 template <class A>
 __device__ __forceinline__ void check_forward(typename A::T q, typename A::Term &a_k, typename A::Acc &p_k,
-                                              typename A::Acc &acc, uint32_t &sign)
+                                              typename A::Acc &acc, Lanes &sign)
 {
     a_k = A::term(q);
     p_k = acc;
     acc = A::add(acc, a_k);
-    sign ^= A::sign_bit(q);
+    sign ^= a_k.neg;
 }
 
 // Backward step: outgoing message of an edge from its term, p_k, the half's
 // running suffix s (started at seed(C_other); it then grows by this edge) and
-// the row's total sign.
+// the row's total sign.  Signs are lane masks: a comparison forward and a
+// select backward per edge, where a sign carried in t's sign bit cost four
+// vector instructions.
+// (Leaving out the merges with the identity at a part's first edge saves
+// four instructions per half row, but the rows then take 115 registers instead
+// of 90 and ran 2-6% slower.)
 template <class A>
 __device__ __forceinline__ typename A::T check_backward(const typename A::Term &a_k, const typename A::Acc &p_k,
-                                                        typename A::Acc &s, uint32_t sign_total)
+                                                        typename A::Acc &s, Lanes sign_total)
 {
     const typename A::Acc ex = A::merge(p_k, s);
     s = A::add(s, a_k);
-    return A::with_sign(A::message(ex), sign_total ^ A::term_sign(a_k));
+    const typename A::T mag = A::message(ex);
+    return lane_of(sign_total ^ a_k.neg) ? -mag : mag;
 }
 
 }  // namespace ldpc
