@@ -164,7 +164,8 @@ ldpc_status ldpc_workspace_bytes(ldpc_code code, ldpc_dtype dtype, int32_t frame
  * check-node and one variable-node kernel per iteration (Section II,
  * Algorithm 1: Loop 2, then Loops 3 and 4; the launch boundary is the
  * two-phase barrier); layered (LDPC_LAYERED; Algorithm 2) one kernel per
- * layer, plus a syndrome kernel per iteration with early stop.  The frames
+ * layer, plus a syndrome kernel per iteration with early stop; a few frames
+ * (up to about 24, fewer for long rows) one kernel per flooding iteration.  The frames
  * are interleaved on the device as in Section III-B.
  *   dtype      LDPC_F32 (llr/posterior are float) or LDPC_F64 (double)
  *   max_iter   >= 0; 0 returns the hard decision of llr, iters 0, posterior = llr

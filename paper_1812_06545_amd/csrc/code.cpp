@@ -361,6 +361,10 @@ ldpc_status upload(const HostLayout &h, int32_t Z, ldpc_code_s *c)
     c->E = static_cast<int64_t>(h.col_idx.size());
     c->max_row_deg = h.max_row_deg;
     c->max_col_deg = h.max_col_deg;
+    for (int32_t j = 0; j < h.n; ++j) {
+        const int64_t d = h.col_ptr[j + 1] - h.col_ptr[j];
+        c->column_reads += d * d;
+    }
     c->shape_hash = shape_hash(h, Z);
     return LDPC_OK;
 }

@@ -1,0 +1,318 @@
+// Flooding for a few frames of a code too long for the frame-resident kernel:
+// one launch per iteration instead of two.
+//
+// With up to kFewFrames frames the streaming kernels are bound by their
+// launches (about 5 us each at any size below that): a chunk's 64 lanes are
+// mostly padding, and a check and a variable launch follow each other for
+// every iteration, also after the last frame has stopped.  Here one launch is
+// a whole iteration (arxiv 1812.06545, Section II, Algorithm 1): the check rows
+// form the posteriors they need, L_n = Lch_n + sum of r_mn in ascending row
+// order, from the messages of the iteration before, so no variable launch has
+// to come first.  A column's sum is formed once per row that holds it, which
+// multiplies the reads of r by the mean column degree; the rule that picks
+// this path (few_frames_path) bounds that product.  The messages alternate
+// between two buffers; nothing else passes from launch to launch.
+//
+// One wavefront is one check row of FW frames: lane k FW + f holds edge k of
+// frame f.  The lanes sum their columns, exchange their edges' terms through
+// LDS, and each forms its own exclusive combination in the order of the other
+// paths (spa_math.h), so that every message has their bits.
+//
+// Early stop: launch t forms the syndrome of x^(t-1) and marks unsatisfied
+// frames.  Launch t + 1 finds a frame that launch t left unmarked stopped at
+// t - 1 and leaves its messages alone from then on: those of iteration t - 1
+// stay in their buffer, from which the output launch forms its posteriors.
+#include <algorithm>
+#include <type_traits>
+
+#include "flood_kernels.h"
+#include "minsum_kernels.h"
+
+namespace ldpc {
+namespace {
+
+// Two message buffers of up to 32 frames take the place of a 64-frame chunk's one.
+constexpr int kFewFrames = 32;
+// Frames per wavefront for rows of degree d.
+constexpr int few_width(int d) { return d <= 8 ? 8 : d <= 16 ? 4 : 2; }
+
+template <class A>
+struct FewArgs {
+    using T = typename A::T;
+    const int32_t *row_ptr, *col_idx, *col_ptr, *col_edge;
+    int32_t m, n, W, groups;    // W: frames of storage (a multiple of FW); groups: frame groups of FW
+    const T *Lch;               // [n][W]
+    const T *Rold;              // [E][W]: the messages of iteration t - 1
+    T *Rnew;
+    int32_t *done;              // [W]: iteration a frame stopped at, or -1
+    const int32_t *unsat_prev;  // [W] of launch t - 1 (null for t = 1)
+    int32_t *unsat;             // [W] of this launch
+    int32_t t;
+    T scale, offset;
+};
+
+// Scaled channel values [n][W] (padding frames get LLR 1) and the frames' state.
+template <class A>
+__global__ __launch_bounds__(256) void k_few_ingest(const typename A::T *__restrict__ llr, int32_t F, int32_t n,
+                                                    int32_t W, typename A::T *__restrict__ Lch,
+                                                    int32_t *__restrict__ done, int32_t *__restrict__ unsat,
+                                                    int32_t unsat_words)
+{
+    using T = typename A::T;
+    const int32_t i = static_cast<int32_t>(blockIdx.x * blockDim.x + threadIdx.x);
+    if (i < W)
+        done[i] = -1;
+    if (i < unsat_words)
+        unsat[i] = 0;
+    const int32_t f = i % W, c = i / W;
+    if (c >= n)
+        return;
+    const T v = f < F ? llr[static_cast<int64_t>(f) * n + c] : T(1);
+    Lch[i] = v * T(A::kIn);
+}
+
+// L of a column: the channel value and its messages, all loads of eight edges
+// issued before their ordered sum.
+template <class T>
+__device__ __forceinline__ T few_column(T acc, const int32_t *__restrict__ edges, int32_t dv, const T *__restrict__ R,
+                                        int32_t W, int32_t f)
+{
+    constexpr int kStep = 8;
+    for (int32_t j0 = 0; j0 < dv; j0 += kStep) {
+        T v[kStep];
+#pragma unroll
+        for (int j = 0; j < kStep; ++j)
+            if (j0 + j < dv)
+                v[j] = R[static_cast<int64_t>(edges[j0 + j]) * W + f];
+#pragma unroll
+        for (int j = 0; j < kStep; ++j)
+            if (j0 + j < dv)
+                acc += v[j];
+    }
+    return acc;
+}
+
+// Orders a wavefront's LDS writes before its lanes' reads of each other's.
+__device__ __forceinline__ void wave_exchange()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <class A, int KL, bool FIRST, bool ES, bool MS>
+__global__ __launch_bounds__(256) void k_few(FewArgs<A> a)
+{
+    using T = typename A::T;
+    constexpr int FW = few_width(KL);
+    static_assert(FW * KL == 64, "a wavefront is KL edges of FW frames");
+    __shared__ T s_t[4][64], s_u[4][64];  // sum-product: an edge's t and u; min-sum: its |q| (in s_t)
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int lane = static_cast<int>(threadIdx.x & 63), k = lane / FW;
+    const int64_t item = static_cast<int64_t>(blockIdx.x) * 4 + wave;
+    const int32_t row = static_cast<int32_t>(item / a.groups), f = static_cast<int32_t>(item % a.groups) * FW + lane % FW;
+    if (row >= a.m)
+        return;
+    bool stopped = false;
+    if constexpr (ES && !FIRST) {
+        const int32_t dn = a.done[f];
+        const bool stops = dn < 0 && a.unsat_prev[f] == 0;
+        stopped = dn >= 0 || stops;
+        if (row == 0 && k == 0 && stops)
+            a.done[f] = a.t - 2;
+        if (__all(stopped))
+            return;
+    }
+    const int32_t e0 = a.row_ptr[row], d = a.row_ptr[row + 1] - e0;
+    const bool real = k < d;
+    T L = T(0), q = T(0);
+    if (real) {
+        const int32_t c = a.col_idx[e0 + k];
+        L = a.Lch[static_cast<int64_t>(c) * a.W + f];
+        if constexpr (FIRST) {
+            q = L;
+        } else {
+            const T own = a.Rold[static_cast<int64_t>(e0 + k) * a.W + f];
+            const int32_t b = a.col_ptr[c];
+            L = few_column(L, a.col_edge + b, a.col_ptr[c + 1] - b, a.Rold, a.W, f);
+            q = L - own;
+        }
+    }
+    // lanes of one frame: bits f, f + FW, ..
+    constexpr uint64_t kFrameLanes = ~0ull / ((1ull << FW) - 1);
+    if constexpr (ES) {
+        const uint64_t ones = __ballot(real && L < T(0)) >> (lane % FW) & kFrameLanes;
+        if (k == 0 && (__popcll(ones) & 1) != 0)
+            a.unsat[f] = 1;
+    }
+    T r;
+    if constexpr (MS) {
+        const uint64_t negs = __ballot(real && q < T(0)) >> (lane % FW) & kFrameLanes;
+        s_t[wave][lane] = fabs(q);
+        wave_exchange();
+        T low = T(__builtin_huge_val());
+        for (int j = 0; j < d; ++j) {
+            const T x = s_t[wave][j * FW + lane % FW];
+            low = j != k && x < low ? x : low;
+        }
+        T mag = a.scale * low - a.offset;
+        mag = mag > T(0) ? mag : T(0);
+        mag = mag < T(A::kRmax) ? mag : T(A::kRmax);
+        r = ((__popcll(negs) & 1) != 0) != (q < T(0)) ? -mag : mag;
+    } else {
+        const typename A::Term own = A::term(q);
+        const uint64_t neg_all = own.neg & __ballot(real);
+        const uint64_t negs = neg_all >> (lane % FW) & kFrameLanes;
+        s_t[wave][lane] = own.t;
+        s_u[wave][lane] = own.u;
+        wave_exchange();
+        auto grow = [&](typename A::Acc x, int j) {
+            typename A::Term e;
+            e.t = s_t[wave][j * FW + lane % FW];
+            e.u = s_u[wave][j * FW + lane % FW];
+            return A::add(x, e);
+        };
+        const int h = (d + 1) / 2;
+        const int lo = k < h ? 0 : h, hi = k < h ? h : d;
+        typename A::Acc p = A::identity(), other = A::identity();
+        for (int j = lo; j < k && j < d; ++j)
+            p = grow(p, j);
+        for (int j = k < h ? h : 0; j < (k < h ? d : h); ++j)
+            other = grow(other, j);
+        typename A::Acc s = A::seed(other);
+        for (int j = hi - 1; j > k; --j)
+            s = grow(s, j);
+        const T mag = A::message(A::merge(p, s));
+        r = ((__popcll(negs) & 1) != 0) != ((neg_all >> lane & 1) != 0) ? -mag : mag;
+    }
+    if (real && !stopped)
+        a.Rnew[static_cast<int64_t>(e0 + k) * a.W + f] = r;
+}
+
+// Bits, iteration counts and posteriors: a frame's posteriors are those of the
+// iteration it stopped at, formed from that iteration's messages.
+template <class A>
+__global__ __launch_bounds__(256) void k_few_output(const int32_t *__restrict__ col_ptr,
+                                                    const int32_t *__restrict__ col_edge,
+                                                    const typename A::T *__restrict__ llr, int32_t F, int32_t n,
+                                                    int32_t W, const typename A::T *__restrict__ Lch,
+                                                    const typename A::T *__restrict__ R0,
+                                                    const typename A::T *__restrict__ R1,
+                                                    const int32_t *__restrict__ done,
+                                                    const int32_t *__restrict__ unsat_last, int32_t max_iter,
+                                                    uint8_t *__restrict__ bits, int32_t *__restrict__ iters,
+                                                    typename A::T *__restrict__ posterior)
+{
+    using T = typename A::T;
+    const int32_t i = static_cast<int32_t>(blockIdx.x * blockDim.x + threadIdx.x);
+    const int32_t f = i % W, c = i / W;
+    if (c >= n || f >= F)
+        return;
+    int32_t it = max_iter;
+    if (unsat_last != nullptr) {  // early stop
+        const int32_t dn = done[f];
+        it = dn >= 0 ? dn : unsat_last[f] == 0 ? max_iter - 1 : max_iter;
+    }
+    T v = Lch[i];
+    if (it > 0)
+        v = few_column(v, col_edge + col_ptr[c], col_ptr[c + 1] - col_ptr[c], (it & 1) ? R1 : R0, W, f);
+    const int64_t o = static_cast<int64_t>(f) * n + c;
+    bits[o] = static_cast<uint8_t>(v < T(0));
+    if (posterior)
+        posterior[o] = it == 0 ? llr[o] : v * T(A::kOut);
+    if (c == 0)
+        iters[f] = it;
+}
+
+template <class A, int KL, bool MS>
+ldpc_status run_few(const ldpc_code_s *c, int32_t frames, int32_t max_iter, bool es, const typename A::T *llr,
+                    uint8_t *bits, int32_t *iters, typename A::T *post, typename A::T *R, typename A::T *Lch,
+                    int32_t *done, int32_t *unsat, hipStream_t s, typename A::T scale, typename A::T offset)
+{
+    using T = typename A::T;
+    constexpr int32_t FW = few_width(KL);
+    const int32_t W = (frames + FW - 1) / FW * FW;
+    T *buffer[2] = {R, R + c->E * W};
+    const int32_t unsat_words = es ? max_iter * W : 0;
+    const int32_t words = std::max(c->n * W, unsat_words);
+    const dim3 vgrid(static_cast<unsigned>((words + 255) / 256)), ogrid(static_cast<unsigned>((c->n * W + 255) / 256));
+    {
+        ProfScope ps(LDPC_KERNEL_INGEST, s);
+        LDPC_LAUNCH(ps, (k_few_ingest<A>), vgrid, dim3(256), 0, s, llr, frames, c->n, W, Lch, done, unsat,
+                    unsat_words);
+    }
+    FewArgs<A> a{c->row_ptr, c->col_idx, c->col_ptr, c->col_edge, c->m, c->n, W, W / FW, Lch, nullptr, nullptr, done,
+                 nullptr, nullptr, 0, scale, offset};
+    const dim3 grid(static_cast<unsigned>((static_cast<int64_t>(c->m) * a.groups + 3) / 4));
+    for (int32_t t = 1; t <= max_iter; ++t) {
+        a.t = t;
+        a.Rold = buffer[(t - 1) & 1];
+        a.Rnew = buffer[t & 1];
+        a.unsat = unsat + static_cast<int64_t>(t - 1) * W;
+        a.unsat_prev = a.unsat - W;
+        ProfScope ps(LDPC_KERNEL_CHECK, s);
+        if (t == 1 && es)
+            LDPC_LAUNCH(ps, (k_few<A, KL, true, true, MS>), grid, dim3(256), 0, s, a);
+        else if (t == 1)
+            LDPC_LAUNCH(ps, (k_few<A, KL, true, false, MS>), grid, dim3(256), 0, s, a);
+        else if (es)
+            LDPC_LAUNCH(ps, (k_few<A, KL, false, true, MS>), grid, dim3(256), 0, s, a);
+        else
+            LDPC_LAUNCH(ps, (k_few<A, KL, false, false, MS>), grid, dim3(256), 0, s, a);
+    }
+    ProfScope ps(LDPC_KERNEL_OUTPUT, s);
+    LDPC_LAUNCH(ps, (k_few_output<A>), ogrid, dim3(256), 0, s, c->col_ptr, c->col_edge, llr, frames, c->n, W, Lch,
+                buffer[0], buffer[1], done, es && max_iter > 0 ? unsat + static_cast<int64_t>(max_iter - 1) * W : nullptr,
+                max_iter, bits, iters, post);
+    return hipGetLastError() == hipSuccess ? LDPC_OK : LDPC_EDEVICE;
+}
+
+}  // namespace
+
+// The streaming kernels cost the same from 1 to 64 frames; a launch here costs
+// in proportion to its wavefronts, m x (frame groups), beyond its latency.
+// Measured on MI355X, 20 iterations, us per call, streaming kernels and 1, 2,
+// 3, 4 groups: n = 16200 of degree 7 FP32 320 and 188, 289, 407, 505, FP64 599
+// and 240, 369, 530, 654; n = 64800 FP32 905 and 550, 977, 1473, FP64 1809 and
+// 717, 1220, 1855; n = 12007 of degree 16 FP32 318 and 164, 249, FP64 735 and
+// 214, 315, .., 460.  The bound on the reads keeps out codes whose dense columns
+// would be summed by very many rows (at its edge: a column of degree 2503, 19.4
+// and 6.7 to 13 ms).
+bool few_frames_path(const ldpc_code_s *c, bool f64, int32_t frames)
+{
+    if (frames > kFewFrames || c->max_row_deg > 32)
+        return false;
+    const int32_t width = few_width(c->max_row_deg), groups = (frames + width - 1) / width;
+    return groups <= (c->m <= 20000 ? 2 : 1) + (f64 ? 1 : 0) && c->column_reads * groups * width <= 1 << 26;
+}
+
+template <class A>
+ldpc_status decode_few(const ldpc_code_s *c, int32_t frames, int32_t max_iter, uint32_t flags,
+                       const typename A::T *llr, uint8_t *bits, int32_t *iters, typename A::T *post,
+                       typename A::T *R, typename A::T *Lch, int32_t *done, int32_t *unsat, hipStream_t s,
+                       typename A::T scale, typename A::T offset)
+{
+    const bool es = (flags & LDPC_EARLY_STOP) != 0;
+    const auto run = [&](auto lanes) {
+        constexpr int KL = decltype(lanes)::value;
+        if (flags & LDPC_MIN_SUM)
+            return run_few<A, KL, true>(c, frames, max_iter, es, llr, bits, iters, post, R, Lch, done, unsat, s, scale,
+                                        offset);
+        return run_few<A, KL, false>(c, frames, max_iter, es, llr, bits, iters, post, R, Lch, done, unsat, s, scale,
+                                     offset);
+    };
+    if (c->max_row_deg <= 8)
+        return run(std::integral_constant<int, 8>());
+    if (c->max_row_deg <= 16)
+        return run(std::integral_constant<int, 16>());
+    return run(std::integral_constant<int, 32>());
+}
+
+template ldpc_status decode_few<ArithF32>(const ldpc_code_s *, int32_t, int32_t, uint32_t, const float *, uint8_t *,
+                                          int32_t *, float *, float *, float *, int32_t *, int32_t *, hipStream_t,
+                                          float, float);
+template ldpc_status decode_few<ArithF64>(const ldpc_code_s *, int32_t, int32_t, uint32_t, const double *, uint8_t *,
+                                          int32_t *, double *, double *, double *, int32_t *, int32_t *, hipStream_t,
+                                          double, double);
+
+}  // namespace ldpc

@@ -36,12 +36,15 @@
 // test x^(t-1) = [L < 0] before pass t, since inside a pass the rows see
 // different posteriors and cannot test one decision together.
 //
+// A few frames take one launch per flooding iteration instead (few.hip).
+//
 // With LDPC_MIN_SUM the check rule is min-sum (minsum_kernels.h) on either
 // schedule; the variable kernel, the syndrome and the retire kernels are
 // shared.
 #include <algorithm>
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 
 #include "flood_kernels.h"
 #include "layered_kernels.h"
@@ -344,6 +347,10 @@ ldpc_status decode_impl(const ldpc_code_s *c, int32_t frames, int32_t max_iter, 
     T *Lch = cv.take<T>(static_cast<size_t>(c->n) * Fp);
     int32_t *done = cv.take<int32_t>(Fp + nchunk);  // per frame, then per chunk (flood_kernels.h)
     int32_t *unsat = cv.take<int32_t>(static_cast<size_t>(std::max(max_iter, 1)) * Fp);
+
+    if ((flags & LDPC_LAYERED) == 0 && few_frames_path(c, std::is_same<A, ArithF64>::value, frames))
+        return decode_few<A>(c, frames, max_iter, flags, llr, bits, iters, post, R, Lch, done, unsat, s,
+                             static_cast<T>(ms_scale), static_cast<T>(ms_offset * A::kIn));
 
     // The frame state is read only with early stop (every read is under the
     // kernels' ES flag), so only then is it initialised.

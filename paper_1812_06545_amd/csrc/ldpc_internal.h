@@ -96,6 +96,7 @@ struct ldpc_code_s {
     int32_t m = 0, n = 0;
     int64_t E = 0;
     int32_t max_row_deg = 0, max_col_deg = 0;
+    int64_t column_reads = 0;  // sum over the edges of their column's degree
     void *d_mem = nullptr;
     const int32_t *row_ptr = nullptr;   // m + 1
     const int32_t *col_idx = nullptr;   // E
@@ -185,6 +186,14 @@ size_t stream_workspace_bytes(const ldpc_code_s *c, ldpc_dtype dt, int32_t frame
 ldpc_status stream_decode(const ldpc_code_s *c, ldpc_dtype dt, int32_t frames, int32_t max_iter, uint32_t flags,
                           const void *llr, uint8_t *bits, int32_t *iters, void *posterior, void *ws,
                           hipStream_t stream, double ms_scale, double ms_offset);
+// Flooding of a few frames with one launch per iteration (few.hip), on the
+// streaming workspace; few_frames_path says whether it is the faster form.
+bool few_frames_path(const ldpc_code_s *c, bool f64, int32_t frames);
+template <class A>
+ldpc_status decode_few(const ldpc_code_s *c, int32_t frames, int32_t max_iter, uint32_t flags,
+                       const typename A::T *llr, uint8_t *bits, int32_t *iters, typename A::T *post,
+                       typename A::T *R, typename A::T *Lch, int32_t *done, int32_t *unsat, hipStream_t s,
+                       typename A::T scale, typename A::T offset);
 // scale finite and > 0, offset finite and >= 0.
 bool minsum_params_ok(double scale, double offset);
 

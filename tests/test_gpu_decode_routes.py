@@ -73,3 +73,39 @@ def test_routes_agree(L, name, dtype, layered, rule):
             assert torch.equal(its, i2)
             bits, post = bits.repeat(1, K), post.repeat(1, K)
         assert torch.equal(b2.reshape(bits.shape), bits) and torch.equal(p2.reshape(post.shape), post)
+
+
+FEW = {
+    "stair": lambda: codes.staircase_irregular(12960, 41),
+    "rows_2_16": lambda: codes.random_rows(6001, 12007, 2, 16, 42),
+    "rows_dense_col": lambda: codes.random_rows(2503, 5003, 17, 31, 43, dense_col=True),
+}
+
+
+@pytest.mark.parametrize("rule", ["spa", "minsum"])
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("name", list(FEW))
+def test_few_frames_match_many(L, name, dtype, rule):
+    """Up to 32 frames of a code that streams take one launch per iteration, more
+    frames the check and variable kernels: a frame decodes to the same bits in
+    both, whatever the number of frames beside it, with and without early stop,
+    from none to several iterations."""
+    import torch
+    code = FEW[name]()
+    h = L.Code.from_workload(code)
+    td = torch.float32 if dtype == "f32" else torch.float64
+    assert not L.ldpc_batch_fits_fused(h, td)[0]
+    rng = np.random.default_rng(44)
+    x = rng.normal(3.0, 1.8, size=(70, code.n)).astype(np.float32)
+    x[::5] = np.abs(x[::5])  # codewords from the start: these stop at once
+    t = torch.from_numpy(x).cuda().to(td)
+    for iters, es in ((0, True), (1, True), (4, False), (9, True)):
+        kw = dict(early_stop=es, rule=rule, ms_scale=0.75)
+        want = L.decode(h, t, iters, **kw)
+        for frames in (1, 5, 8, 11, 32):
+            print(f"[gpu] few {name} {dtype} {rule} T={iters} es={es} frames={frames}", flush=True)
+            got = L.decode(h, t[:frames].contiguous(), iters, **kw)
+            for a, b in zip(got, want):
+                assert torch.equal(a, b[:frames])
+        if es and iters == 9:
+            assert len(set(want[1].tolist())) > 1
