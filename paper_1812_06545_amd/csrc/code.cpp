@@ -316,6 +316,8 @@ FusedOffsets fused_tables(const HostLayout &h, const std::vector<int32_t> &layer
 ldpc_status upload(const HostLayout &h, int32_t Z, ldpc_code_s *c)
 {
     layer_tables(h, c->layer_ptr, c->layer_dmax);
+    for (size_t l = 0; l + 1 < c->layer_ptr.size(); ++l)
+        c->layer_rows = std::max(c->layer_rows, c->layer_ptr[l + 1] - c->layer_ptr[l]);
     TableImage im;
     im.words.reserve(10 * h.col_idx.size() + 4 * h.row_ptr.size() + 4 * h.col_ptr.size() + 4096);
     const FusedOffsets fo = fused_tables(h, c->layer_ptr, im);

@@ -64,7 +64,7 @@ struct Code {
     int32_t n, E;
     int32_t row_groups, nlayers;
     int32_t r_words;  // message words of a flooding frame (E with an explicit order)
-    int32_t m;
+    int32_t m, layer_rows;  // rows; rows of the largest layer
     const int32_t *row_grp, *row_tab, *row_pos, *col_grp, *col_tab, *lay_ptr, *lay_grp, *lay_tab;
 };
 
@@ -841,60 +841,108 @@ inline size_t batch_lds_bytes(const Batch &b, size_t tsize)
     return bytes;
 }
 
-// Workgroup size of a one-frame launch whose caller left it at kBaseThreads.
-// A frame's iteration (a layered frame's pass) is a chain of rounds: a
-// wavefront takes 32 check rows at a time (16 of a layer's) and 64 columns.  The unit below is one 32-row group's VALU time on
-// a whole CU (0.20 us for rows of degree 17): a wavefront alone on its SIMD
-// takes 4 of them, and no round less than its latency, about 11 in FP32 and 5
-// in FP64, whose instructions hold the SIMD longer.  k frames on a CU take at
-// least the VALU time of all their rows.  The size with the least (passes
-// over the device) x (time of a frame) is taken; of equals the smallest,
-// which holds more frames at once, or in FP64 with early stop the largest,
-// which ends the long frames of the last pass sooner.  512 threads and this rule,
-// us per call of 10 iterations: one frame of qc n = 648 46.7 and 36.4, of n =
-// 1944 99.1 and 75.8; 64 frames of four codes in a plan 64.9 and 52.0; 1024
-// FP64 frames of n = 504 134 and 110.
+// Workgroup size of a launch whose caller left it at kBaseThreads, for the job
+// with the most rows to run.  Measured on MI355X over eleven codes, 64 to 4000
+// frames and 64 to 1024 threads; the figures are us per call of 10 iterations
+// by wavefronts per workgroup.
+//
+// Every frame has a CU to itself: the size with the shortest chain of rounds.
+// A wavefront takes 32 check rows at a time and 64 columns; the unit is a
+// group's VALU time on a whole CU (a wavefront alone on its SIMD takes 4), a
+// round's latency 11 of them in FP32 and 5 in FP64, a column round's 2.  (64
+// frames of qc n = 1944: 4, 8, 12, 16 wavefronts 133, 86, 72, 70; n = 648,
+// eleven groups: 4, 8, 11, 16 55, 40, 34, 34.)  A layer's rows, 16 to a
+// wavefront, are one round, and wider workgroups wait at its barriers.
+//
+// Frames share the CUs: the fewest wavefronts per frame, in fours (one to each
+// SIMD: sizes between place unevenly), with which the resident frames hold 16
+// on a CU, 24 for min-sum, whose rounds are mostly latency; but 8 for more than
+// twelve groups.  (4000 frames: qc n = 648 4, 5, 8, 11 wavefronts 270, 357,
+// 357, 506; n = 1944 4, 8, 12, 16 1221, 851, 1104, 1069; (3,6)-regular n =
+// 2040 462, 382, 395, 595; min-sum n = 1944 861, 565, 466, 647.)  Workgroups
+// that would fill a CU's 32 wavefronts in one pass did not all start at once
+// (1024 min-sum frames of n = 648: 4 and 8 wavefronts 56 and 73), and a size
+// that needs a second pass where a smaller one does not is no gain.  FP64
+// sum-product takes the wider of equals (1024 frames of n = 648: 4 and 8
+// wavefronts 325 and 299), and with early stop the wider always, which ends the
+// last pass's long frames sooner.  Layered frames: a layer's rows in one round, at
+// most 8 wavefronts where a CU holds two frames (4000 frames of qc n = 1944: 4,
+// 6, 8, 16 wavefronts 2239, 1638, 1633, 2603), and one to spare for the layers
+// of two wavefronts or less (n = 648: 1, 2, 3, 8 wavefronts 753, 481, 475, 800).
 template <class K>
 ldpc_status workgroup_threads(K kern, const Batch &b, size_t tsize, size_t lds, int max_threads, int &threads)
 {
-    const int64_t round = tsize == sizeof(float) ? 11 : 5, col_round = 2;
+    const bool f32 = tsize == sizeof(float);
+    const Job *main_job = &b.jobs[0];
+    int64_t most = -1;
     bool stops = false;
-    int widest = 2;  // a layer's few rows leave wider workgroups' wavefronts idle at every barrier
     for (int32_t i = 0; i < b.njobs; ++i) {
         const Job &j = b.jobs[i];
-        const Code &c = b.codes[j.code];
         stops |= (j.flags & LDPC_EARLY_STOP) != 0;
-        widest = std::max(widest, (j.flags & LDPC_LAYERED)
-                                      ? std::max((c.m / std::max(c.nlayers, 1) + 15) / 16, c.n / 256 + 1)
-                                      : max_threads / 64);
-    }
-    int64_t best = -1;
-    for (int w = 2; w * 64 <= max_threads && w <= widest; ++w) {
-        int per_cu = 0, cus = 0;
-        const ldpc_status rc = launch_shape(reinterpret_cast<const void *>(kern), lds, w * 64, per_cu, cus);
-        if (rc != LDPC_OK)
-            return rc;
-        const int64_t k = std::min<int64_t>(per_cu, (b.nitems + cus - 1) / cus);
-        int64_t work = 0;
-        for (int32_t i = 0; i < b.njobs; ++i) {
-            const Job &j = b.jobs[i];
-            const Code &c = b.codes[j.code];
-            const bool layered = (j.flags & LDPC_LAYERED) != 0;
-            const int64_t steps = layered ? std::max(c.nlayers, 1) : 1;
-            const int64_t rows = (c.m + steps - 1) / steps;
-            const int64_t per_wave = layered ? 16 : 32;
-            const int64_t g = (rows + per_wave - 1) / per_wave, cols = layered ? 0 : (c.n + 63) / 64;
-            const int64_t rest = (g % w + 3) / 4 * 4;
-            const int64_t latency = g / w * std::max<int64_t>(round, (w + 3) / 4 * 4) +
-                                    (rest > 0 ? std::max(round, rest) : 0) + (cols + w - 1) / w * col_round;
-            work += j.frames * steps * std::max(latency, k * g);
-        }
-        const int64_t t = work * ((b.nitems + k * cus - 1) / (k * cus));
-        if (best < 0 || t < best || (stops && tsize == sizeof(double) && t == best)) {
-            best = t;
-            threads = w * 64;
+        const int64_t work = static_cast<int64_t>(j.frames) * b.codes[j.code].m;
+        if (work > most) {
+            most = work;
+            main_job = &j;
         }
     }
+    const Code &c = b.codes[main_job->code];
+    const bool layered = (main_job->flags & LDPC_LAYERED) != 0, ms = (main_job->flags & LDPC_MIN_SUM) != 0;
+    const int max_waves = max_threads / 64, g = (c.m + 31) / 32, cols = (c.n + 63) / 64;
+    int per_cu = 0, cus = 0;
+    const auto shape = [&](int w) {
+        return launch_shape(reinterpret_cast<const void *>(kern), lds, w * 64, per_cu, cus);
+    };
+    ldpc_status rc = shape(4);
+    if (rc != LDPC_OK)
+        return rc;
+    const int64_t share = (b.nitems + cus - 1) / cus;  // frames per CU
+    int best = 4;
+    if (layered) {
+        const int most_rows = (c.layer_rows + 15) / 16;
+        const int mean_rows = (c.m / std::max(c.nlayers, 1) + 15) / 16;
+        if (share <= 1)
+            best = std::max({most_rows, c.n / 256 + 1, 2});
+        else if (mean_rows <= 2)
+            best = std::max(mean_rows, 1) + 1;
+        else {
+            rc = shape(8);
+            if (rc != LDPC_OK)
+                return rc;
+            best = std::min((most_rows + 3) / 4 * 4, per_cu >= 2 ? 8 : max_waves);
+        }
+        best = std::min(best, max_waves);
+    } else if (share <= 1) {
+        const int unit = ms ? 1 : 3, round = 3 * (f32 ? 11 : 5);  // in thirds
+        int least = 0;
+        for (int w = 2; w <= max_waves; ++w) {
+            const int rest = (g % w + 3) / 4 * 4;
+            const int time = std::max(unit * g, g / w * std::max(round, unit * ((w + 3) / 4 * 4)) +
+                                                    (rest > 0 ? std::max(round, unit * rest) : 0) +
+                                                    (cols + w - 1) / w * 6);
+            if (least == 0 || time < least) {
+                least = time;
+                best = w;
+            }
+        }
+    } else {
+        const int64_t enough = f32 ? (ms ? 24 : 16) : stops ? 24 : 16;
+        int64_t held = 0;
+        bool one_pass = false;
+        for (int w = g <= 12 ? 4 : 8; w <= max_waves && held < enough; w += 4) {
+            rc = shape(w);
+            if (rc != LDPC_OK)
+                return rc;
+            const int64_t waves = std::min<int64_t>(per_cu, share) * w;
+            if ((f32 && waves > 28 && share <= per_cu) || (one_pass && share > per_cu))
+                continue;
+            if (waves > held || (waves == held && !f32 && !ms)) {
+                held = waves;
+                best = w;
+                one_pass = f32 && share <= per_cu;
+            }
+        }
+    }
+    threads = best * 64;
     return LDPC_OK;
 }
 

@@ -113,6 +113,7 @@ struct ldpc_code_s {
     // in ascending order, in which no two rows share a variable.  Layer l is
     // rows [layer_ptr[l], layer_ptr[l+1]); layer_dmax[l] its largest degree.
     std::vector<int32_t> layer_ptr, layer_dmax;
+    int32_t layer_rows = 0;  // of the largest layer
     // Hash of the code's shape (sizes, lifting size, row and column degree
     // histograms): the key of tuning choices, which depend on shape only.
     uint64_t shape_hash = 0;
