@@ -354,6 +354,9 @@ fused::Code code_entry(const ldpc_code_s *c, size_t tsize, size_t limit)
     e.row_groups = t.row_groups;
     e.nlayers = static_cast<int32_t>(c->layer_dmax.size());
     e.layer_rows = c->layer_rows;
+    e.row_words = t.row_words;
+    e.col_words = t.col_words;
+    e.lay_words = t.lay_words;
     e.r_words = padded ? t.slot_words : e.E;
     e.row_grp = padded ? t.row_grp : t.row_grp_x;
     e.row_tab = padded ? t.row_tab : t.row_tab_x;

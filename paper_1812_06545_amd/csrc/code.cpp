@@ -160,6 +160,7 @@ void part_span(int32_t d, int part, int parts, int32_t &k0, int32_t &len)
 struct FusedOffsets {
     bool built = false, explicit_too = false;
     int32_t row_groups = 0, slot_words = 0;
+    int32_t row_words = 0, col_words = 0, lay_words = 0;
     size_t row_grp = 0, row_tab = 0, col_grp = 0, col_tab = 0;
     size_t row_grp_x = 0, row_tab_x = 0, row_pos_x = 0, col_tab_x = 0;
     size_t lay_ptr = 0, lay_grp = 0, lay_tab = 0;
@@ -196,6 +197,8 @@ FusedOffsets fused_tables(const HostLayout &h, const std::vector<int32_t> &layer
             quad_rows += x ? 4 : ((degree(order[32 * g]) + 1) / 2 + 3) / 4;
         grp_at = im.take(2 * static_cast<size_t>(o.row_groups), 0);
         tab_at = im.take(quad_rows * 256, inf);
+        if (!x)
+            o.row_words = static_cast<int32_t>(quad_rows * 256);
         if (x)
             *pos_at = im.take(quad_rows * 256, junk);
         int32_t *grp = im.words.data() + grp_at, *tab = im.words.data() + tab_at;
@@ -239,6 +242,8 @@ FusedOffsets fused_tables(const HostLayout &h, const std::vector<int32_t> &layer
         if (grp_at)
             *grp_at = im.take(2 * static_cast<size_t>(groups), 0);
         tab_at = im.take(quad_rows * 256, minus_zero);
+        if (!x)
+            o.col_words = static_cast<int32_t>(quad_rows * 256);
         int32_t *grp = grp_at ? im.words.data() + *grp_at : nullptr, *tab = im.words.data() + tab_at;
         int32_t quad_row = 0;
         for (int32_t g = 0; g < groups; ++g) {
@@ -283,6 +288,7 @@ FusedOffsets fused_tables(const HostLayout &h, const std::vector<int32_t> &layer
     o.lay_ptr = im.take(layers + 1, 0);
     o.lay_grp = im.take(2 * groups, 0);
     o.lay_tab = im.take(words, inf);
+    o.lay_words = static_cast<int32_t>(words);
     int32_t *ptr = im.words.data() + o.lay_ptr, *grp = im.words.data() + o.lay_grp;
     int32_t *tab = im.words.data() + o.lay_tab;
     size_t g = 0, base = 0;
@@ -344,6 +350,9 @@ ldpc_status upload(const HostLayout &h, int32_t Z, ldpc_code_s *c)
         ldpc::FusedTables &t = c->fused;
         t.row_groups = fo.row_groups;
         t.slot_words = fo.slot_words;
+        t.row_words = fo.row_words;
+        t.col_words = fo.col_words;
+        t.lay_words = fo.lay_words;
         t.row_grp = base + fo.row_grp;
         t.row_tab = base + fo.row_tab;
         t.col_grp = base + fo.col_grp;

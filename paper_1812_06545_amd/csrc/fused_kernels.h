@@ -65,6 +65,7 @@ struct Code {
     int32_t row_groups, nlayers;
     int32_t r_words;  // message words of a flooding frame (E with an explicit order)
     int32_t m, layer_rows;  // rows; rows of the largest layer
+    int32_t row_words, col_words, lay_words;  // sizes of the tables
     const int32_t *row_grp, *row_tab, *row_pos, *col_grp, *col_tab, *lay_ptr, *lay_grp, *lay_tab;
 };
 
@@ -84,7 +85,8 @@ struct Job {
 struct Batch {
     int32_t njobs, ncodes;
     int32_t nitems, frames_per_item;
-    uint32_t flags_at;  // LDS address of the workgroup's flag words
+    uint32_t flags_at;   // LDS address of the workgroup's flag words
+    uint32_t tables_at;  // and of its code's tables (kernels that copy them)
     int32_t begin[kMaxJobs];
     Code codes[kMaxCodes];
     Job jobs[kMaxJobs];
@@ -216,11 +218,30 @@ __device__ __forceinline__ ArithF64::Acc lane_swap(const ArithF64::Acc &v)
 typedef int32_t Quad __attribute__((ext_vector_type(4)));
 constexpr int quads(int d) { return (d + 3) / 4; }
 
+// A table: in device memory, or (LT) the workgroup's copy in LDS.  Where every
+// frame has a CU to itself, nothing hides the L2 latency that starts each
+// group's work, and the CU's LDS is mostly free: the frame's workgroup copies
+// its code's tables there first, if they fit.  us per call of 10 iterations,
+// tables in L2 and in LDS: 24 layered frames of qc n = 1296, rate 2/3, early stop
+// 104 and 92; a plan of 64 frames of four codes 48.8 and 45.6; one frame of
+// (3,6)-regular n = 2040 40 and 36; of qc n = 648 34 and 33.
+template <bool LT>
+using Table = typename std::conditional<LT, const Lds<Quad> *, const Quad *>::type;
+template <bool LT>
+__device__ __forceinline__ Table<LT> table_at(const int32_t *tab, uint32_t copy)
+{
+    if constexpr (LT)
+        return lds_at<Quad>(copy);
+    else
+        return reinterpret_cast<const Quad *>(tab);
+}
+
 // Table addresses of D slots, from this lane's first quad, quads `stride` apart.
 template <class T, int D>
 struct Addresses {
     Quad q[quads(D)];
-    __device__ __forceinline__ void load(const Quad *tab, int stride)
+    template <class Tab>
+    __device__ __forceinline__ void load(Tab tab, int stride)
     {
 #pragma unroll
         for (int i = 0; i < quads(D); ++i)
@@ -258,8 +279,8 @@ __device__ __forceinline__ bool some_odd(uint64_t half_parity)
 // the arithmetic.  PAR: `odd` is set if a row of the wavefront is unsatisfied
 // by the decision [L < 0] that the gathered posteriors hold (one comparison
 // per slot; the parities are lane masks in scalar registers).
-template <class A, int D, bool PAR, bool POS>
-__device__ __forceinline__ void half_row(const Quad *tab, const Messages<typename A::T, D, POS> &msg, bool &odd)
+template <class A, int D, bool PAR, bool POS, class Tab>
+__device__ __forceinline__ void half_row(Tab tab, const Messages<typename A::T, D, POS> &msg, bool &odd)
 {
     using T = typename A::T;
     Addresses<T, D> ci;
@@ -357,8 +378,8 @@ __device__ __forceinline__ void min_row(const typename A::T (&q)[D], typename A:
 }
 
 // half_row under the min-sum rule.
-template <class A, int D, bool PAR, bool POS>
-__device__ __forceinline__ void ms_half_row(const Quad *tab, const Messages<typename A::T, D, POS> &msg, bool &odd,
+template <class A, int D, bool PAR, bool POS, class Tab>
+__device__ __forceinline__ void ms_half_row(Tab tab, const Messages<typename A::T, D, POS> &msg, bool &odd,
                                             typename A::T scale, typename A::T offset)
 {
     using T = typename A::T;
@@ -389,8 +410,8 @@ __device__ __forceinline__ void ms_half_row(const Quad *tab, const Messages<type
 // halves, which gives every lane O_i in the same association as the streaming
 // layer kernel; new posteriors are stored at once.  `stride`: quads of one
 // slot quad of the group (4 lanes per row).
-template <class A, int D>
-__device__ __forceinline__ void layered_quarter(const Quad *tab, int stride, bool ms, typename A::T scale,
+template <class A, int D, class Tab>
+__device__ __forceinline__ void layered_quarter(Tab tab, int stride, bool ms, typename A::T scale,
                                                 typename A::T offset)
 {
     using T = typename A::T;
@@ -434,8 +455,8 @@ __device__ __forceinline__ void layered_quarter(const Quad *tab, int stride, boo
 }
 
 // Exact-length bodies for D in [D, DB], by the group's longest part.
-template <class A, int D, int DB, bool PAR, bool POS, bool MS>
-__device__ __forceinline__ void half_row_dispatch(int d, const Quad *tab, const Quad *pos, uint32_t ra, bool &odd,
+template <class A, int D, int DB, bool PAR, bool POS, bool MS, class Tab>
+__device__ __forceinline__ void half_row_dispatch(int d, Tab tab, const Quad *pos, uint32_t ra, bool &odd,
                                                   typename A::T scale, typename A::T offset)
 {
     if constexpr (D < DB) {
@@ -454,8 +475,8 @@ __device__ __forceinline__ void half_row_dispatch(int d, const Quad *tab, const 
         half_row<A, D, PAR, POS>(tab, msg, odd);
 }
 
-template <class A, int D, int DB>
-__device__ __forceinline__ void layered_dispatch(int d, const Quad *tab, int stride, bool ms, typename A::T scale,
+template <class A, int D, int DB, class Tab>
+__device__ __forceinline__ void layered_dispatch(int d, Tab tab, int stride, bool ms, typename A::T scale,
                                                  typename A::T offset)
 {
     if constexpr (D < DB) {
@@ -468,8 +489,8 @@ __device__ __forceinline__ void layered_dispatch(int d, const Quad *tab, int str
 }
 
 // acc plus a column's messages in ascending row order, D slots (dummies add -0).
-template <class A, int D>
-__device__ __forceinline__ typename A::T column_sum(const Quad *tab, typename A::T acc)
+template <class A, int D, class Tab>
+__device__ __forceinline__ typename A::T column_sum(Tab tab, typename A::T acc)
 {
     using T = typename A::T;
     if constexpr (D > 0) {
@@ -486,8 +507,8 @@ __device__ __forceinline__ typename A::T column_sum(const Quad *tab, typename A:
     return acc;
 }
 constexpr int kColExact = 16;  // longer columns run in steps of four slots
-template <class A, int D>
-__device__ __forceinline__ typename A::T column_dispatch(int d, const Quad *tab, typename A::T acc)
+template <class A, int D, class Tab>
+__device__ __forceinline__ typename A::T column_dispatch(int d, Tab tab, typename A::T acc)
 {
     if constexpr (D <= kColExact) {
         if (d == D)
@@ -530,8 +551,8 @@ __device__ __forceinline__ void start_frame(const Code &c, const typename A::T *
 }
 
 // One frame on the flooding schedule; returns the iterations it ran.
-template <class A, int DB, Instance INST>
-__device__ __forceinline__ int32_t decode_frame(const Code &c, const Job &job, int64_t f, Vote &vote)
+template <class A, int DB, Instance INST, bool LT>
+__device__ __forceinline__ int32_t decode_frame(const Code &c, const Job &job, int64_t f, uint32_t tables, Vote &vote)
 {
     using T = typename A::T;
     constexpr uint32_t TS = sizeof(T);
@@ -540,15 +561,16 @@ __device__ __forceinline__ int32_t decode_frame(const Code &c, const Job &job, i
     const int32_t n = c.n, col_groups = (n + 63) / 64;
     const T *llr = static_cast<const T *>(job.llr) + f * n;
     Lds<T> *sL = lds_at<T>(0);
-    const Quad *row_tab = reinterpret_cast<const Quad *>(c.row_tab) + lane;
+    const Table<LT> row_tab = table_at<LT>(c.row_tab, tables) + lane;
     const Quad *row_pos = reinterpret_cast<const Quad *>(c.row_pos) + lane;
-    const Quad *col_tab = reinterpret_cast<const Quad *>(c.col_tab) + lane;
+    const Table<LT> col_tab =
+        table_at<LT>(c.col_tab, tables + 4u * static_cast<uint32_t>(c.row_words)) + lane;
     const uint32_t r0 = TS * static_cast<uint32_t>(fused_first_message(n) + lane);
     start_frame<A>(c, llr, c.r_words);
 
     const bool es = (job.flags & LDPC_EARLY_STOP) != 0;
     const bool ms = INST == kMinSum || (INST == kAnyJob && (job.flags & LDPC_MIN_SUM) != 0);
-    const bool pos = INST == kAnyJob && c.row_pos != nullptr;
+    const bool pos = INST == kAnyJob && !LT && c.row_pos != nullptr;
     const T scale = static_cast<T>(job.ms_scale), offset = static_cast<T>(job.ms_offset * A::kIn);
     for (int32_t t = 1; t <= job.max_iter; ++t) {
         bool odd = false;
@@ -557,19 +579,19 @@ __device__ __forceinline__ int32_t decode_frame(const Code &c, const Job &job, i
             const int32_t w = c.row_grp[2 * g], first = c.row_grp[2 * g + 1];
             const int d = w >> 16;
             const uint32_t ra = r0 + TS * 64u * static_cast<uint32_t>(w & 0xffff);
-            const Quad *tab = row_tab + static_cast<int64_t>(first) * 64;
+            const Table<LT> tab = row_tab + first * 64;
             const Quad *pt = row_pos + static_cast<int64_t>(first) * 64;
             if (d == 0)
                 continue;
             if (ms) {
                 if constexpr (INST == kMinSum || INST == kAnyJob) {
-                    if (INST == kAnyJob && pos)
+                    if (INST == kAnyJob && !LT && pos)
                         half_row_dispatch<A, DB / 2, DB / 2, true, true, true>(d, tab, pt, ra, odd, scale, offset);
                     else
                         half_row_dispatch<A, 1, DB / 2, true, false, true>(d, tab, pt, ra, odd, scale, offset);
                 }
             } else if constexpr (INST != kMinSum) {
-                if (INST == kAnyJob && pos)
+                if (INST == kAnyJob && !LT && pos)
                     half_row_dispatch<A, DB / 2, DB / 2, true, true, false>(d, tab, pt, ra, odd, scale, offset);
                 else if (es)
                     half_row_dispatch<A, 1, DB / 2, true, false, false>(d, tab, pt, ra, odd, scale, offset);
@@ -590,7 +612,7 @@ __device__ __forceinline__ int32_t decode_frame(const Code &c, const Job &job, i
             if (j < n)
                 acc = llr[j] * T(A::kIn);
             const int32_t d = c.col_grp[2 * g], first = c.col_grp[2 * g + 1];  // longest column, first quad
-            const T v = column_dispatch<A, 0>(d, col_tab + static_cast<int64_t>(first) * 64, acc);
+            const T v = column_dispatch<A, 0>(d, col_tab + first * 64, acc);
             if (j < n)
                 sL[j] = v;
         }
@@ -604,13 +626,16 @@ __device__ __forceinline__ int32_t decode_frame(const Code &c, const Job &job, i
 // With early stop the syndrome of [L < 0] is tested before the first pass and
 // after every pass but the last.  Each row's arithmetic is the plain layered
 // path's, bit for bit.  Returns the passes run.
-template <class A, int DB, Instance INST>
-__device__ __forceinline__ int32_t decode_frame_layered(const Code &c, const Job &job, int64_t f, Vote &vote)
+template <class A, int DB, Instance INST, bool LT>
+__device__ __forceinline__ int32_t decode_frame_layered(const Code &c, const Job &job, int64_t f, uint32_t tables,
+                                                        Vote &vote)
 {
     using T = typename A::T;
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int lane = static_cast<int>(threadIdx.x & 63), nwaves = static_cast<int>(blockDim.x >> 6);
     const T *llr = static_cast<const T *>(job.llr) + f * c.n;
+    const Table<LT> row_tab = table_at<LT>(c.row_tab, tables) + lane;
+    const Table<LT> lay_tab = table_at<LT>(c.lay_tab, tables + 4u * static_cast<uint32_t>(c.row_words));
     start_frame<A>(c, llr, c.E);
 
     // Whether some row is unsatisfied by the decision [L < 0], from the
@@ -620,7 +645,7 @@ __device__ __forceinline__ int32_t decode_frame_layered(const Code &c, const Job
         bool odd = false;
         for (int g = wave; g < c.row_groups && !odd; g += nwaves) {
             const int32_t w = c.row_grp[2 * g], first = c.row_grp[2 * g + 1];
-            const Quad *tab = reinterpret_cast<const Quad *>(c.row_tab) + (static_cast<int64_t>(first) * 64 + lane);
+            const Table<LT> tab = row_tab + first * 64;
             uint64_t par = 0;
             for (int i = 0; i < quads(w >> 16); ++i) {
                 Addresses<T, 4> ci;
@@ -649,8 +674,7 @@ __device__ __forceinline__ int32_t decode_frame_layered(const Code &c, const Job
                 const int rows = w & 0xff, d = w >> 8;  // word 1: first quad
                 if ((lane & 15) < rows && d > 0)
                     layered_dispatch<A, 1, DB / 4>(
-                        d, reinterpret_cast<const Quad *>(c.lay_tab) + (first + (lane >> 4) * rows + (lane & 15)),
-                        4 * rows, ms, scale, offset);
+                        d, lay_tab + (first + (lane >> 4) * rows + (lane & 15)), 4 * rows, ms, scale, offset);
             }
             __syncthreads();
         }
@@ -718,7 +742,21 @@ constexpr int kFusedWavesPerEU = std::is_same<A, ArithF32>::value ? 4 : 2;
 template <class A>
 constexpr int kFusedMaxThreads = std::is_same<A, ArithF32>::value ? kMaxThreads : kBaseThreads;
 
-template <class A, int DB, Instance INST = kAnyJob>
+// The code's tables for a job, copied into LDS at b.tables_at (published by the
+// barrier of start_frame).
+__device__ __forceinline__ void copy_tables(const Batch &b, const Code &c, const Job &job)
+{
+    Lds<Quad> *to = lds_at<Quad>(b.tables_at);
+    const int32_t rows = c.row_words / 4, rest = ((job.flags & LDPC_LAYERED) ? c.lay_words : c.col_words) / 4;
+    const Quad *row_tab = reinterpret_cast<const Quad *>(c.row_tab);
+    const Quad *tab = reinterpret_cast<const Quad *>((job.flags & LDPC_LAYERED) ? c.lay_tab : c.col_tab);
+    for (int i = static_cast<int>(threadIdx.x); i < rows; i += static_cast<int>(blockDim.x))
+        to[i] = row_tab[i];
+    for (int i = static_cast<int>(threadIdx.x); i < rest; i += static_cast<int>(blockDim.x))
+        to[rows + i] = tab[i];
+}
+
+template <class A, int DB, Instance INST = kAnyJob, bool LT = false>
 __global__ __launch_bounds__(kFusedMaxThreads<A>) __attribute__((amdgpu_waves_per_eu(kFusedWavesPerEU<A>))) void k_fused(const Batch b, uint32_t *counter)
 {
     Lds<int32_t> *flags = lds_at<int32_t>(b.flags_at);
@@ -731,14 +769,16 @@ __global__ __launch_bounds__(kFusedMaxThreads<A>) __attribute__((amdgpu_waves_pe
         const Code &c = b.codes[job.code];
         const int32_t f0 = (item - b.begin[j]) * b.frames_per_item;
         uint32_t drawn = 0;
+        if constexpr (LT)
+            copy_tables(b, c, job);
         for (int32_t f = f0; f < f0 + b.frames_per_item && f < job.frames; ++f) {
             if (f > f0)
                 __syncthreads();  // the last frame's posteriors have been read
             int32_t it;
             if (INST == kLayered || (INST == kAnyJob && (job.flags & LDPC_LAYERED)))
-                it = decode_frame_layered<A, DB, INST>(c, job, f, vote);
+                it = decode_frame_layered<A, DB, INST, LT>(c, job, f, b.tables_at, vote);
             else
-                it = decode_frame<A, DB, INST>(c, job, f, vote);
+                it = decode_frame<A, DB, INST, LT>(c, job, f, b.tables_at, vote);
             if (f == f0)
                 drawn = draw_item(counter);
             write_frame<A>(c, job, f, it);
@@ -839,6 +879,23 @@ inline size_t batch_lds_bytes(const Batch &b, size_t tsize)
         bytes = std::max(bytes, lds_bytes(c.n, (b.jobs[i].flags & LDPC_LAYERED) ? c.E : c.r_words, tsize));
     }
     return bytes;
+}
+
+// LDS bytes of a launch whose workgroups hold their code's tables too, or 0 if
+// a job's tables lie in CSR order; sets where they start.
+inline size_t batch_table_lds_bytes(const Batch &b, size_t tsize, uint32_t &tables_at)
+{
+    const size_t frame = batch_lds_bytes(b, tsize) - kFlagWords * sizeof(int32_t);
+    size_t words = 0;
+    for (int32_t i = 0; i < b.njobs; ++i) {
+        const Code &c = b.codes[b.jobs[i].code];
+        if (c.row_pos != nullptr)
+            return 0;
+        const bool layered = (b.jobs[i].flags & LDPC_LAYERED) != 0;
+        words = std::max(words, static_cast<size_t>(c.row_words) + static_cast<size_t>(layered ? c.lay_words : c.col_words));
+    }
+    tables_at = static_cast<uint32_t>(frame);
+    return frame + words * sizeof(int32_t) + kFlagWords * sizeof(int32_t);
 }
 
 // Workgroup size of a launch whose caller left it at kBaseThreads, for the job
@@ -960,11 +1017,11 @@ void launch_zero_counter(uint32_t *counter, hipStream_t s, bool profile);
 template <class A, int DB>
 ldpc_status launch_fused_bucket(fused::Batch &batch, uint32_t *counter, int threads, hipStream_t s, bool profile);
 
+// lds_bytes: the launch's LDS, its flag words last.
 template <class A, class K>
-ldpc_status launch_fused_kernel(K kern, fused::Batch &batch, uint32_t *counter, int threads, hipStream_t s,
-                                bool profile)
+ldpc_status launch_fused_kernel(K kern, fused::Batch &batch, size_t lds_bytes, uint32_t *counter, int threads,
+                                hipStream_t s, bool profile)
 {
-    const size_t lds_bytes = fused::batch_lds_bytes(batch, sizeof(typename A::T));
     batch.flags_at = static_cast<uint32_t>(lds_bytes - fused::kFlagWords * sizeof(int32_t));
     if (threads == fused::kBaseThreads) {
         const ldpc_status rc = fused::workgroup_threads(kern, batch, sizeof(typename A::T), lds_bytes,
@@ -988,23 +1045,44 @@ ldpc_status launch_fused_kernel(K kern, fused::Batch &batch, uint32_t *counter, 
     return hipGetLastError() == hipSuccess ? LDPC_OK : LDPC_EDEVICE;
 }
 
+// Launches an instance: with the tables copied to LDS where every item has a CU
+// to itself and they fit, else with the tables in L2.
+template <class A, int DB, fused::Instance INST>
+ldpc_status launch_fused_instance(fused::Batch &batch, uint32_t *counter, int threads, hipStream_t s, bool profile)
+{
+    constexpr size_t tsize = sizeof(typename A::T);
+    int dev = 0, cus = 0, limit = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipDeviceGetAttribute(&limit, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
+        return LDPC_EDEVICE;
+    if (batch.nitems <= cus) {
+        const size_t bytes = fused::batch_table_lds_bytes(batch, tsize, batch.tables_at);
+        if (bytes != 0 && bytes <= static_cast<size_t>(limit))
+            return launch_fused_kernel<A>(fused::k_fused<A, DB, INST, true>, batch, bytes, counter, threads, s,
+                                          profile);
+    }
+    return launch_fused_kernel<A>(fused::k_fused<A, DB, INST, false>, batch, fused::batch_lds_bytes(batch, tsize),
+                                  counter, threads, s, profile);
+}
+
 #define LDPC_DEFINE_FUSED_BUCKET(A_, DB_)                                                                        \
     template <>                                                                                                  \
     ldpc_status launch_fused_bucket<A_, DB_>(fused::Batch & batch, uint32_t *counter, int threads,               \
                                              hipStream_t s, bool profile)                                        \
     {                                                                                                            \
-        const auto launch = [&](auto kern) {                                                                     \
-            return launch_fused_kernel<A_>(kern, batch, counter, threads, s, profile);                           \
-        };                                                                                                       \
         if constexpr (std::is_same<A_, ArithF32>::value) {                                                       \
             switch (fused::batch_instance(batch)) {                                                              \
-            case fused::kFlood: return launch(fused::k_fused<A_, DB_, fused::kFlood>);                           \
-            case fused::kLayered: return launch(fused::k_fused<A_, DB_, fused::kLayered>);                       \
-            case fused::kMinSum: return launch(fused::k_fused<A_, DB_, fused::kMinSum>);                         \
+            case fused::kFlood:                                                                                  \
+                return launch_fused_instance<A_, DB_, fused::kFlood>(batch, counter, threads, s, profile);       \
+            case fused::kLayered:                                                                                \
+                return launch_fused_instance<A_, DB_, fused::kLayered>(batch, counter, threads, s, profile);     \
+            case fused::kMinSum:                                                                                 \
+                return launch_fused_instance<A_, DB_, fused::kMinSum>(batch, counter, threads, s, profile);      \
             default: break;                                                                                      \
             }                                                                                                    \
         }                                                                                                        \
-        return launch(fused::k_fused<A_, DB_>);                                                                  \
+        return launch_fused_instance<A_, DB_, fused::kAnyJob>(batch, counter, threads, s, profile);              \
     }
 
 }  // namespace ldpc

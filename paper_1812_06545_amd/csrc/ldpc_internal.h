@@ -79,6 +79,7 @@ inline int32_t fused_first_message(int32_t n)
 struct FusedTables {
     int32_t row_groups = 0;
     int32_t slot_words = 0;  // message words of the padded slot order
+    int32_t row_words = 0, col_words = 0, lay_words = 0;  // sizes of row_tab, col_tab, lay_tab
     const int32_t *row_grp = nullptr, *row_tab = nullptr, *col_grp = nullptr, *col_tab = nullptr;
     const int32_t *row_grp_x = nullptr, *row_tab_x = nullptr, *row_pos_x = nullptr, *col_tab_x = nullptr;
     const int32_t *lay_ptr = nullptr, *lay_grp = nullptr, *lay_tab = nullptr;
