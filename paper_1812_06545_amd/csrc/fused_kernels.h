@@ -572,11 +572,18 @@ __device__ __forceinline__ int32_t decode_frame(const Code &c, const Job &job, i
     const bool ms = INST == kMinSum || (INST == kAnyJob && (job.flags & LDPC_MIN_SUM) != 0);
     const bool pos = INST == kAnyJob && !LT && c.row_pos != nullptr;
     const T scale = static_cast<T>(job.ms_scale), offset = static_cast<T>(job.ms_offset * A::kIn);
+    // Alone on its CU (LT), a wavefront keeps the words of its first groups: a
+    // scalar load less in every phase.  Where others hide it, the selects cost more.
+    const int32_t row0 = min(wave, c.row_groups - 1), col0 = min(wave, col_groups - 1);
+    const int32_t row_w0 = LT && row0 >= 0 ? c.row_grp[2 * row0] : 0;
+    const int32_t row_first0 = LT && row0 >= 0 ? c.row_grp[2 * row0 + 1] : 0;
+    const int32_t col_w0 = LT ? c.col_grp[2 * col0] : 0, col_first0 = LT ? c.col_grp[2 * col0 + 1] : 0;
     for (int32_t t = 1; t <= job.max_iter; ++t) {
         bool odd = false;
         for (int g = wave; g < c.row_groups; g += nwaves) {
             // group word 0: message slots before the group (16 bits), its longest half; word 1: first quad
-            const int32_t w = c.row_grp[2 * g], first = c.row_grp[2 * g + 1];
+            const int32_t w = LT && g == wave ? row_w0 : c.row_grp[2 * g];
+            const int32_t first = LT && g == wave ? row_first0 : c.row_grp[2 * g + 1];
             const int d = w >> 16;
             const uint32_t ra = r0 + TS * 64u * static_cast<uint32_t>(w & 0xffff);
             const Table<LT> tab = row_tab + first * 64;
@@ -611,7 +618,9 @@ __device__ __forceinline__ int32_t decode_frame(const Code &c, const Job &job, i
             T acc = T(0);
             if (j < n)
                 acc = llr[j] * T(A::kIn);
-            const int32_t d = c.col_grp[2 * g], first = c.col_grp[2 * g + 1];  // longest column, first quad
+            // longest column, first quad
+            const int32_t d = LT && g == wave ? col_w0 : c.col_grp[2 * g];
+            const int32_t first = LT && g == wave ? col_first0 : c.col_grp[2 * g + 1];
             const T v = column_dispatch<A, 0>(d, col_tab + first * 64, acc);
             if (j < n)
                 sL[j] = v;
@@ -664,18 +673,42 @@ __device__ __forceinline__ int32_t decode_frame_layered(const Code &c, const Job
     const T scale = static_cast<T>(job.ms_scale), offset = static_cast<T>(job.ms_offset * A::kIn);
     if (es && !unsatisfied())
         return 0;
+    // The group a wavefront takes first in a layer, and where the layer after
+    // it ends, are read a layer ahead, by vector loads (scalar ones return out
+    // of order, so that every LDS wait would wait for them too): the two reads
+    // depend on each other and would start every layer with both latencies.
+    int lane0 = 0;
+    asm("" : "+v"(lane0));  // the same in every lane, which the compiler does not know
+    const int32_t nlayers = c.nlayers, ngroups = c.lay_ptr[nlayers];
+    auto group_words = [&](int32_t g, int32_t &w, int32_t &first) {
+        const int32_t *at = c.lay_grp + 2 * min(g, ngroups - 1) + lane0;
+        w = at[0];
+        first = at[1];
+    };
+    auto layer_after = [&](int32_t l) { return l + 1 == nlayers ? 0 : l + 1; };
+    int32_t begin = 0, end = c.lay_ptr[1], w_ahead, first_ahead;
+    int32_t end_ahead = c.lay_ptr[layer_after(0) + 1 + lane0];
+    group_words(wave, w_ahead, first_ahead);
     for (int32_t t = 1; t <= job.max_iter; ++t) {
-        int32_t end = c.lay_ptr[0];
-        for (int32_t l = 0; l < c.nlayers; ++l) {
-            const int32_t begin = end;
-            end = c.lay_ptr[l + 1];
-            for (int g = begin + wave; g < end; g += nwaves) {
-                const int32_t w = c.lay_grp[2 * g], first = c.lay_grp[2 * g + 1];
-                const int rows = w & 0xff, d = w >> 8;  // word 1: first quad
+        for (int32_t l = 0; l < nlayers; ++l) {
+            const int32_t next = layer_after(l), next_begin = next == 0 ? 0 : end;
+            const int32_t next_end = __builtin_amdgcn_readfirstlane(end_ahead);
+            int32_t w = __builtin_amdgcn_readfirstlane(w_ahead), first = __builtin_amdgcn_readfirstlane(first_ahead);
+            group_words(next_begin + wave, w_ahead, first_ahead);
+            end_ahead = c.lay_ptr[layer_after(next) + 1 + lane0];
+            for (int g = begin + wave; g < end;) {
+                const int rows = w & 0xff, d = w >> 8;  // first: the group's first quad
                 if ((lane & 15) < rows && d > 0)
                     layered_dispatch<A, 1, DB / 4>(
                         d, lay_tab + (first + (lane >> 4) * rows + (lane & 15)), 4 * rows, ms, scale, offset);
+                g += nwaves;
+                if (g < end) {
+                    w = c.lay_grp[2 * g];
+                    first = c.lay_grp[2 * g + 1];
+                }
             }
+            begin = next_begin;
+            end = next_end;
             __syncthreads();
         }
         if (es && t < job.max_iter && !unsatisfied())
