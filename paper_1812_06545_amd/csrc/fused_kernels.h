@@ -116,10 +116,11 @@ constexpr int kBaseThreads = 512, kMaxThreads = 1024;
 constexpr int kInfWord = 0, kMinusZeroWord = 1, kJunkWord = 2;  // junk: a dummy's message (any finite value)
 constexpr int kFlagWords = 4, kItemFlag = 3;                    // three vote words, then the workgroup's next item
 
-// Bytes for the flag words and a frame of n variables and `r_words` messages.
+// Bytes for the flag words and a frame of n variables and `r_words` messages
+// (cleared by fours).
 inline size_t lds_bytes(int32_t n, int64_t r_words, size_t tsize)
 {
-    return align_up((static_cast<size_t>(fused_first_message(n)) + static_cast<size_t>(r_words)) * tsize, 16) +
+    return (static_cast<size_t>(fused_first_message(n)) + align_up(static_cast<size_t>(r_words), 4)) * tsize +
            kFlagWords * sizeof(int32_t);
 }
 
@@ -526,6 +527,16 @@ __device__ __forceinline__ typename A::T column_dispatch(int d, Tab tab, typenam
 // it (FP32).
 enum Instance { kAnyJob = 0, kFlood = 1, kLayered = 2, kMinSum = 3 };
 
+// Four consecutive values of a frame's arrays.  Frames are moved by fours
+// where n and the caller's pointers allow it (frame f starts f n values in).
+template <class T>
+using Four = T __attribute__((ext_vector_type(4)));
+template <class T>
+__device__ __forceinline__ bool by_four(int32_t n, const void *p)
+{
+    return (n & 3) == 0 && (reinterpret_cast<uintptr_t>(p) & (4 * sizeof(T) - 1)) == 0;
+}
+
 // A frame's posteriors (the channel values), the dummies' constants and its
 // messages, which start at 0: the first iteration then forms q = L - 0 = L
 // exactly, as the streaming kernels' first iteration, with the same code as
@@ -537,16 +548,26 @@ __device__ __forceinline__ void start_frame(const Code &c, const typename A::T *
     const int tid = static_cast<int>(threadIdx.x), NT = static_cast<int>(blockDim.x);
     const int32_t n = c.n;
     Lds<T> *sL = lds_at<T>(0);
-    for (int j = tid; j < n; j += NT)
-        sL[j] = llr[j] * T(A::kIn);
+    if (by_four<T>(n, llr)) {
+        for (int j = 4 * tid; j < n; j += 4 * NT) {
+            Four<T> v = *reinterpret_cast<const Four<T> *>(llr + j);
+            v *= T(A::kIn);
+            *reinterpret_cast<Lds<Four<T>> *>(sL + j) = v;
+        }
+    } else {
+        for (int j = tid; j < n; j += NT)
+            sL[j] = llr[j] * T(A::kIn);
+    }
     if (tid == 0) {
         sL[n + kInfWord] = T(__builtin_huge_val());
         sL[n + kMinusZeroWord] = T(-0.0);
         sL[n + kJunkWord] = T(0);
     }
-    Lds<T> *sR = sL + fused_first_message(n);
-    for (int e = tid; e < r_words; e += NT)
-        sR[e] = T(0);
+    // whole fours: the messages start at a multiple of four words, and
+    // lds_bytes counts their last four
+    Lds<Four<T>> *sR = reinterpret_cast<Lds<Four<T>> *>(sL + fused_first_message(n));
+    for (int e = tid; 4 * e < r_words; e += NT)
+        sR[e] = Four<T>(T(0));
     __syncthreads();
 }
 
@@ -729,6 +750,26 @@ __device__ __forceinline__ void write_frame(const Code &c, const Job &job, int64
     const T *llr = static_cast<const T *>(job.llr) + f * n;
     uint8_t *bits = job.bits + f * n;
     T *post = job.post ? static_cast<T *>(job.post) + f * n : nullptr;
+    if (by_four<T>(n, llr) && by_four<T>(n, post) && by_four<uint8_t>(n, bits)) {
+        for (int j = 4 * tid; j < n; j += 4 * NT) {
+            Four<T> v = *reinterpret_cast<const Lds<Four<T>> *>(sL + j);
+            uint32_t four = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                four |= static_cast<uint32_t>(v[k] < T(0)) << (8 * k);
+            *reinterpret_cast<uint32_t *>(bits + j) = four;
+            if (post) {
+                if (it == 0)
+                    v = *reinterpret_cast<const Four<T> *>(llr + j);
+                else
+                    v *= T(A::kOut);
+                *reinterpret_cast<Four<T> *>(post + j) = v;
+            }
+        }
+        if (tid == 0)
+            job.iters[f] = it;
+        return;
+    }
     for (int j = tid; j < n; j += NT) {
         const T v = sL[j];
         bits[j] = static_cast<uint8_t>(v < T(0));

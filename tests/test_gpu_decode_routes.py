@@ -109,3 +109,43 @@ def test_few_frames_match_many(L, name, dtype, rule):
                 assert torch.equal(a, b[:frames])
         if es and iters == 9:
             assert len(set(want[1].tolist())) > 1
+
+
+@pytest.mark.parametrize("shift", [1, 2, 3])
+def test_unaligned_buffers(L, shift):
+    """Frames are moved by fours where n and the pointers allow it: buffers that
+    start `shift` elements off a 16-byte boundary (and, for the bits, `shift`
+    bytes off a word) give the aligned buffers' outputs, and nothing before or
+    behind them is written."""
+    import torch
+    code = codes.qc_code(12, 24, 27, 31)
+    h = L.Code.from_workload(code)
+    rng = np.random.default_rng(45)
+    frames, n = 9, code.n
+    x = torch.from_numpy(rng.normal(2.0, 2.0, size=(frames, n)).astype(np.float32)).cuda()
+    for layered in (False, True):
+        want = L.Job(h, x, 5, early_stop=True, layered=layered)
+        L.decode_batch([want])
+        print(f"[gpu] unaligned shift={shift} layered={layered}", flush=True)
+
+        def off(dtype, fill):
+            whole = torch.full((frames * n + 8,), fill, dtype=dtype, device="cuda")
+            return whole, whole[shift:shift + frames * n].view(frames, n)
+        for moved in ("llr", "bits", "posterior", "all"):
+            job = L.Job(h, x, 5, early_stop=True, layered=layered)
+            edges = []
+            if moved in ("llr", "all"):
+                _, job.llr = off(torch.float32, 0.0)
+                job.llr.copy_(x)
+            if moved in ("bits", "all"):
+                whole, job.bits = off(torch.uint8, 7)
+                edges.append(whole)
+            if moved in ("posterior", "all"):
+                whole, job.posterior = off(torch.float32, 7.0)
+                edges.append(whole)
+            L.decode_batch([job])
+            torch.cuda.synchronize()
+            assert torch.equal(job.bits, want.bits) and torch.equal(job.iters, want.iters)
+            assert torch.equal(job.posterior, want.posterior)
+            for whole in edges:
+                assert (whole[:shift] == 7).all() and (whole[shift + frames * n:] == 7).all()
