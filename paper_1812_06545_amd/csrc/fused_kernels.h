@@ -670,26 +670,45 @@ __device__ __forceinline__ int32_t decode_frame_layered(const Code &c, const Job
 
     // Whether some row is unsatisfied by the decision [L < 0], from the
     // flooding table.  A wavefront stops at its first group of 32 rows holding
-    // one (the answer is then known; in most passes that is the first group).
+    // one (the answer is then known; in most passes that is the first group,
+    // whose addresses therefore stay in registers).
+    const bool es = (job.flags & LDPC_EARLY_STOP) != 0;
+    constexpr int kFirstQuads = quads(DB / 2);
+    Quad first_quads[kFirstQuads];
+    int first_slots = 0;
+    if (es && wave < c.row_groups) {
+        first_slots = c.row_grp[2 * wave] >> 16;
+        const Table<LT> tab = row_tab + c.row_grp[2 * wave + 1] * 64;
+#pragma unroll
+        for (int i = 0; i < kFirstQuads; ++i)
+            if (4 * i < first_slots)
+                first_quads[i] = tab[i * 64];
+    }
+    auto parity_of = [&](const Quad &q, uint64_t &par) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            par ^= __ballot(lds_ld<T>(static_cast<uint32_t>(q[k]) * static_cast<uint32_t>(sizeof(T) / 4)) < T(0));
+    };
     auto unsatisfied = [&]() -> int32_t {
-        bool odd = false;
-        for (int g = wave; g < c.row_groups && !odd; g += nwaves) {
+        uint64_t par = 0;
+#pragma unroll
+        for (int i = 0; i < kFirstQuads; ++i)
+            if (4 * i < first_slots)
+                parity_of(first_quads[i], par);
+        bool odd = some_odd(par);
+        for (int g = wave + nwaves; g < c.row_groups && !odd; g += nwaves) {
             const int32_t w = c.row_grp[2 * g], first = c.row_grp[2 * g + 1];
             const Table<LT> tab = row_tab + first * 64;
-            uint64_t par = 0;
+            par = 0;
             for (int i = 0; i < quads(w >> 16); ++i) {
-                Addresses<T, 4> ci;
-                ci.load(tab + i * 64, 64);
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    par ^= __ballot(lds_ld<T>(ci[k]) < T(0));
+                const Quad q = tab[i * 64];
+                parity_of(q, par);
             }
             odd = some_odd(par);
         }
         return vote.any(odd);
     };
 
-    const bool es = (job.flags & LDPC_EARLY_STOP) != 0;
     const bool ms = INST == kAnyJob && (job.flags & LDPC_MIN_SUM) != 0;
     const T scale = static_cast<T>(job.ms_scale), offset = static_cast<T>(job.ms_offset * A::kIn);
     if (es && !unsatisfied())
