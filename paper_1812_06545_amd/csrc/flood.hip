@@ -410,8 +410,10 @@ ldpc_status decode_impl(const ldpc_code_s *c, int32_t frames, int32_t max_iter, 
                                    R, L, done, unsat_t, scale, offset};
             launch_ms<A>(c->max_row_deg, false, first, es, rgrid, s, ma);
         } else {
-            const CheckArgs<A> ca{c->row_ptr, c->col_idx, c->m, c->n, c->E, rgroups, nchunk, R, L, done, unsat_t};
-            launch_check<A>(c, first, es, rgrid, s, ca);
+            const int32_t steps = rgrid.x >= 6000 ? 2 : 1, takings = (rgroups + steps - 1) / steps;
+            const CheckArgs<A> ca{c->row_ptr, c->col_idx, c->m, c->n, c->E, takings, steps, nchunk,
+                                  R, L, done, unsat_t};
+            launch_check<A>(c, first, es, dim3(static_cast<unsigned>(takings) * nchunk), s, ca);
         }
         ProfScope ps(LDPC_KERNEL_VARIABLE, s);
         if (es)
