@@ -71,8 +71,17 @@ __global__ __launch_bounds__(256) void k_few_ingest(const typename A::T *__restr
     Lch[i] = v * T(A::kIn);
 }
 
-// L of a column: the channel value and its messages, all loads of eight edges
-// issued before their ordered sum.
+// Byte offset of frame f of item i in an array [items][W]: 24-bit factors and a
+// 32-bit product (few_frames_path bounds them).
+template <class T>
+__device__ __forceinline__ uint32_t frame_offset(uint32_t i, uint32_t W, uint32_t f)
+{
+    return (__umul24(i, W) + f) * static_cast<uint32_t>(sizeof(T));
+}
+
+// L of a column: the channel value and its messages in ascending row order, the
+// loads of eight edges issued before their sum.  Past the column's end the last
+// edge is read again and not added.
 template <class T>
 __device__ __forceinline__ T few_column(T acc, const int32_t *__restrict__ edges, int32_t dv, const T *__restrict__ R,
                                         int32_t W, int32_t f)
@@ -81,13 +90,13 @@ __device__ __forceinline__ T few_column(T acc, const int32_t *__restrict__ edges
     for (int32_t j0 = 0; j0 < dv; j0 += kStep) {
         T v[kStep];
 #pragma unroll
-        for (int j = 0; j < kStep; ++j)
-            if (j0 + j < dv)
-                v[j] = R[static_cast<int64_t>(edges[j0 + j]) * W + f];
+        for (int j = 0; j < kStep; ++j) {
+            const uint32_t e = static_cast<uint32_t>(edges[min(j0 + j, dv - 1)]);
+            v[j] = flood::ld_lane(R, frame_offset<T>(e, static_cast<uint32_t>(W), static_cast<uint32_t>(f)));
+        }
 #pragma unroll
         for (int j = 0; j < kStep; ++j)
-            if (j0 + j < dv)
-                acc += v[j];
+            acc = j0 + j < dv ? acc + v[j] : acc;
     }
     return acc;
 }
@@ -106,7 +115,7 @@ __global__ __launch_bounds__(256) void k_few(FewArgs<A> a)
     using T = typename A::T;
     constexpr int FW = few_width(KL);
     static_assert(FW * KL == 64, "a wavefront is KL edges of FW frames");
-    __shared__ T s_t[4][64], s_u[4][64];  // sum-product: an edge's t and u; min-sum: its |q| (in s_t)
+    __shared__ T s_t[4][64], s_u[4][64];  // sum-product: an edge's t and u, by slot; min-sum: its |q| (in s_t)
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int lane = static_cast<int>(threadIdx.x & 63), k = lane / FW;
     const int64_t item = static_cast<int64_t>(blockIdx.x) * 4 + wave;
@@ -128,11 +137,11 @@ __global__ __launch_bounds__(256) void k_few(FewArgs<A> a)
     T L = T(0), q = T(0);
     if (real) {
         const int32_t c = a.col_idx[e0 + k];
-        L = a.Lch[static_cast<int64_t>(c) * a.W + f];
+        L = flood::ld_lane(a.Lch, frame_offset<T>(static_cast<uint32_t>(c), a.W, f));
         if constexpr (FIRST) {
             q = L;
         } else {
-            const T own = a.Rold[static_cast<int64_t>(e0 + k) * a.W + f];
+            const T own = flood::ld_lane(a.Rold, frame_offset<T>(static_cast<uint32_t>(e0 + k), a.W, f));
             const int32_t b = a.col_ptr[c];
             L = few_column(L, a.col_edge + b, a.col_ptr[c + 1] - b, a.Rold, a.W, f);
             q = L - own;
@@ -163,30 +172,41 @@ __global__ __launch_bounds__(256) void k_few(FewArgs<A> a)
         const typename A::Term own = A::term(q);
         const uint64_t neg_all = own.neg & __ballot(real);
         const uint64_t negs = neg_all >> (lane % FW) & kFrameLanes;
-        s_t[wave][lane] = own.t;
-        s_u[wave][lane] = own.u;
+        // The halves lie in slots 0 .. KH - 1 and KH .. 2 KH - 1, each from its
+        // first edge on; the lanes past the row's end fill the other slots with
+        // identities (t = 1, u = 0), which change no bit of a combination, so
+        // that every lane runs the same straight code over its own half and the
+        // other.
+        constexpr int KH = KL / 2;
+        const int h = (d + 1) / 2, spare = k - d;
+        const int own_lo = k < h ? 0 : KH, at = k < h ? k : k - h;  // this edge's half, its place there
+        const int slot = real ? own_lo + at : spare < KH - h ? h + spare : d - h + KH + spare - (KH - h);
+        s_t[wave][slot * FW + lane % FW] = real ? own.t : T(1);
+        s_u[wave][slot * FW + lane % FW] = real ? own.u : T(0);
         wave_exchange();
-        auto grow = [&](typename A::Acc x, int j) {
-            typename A::Term e;
-            e.t = s_t[wave][j * FW + lane % FW];
-            e.u = s_u[wave][j * FW + lane % FW];
-            return A::add(x, e);
+        auto term_at = [&](int j, bool use) {
+            typename A::Term x;
+            const T t = s_t[wave][j * FW + lane % FW], u = s_u[wave][j * FW + lane % FW];
+            x.t = use ? t : T(1);
+            x.u = use ? u : T(0);
+            return x;
         };
-        const int h = (d + 1) / 2;
-        const int lo = k < h ? 0 : h, hi = k < h ? h : d;
         typename A::Acc p = A::identity(), other = A::identity();
-        for (int j = lo; j < k && j < d; ++j)
-            p = grow(p, j);
-        for (int j = k < h ? h : 0; j < (k < h ? d : h); ++j)
-            other = grow(other, j);
+#pragma unroll
+        for (int j = 0; j < KH - 1; ++j)
+            p = A::add(p, term_at(own_lo + j, j < at));
+#pragma unroll
+        for (int j = 0; j < KH; ++j)
+            other = A::add(other, term_at(KH - own_lo + j, true));
         typename A::Acc s = A::seed(other);
-        for (int j = hi - 1; j > k; --j)
-            s = grow(s, j);
+#pragma unroll
+        for (int j = KH - 1; j > 0; --j)
+            s = A::add(s, term_at(own_lo + j, j > at));
         const T mag = A::message(A::merge(p, s));
         r = ((__popcll(negs) & 1) != 0) != ((neg_all >> lane & 1) != 0) ? -mag : mag;
     }
     if (real && !stopped)
-        a.Rnew[static_cast<int64_t>(e0 + k) * a.W + f] = r;
+        flood::st_lane(a.Rnew, frame_offset<T>(static_cast<uint32_t>(e0 + k), a.W, f), r);
 }
 
 // Bits, iteration counts and posteriors: a frame's posteriors are those of the
@@ -272,18 +292,20 @@ ldpc_status run_few(const ldpc_code_s *c, int32_t frames, int32_t max_iter, bool
 // The streaming kernels cost the same from 1 to 64 frames; a launch here costs
 // in proportion to its wavefronts, m x (frame groups), beyond its latency.
 // Measured on MI355X, 20 iterations, us per call, streaming kernels and 1, 2,
-// 3, 4 groups: n = 16200 of degree 7 FP32 320 and 188, 289, 407, 505, FP64 599
-// and 240, 369, 530, 654; n = 64800 FP32 905 and 550, 977, 1473, FP64 1809 and
-// 717, 1220, 1855; n = 12007 of degree 16 FP32 318 and 164, 249, FP64 735 and
-// 214, 315, .., 460.  The bound on the reads keeps out codes whose dense columns
-// would be summed by very many rows (at its edge: a column of degree 2503, 19.4
-// and 6.7 to 13 ms).
+// 3, 4 groups: n = 16200 of degree 7 FP32 335 and 161, 223, 307, -, FP64 600
+// and 207, 300, 420, 512; n = 64800 FP32 905 and 414, 688, FP64 1840 and 550,
+// 928, 1396; n = 12007 of degree 16 FP32 350 and 147, 213, -, 338 (four groups:
+// left to the streaming kernels), FP64 730 and 199, 286, -, 450.  The bound on
+// the reads keeps out codes whose dense columns would be summed by very many
+// rows (near it: a column of degree 2503, 19.3 and 3.3 to 17.5 ms).
 bool few_frames_path(const ldpc_code_s *c, bool f64, int32_t frames)
 {
     if (frames > kFewFrames || c->max_row_deg > 32)
         return false;
     const int32_t width = few_width(c->max_row_deg), groups = (frames + width - 1) / width;
-    return groups <= (c->m <= 20000 ? 2 : 1) + (f64 ? 1 : 0) && c->column_reads * groups * width <= 1 << 26;
+    if (std::max<int64_t>(c->E, c->n) * groups * width >= 1 << 24)  // 24-bit factors, 32-bit byte offsets
+        return false;
+    return groups <= (c->m <= 20000 ? 3 : 2) + (f64 ? 1 : 0) && c->column_reads * groups * width <= 1 << 26;
 }
 
 template <class A>
