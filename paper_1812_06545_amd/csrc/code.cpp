@@ -476,7 +476,6 @@ try {
     }
     c->is_qc = true;
     c->mb = mb;
-    c->nb = nb;
     c->Z = Z;
     c->nblocks = nblocks;
     c->qc_words = (mb + 1) + 3 * nblocks + (nb + 1);

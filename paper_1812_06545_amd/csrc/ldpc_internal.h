@@ -105,8 +105,7 @@ struct ldpc_code_s {
     const int32_t *col_edge = nullptr;  // E
     // circulant-block structure (is_qc)
     bool is_qc = false;
-    int32_t mb = 0, nb = 0, Z = 0, nblocks = 0;
-    int32_t max_brow_deg = 0, max_bcol_deg = 0;
+    int32_t mb = 0, Z = 0, nblocks = 0;
     int32_t qc_words = 0;  // words of a table of the block structure: part of the frame-resident kernel's fit rule
     // Address tables of the frame-resident kernel (codes that can fit it).
     ldpc::FusedTables fused;
@@ -173,12 +172,12 @@ size_t fused_group_bytes();
 // ldpc_decode's frames as one frame-resident launch, if the code fits that
 // kernel, which is the faster route at every size measured (MI355X, FP32, 10
 // iterations, us per call, frames 1 / 256 / 1024, streaming and frame-resident:
-// qc n = 648 88 / 119 / 186 and 34 / 38 / 100; qc n = 3840, one frame to a CU,
-// 125 / 273 / 761 and 120 / 134 / 507; n = 1999 of degrees 2 to 29 107 / 200 /
-// 487 and 77 / 86 / 260; layered qc n = 1944 446 / 533 / 734 and 172 / 182 /
-// 457; FP64 n = 504 131 / 156 / 304 and 27 / 31 / 99): true, with the call's status in *rc (nothing is left to do), or
-// false, and the streaming path takes the call.  ws: at least 4 bytes of
-// device memory of the call's own.
+// qc n = 648 88 / 119 / 186 and 31 / 35 / 96; qc n = 3840, one frame to a CU,
+// 125 / 273 / 761 and 111 / 131 / 505; n = 1999 of degrees 2 to 29 107 / 200 /
+// 487 and 58 / 67 / 224; layered qc n = 1944 446 / 533 / 734 and 157 / 170 /
+// 468; FP64 n = 504 131 / 156 / 304 and 25 / 29 / 82): true, with the call's
+// status in *rc (nothing is left to do), or false, and the streaming path
+// takes the call.  ws: at least 4 bytes of device memory of the call's own.
 bool fused_decode(const ldpc_job &job, ldpc_dtype dt, void *ws, hipStream_t stream, ldpc_status *rc);
 
 // Streaming (per-iteration) path.

@@ -17,7 +17,7 @@
 
 namespace ldpc {
 
-// Running minimum state of one row (or half row).
+// Running minimum state of one row.
 template <class T>
 struct MinState {
     T m1, m2;       // smallest and second-smallest |q|
@@ -43,20 +43,6 @@ __device__ __forceinline__ void min_add(MinState<T> &s, T q, int32_t k)
     s.idx = lower ? k : s.idx;
     s.m1 = lower ? a : s.m1;
     s.neg ^= static_cast<uint32_t>(q < T(0));
-}
-
-// Merge of two halves' states (the partner's is `o`); the first half's
-// positions precede the second's, so ties keep the first half's position.
-template <class T>
-__device__ __forceinline__ void min_merge(MinState<T> &s, T o_m1, T o_m2, int32_t o_idx, uint32_t o_neg)
-{
-    const bool other_lower = o_m1 < s.m1;
-    const T hi = other_lower ? s.m1 : o_m1;
-    const T m2 = s.m2 < o_m2 ? s.m2 : o_m2;
-    s.m2 = hi < m2 ? hi : m2;
-    s.idx = other_lower ? o_idx : s.idx;
-    s.m1 = other_lower ? o_m1 : s.m1;
-    s.neg ^= o_neg;
 }
 
 // Outgoing message of edge k with incoming q_k.
