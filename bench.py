@@ -294,8 +294,7 @@ def _time_ms(fn, reps):
 
 
 def batch_path_run(h, llrs, bits, iters, post, F, n, T, steps):
-    """The same workload through ldpc_decode_batch (the fused frame-resident
-    persistent kernel), timed on its own after the headline region."""
+    """The same workload through ldpc_decode_batch, timed on its own after the headline region."""
     import torch
 
     import paper_1812_06545_amd as L
@@ -310,7 +309,7 @@ def batch_path_run(h, llrs, bits, iters, post, F, n, T, steps):
             raise RuntimeError("ldpc_decode_batch failed")
         k[0] += 1
     ms = _time_ms(step, steps)
-    return {"entry": "ldpc_decode_batch (fused frame-resident persistent kernel)", "ms_per_step": ms,
+    return {"entry": "ldpc_decode_batch (fused frame-resident kernel)", "ms_per_step": ms,
             "mbps": F * n / (ms * 1e-3) / 1e6, "step_floor": floor_frac(h.edges, n, 4, F * T, ms)}
 
 
@@ -318,11 +317,11 @@ def extra_workloads(only=None):
     """The other seeded workloads, each timed with HIP events on the device:
     - gallager504 (FP64, 1000 frames, 20 iterations, early stop): plain and batch;
     - qc_mix (12 codes, 16384 frames, 10 iterations, early stop): one batched
-      launch vs twelve plain per-code launches (identical outputs), the batch
+      call vs twelve ldpc_decode calls (identical outputs), the batch
       with the default launch shape, after ldpc_autotune_batch, and replayed
       from a HIP-graph plan;
-    - stair64800 (256 frames, 50 iterations, early stop): plain path and
-      ldpc_decode_batch (which takes the plain kernels for this code).
+    - stair64800 (256 frames, 50 iterations, early stop): ldpc_decode
+      and ldpc_decode_batch (both take the streaming kernels for this code).
     `only` names one of them to time alone.
     Each carries the whole step's algorithmic-floor fraction (floor_frac)
     over the iterations its frames actually ran."""
@@ -393,12 +392,12 @@ def extra_workloads(only=None):
 
 def layered_workloads(steps):
     """The layered schedule (LDPC_LAYERED), timed with HIP events:
-    - qc1944 at 2.0 dB, 4096 frames, 10 passes fixed, on the plain path (one
-      launch per layer; the layer kernel's achieved bandwidth: per edge and
-      frame a layer reads r and L and writes both, 16 bytes, 12 on the first
-      pass, which reads no r) and on the fused frame-resident kernel;
+    - qc1944 at 2.0 dB, 4096 frames, 10 passes fixed, through ldpc_decode and
+      ldpc_decode_batch (if ldpc_decode runs one kernel per layer, that
+      kernel's achieved bandwidth: per edge and frame a layer reads r and L
+      and writes both, 16 bytes, 12 on the first pass, which reads no r);
     - time to decode with early stop (max 20) against flooding on the same
-      inputs, both paths: qc1944 code at 3.5 dB and gallager504 (FP64) at 2.0 dB.
+      inputs, both entries: qc1944 code at 3.5 dB and gallager504 (FP64) at 2.0 dB.
     Fused-kernel timings here follow ldpc_autotune_batch for their shape."""
     import torch
 
@@ -461,11 +460,10 @@ def layered_workloads(steps):
 def minsum_workloads(steps):
     """The min-sum check rule (LDPC_MIN_SUM), HIP-event timed:
     - qc1944 2.0 dB, 4096 frames, 10 iterations, normalised min-sum (scale
-      0.75), plain flooding path: Mbit/s and the min-sum check kernel's
-      achieved bandwidth on the sum-product check kernel's algorithmic bytes
-      (no transcendentals: the kernel is a pure HBM stream); the fused path
-      and the layered schedule on the same input;
-    - early stop (max 20) at 3.5 dB against sum-product, plain flooding."""
+      0.75), flooding: Mbit/s and, if ldpc_decode runs the streaming
+      kernels, the check kernel's achieved bandwidth; ldpc_decode_batch and
+      the layered schedule on the same input;
+    - early stop (max 20) at 3.5 dB against sum-product, flooding."""
     import torch
 
     import paper_1812_06545_amd as L

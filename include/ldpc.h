@@ -125,8 +125,7 @@ ldpc_status ldpc_code_from_csr(int32_t m, int32_t n, const int32_t *row_ptr, con
  * (i, j) with shift s joins check row i*Z + r to variable column
  * j*Z + ((r + s) mod Z), r = 0 .. Z-1; so m = mb*Z, n = nb*Z.
  * Errors as ldpc_code_from_csr, plus EINVAL for shifts outside [-1, Z).
- * QC codes additionally get the circulant-block layout used by the fused
- * (frame-resident) kernels.
+ * Outputs are those of the expanded matrix given to ldpc_code_from_csr.
  */
 ldpc_status ldpc_code_from_qc(int32_t mb, int32_t nb, int32_t Z, const int32_t *shifts, ldpc_code *out);
 
@@ -492,7 +491,7 @@ typedef enum {
     LDPC_KERNEL_CHECK = 1,     /* check-node update: one iteration (flooding) or one layer (layered) */
     LDPC_KERNEL_VARIABLE = 2,  /* variable-node update + hard decision, one iteration */
     LDPC_KERNEL_OUTPUT = 3,    /* frame-interleaved -> caller layout */
-    LDPC_KERNEL_FUSED = 4,     /* persistent frame-resident decoder (all iterations) */
+    LDPC_KERNEL_FUSED = 4,     /* frame-resident decoder (all iterations) */
     LDPC_KERNEL_OTHER = 5,     /* small bookkeeping kernels */
     LDPC_KERNEL_KINDS = 6
 } ldpc_kernel_kind;
