@@ -726,17 +726,30 @@ __device__ __forceinline__ int32_t decode_frame_layered(const Code &c, const Job
         first = at[1];
     };
     auto layer_after = [&](int32_t l) { return l + 1 == nlayers ? 0 : l + 1; };
+    // A layer's groups go to the wavefronts from where the last layer's ended:
+    // six groups always on the first six of eight wavefronts would give two of
+    // the four SIMDs twice the work of the others, for both frames of a CU.
+    int mine = wave;
+    auto turn = [&](int32_t groups) {
+        if (LT)
+            return;  // a frame alone on its CU
+        mine -= groups;
+        while (mine < 0)
+            mine += nwaves;
+    };
     int32_t begin = 0, end = c.lay_ptr[1], w_ahead, first_ahead;
     int32_t end_ahead = c.lay_ptr[layer_after(0) + 1 + lane0];
-    group_words(wave, w_ahead, first_ahead);
+    group_words(mine, w_ahead, first_ahead);
     for (int32_t t = 1; t <= job.max_iter; ++t) {
         for (int32_t l = 0; l < nlayers; ++l) {
             const int32_t next = layer_after(l), next_begin = next == 0 ? 0 : end;
             const int32_t next_end = __builtin_amdgcn_readfirstlane(end_ahead);
             int32_t w = __builtin_amdgcn_readfirstlane(w_ahead), first = __builtin_amdgcn_readfirstlane(first_ahead);
-            group_words(next_begin + wave, w_ahead, first_ahead);
+            int g = begin + mine;
+            turn(end - begin);
+            group_words(next_begin + mine, w_ahead, first_ahead);
             end_ahead = c.lay_ptr[layer_after(next) + 1 + lane0];
-            for (int g = begin + wave; g < end;) {
+            while (g < end) {
                 const int rows = w & 0xff, d = w >> 8;  // first: the group's first quad
                 if ((lane & 15) < rows && d > 0)
                     layered_dispatch<A, 1, DB / 4>(
