@@ -87,6 +87,7 @@ struct Batch {
     int32_t nitems, frames_per_item;
     uint32_t flags_at;   // LDS address of the workgroup's flag words
     uint32_t tables_at;  // and of its code's tables (kernels that copy them)
+    int32_t layer_turn;  // by what the wavefronts' places in a layer change from each to the next
     int32_t begin[kMaxJobs];
     Code codes[kMaxCodes];
     Job jobs[kMaxJobs];
@@ -658,7 +659,7 @@ __device__ __forceinline__ int32_t decode_frame(const Code &c, const Job &job, i
 // path's, bit for bit.  Returns the passes run.
 template <class A, int DB, Instance INST, bool LT>
 __device__ __forceinline__ int32_t decode_frame_layered(const Code &c, const Job &job, int64_t f, uint32_t tables,
-                                                        Vote &vote)
+                                                        int32_t turn, Vote &vote)
 {
     using T = typename A::T;
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
@@ -726,17 +727,9 @@ __device__ __forceinline__ int32_t decode_frame_layered(const Code &c, const Job
         first = at[1];
     };
     auto layer_after = [&](int32_t l) { return l + 1 == nlayers ? 0 : l + 1; };
-    // A layer's groups go to the wavefronts from where the last layer's ended:
-    // six groups always on the first six of eight wavefronts would give two of
-    // the four SIMDs twice the work of the others, for both frames of a CU.
+    // This wavefront's first group of the layer; `turn` swaps pairs of
+    // wavefronts from layer to layer (layer_turn).
     int mine = wave;
-    auto turn = [&](int32_t groups) {
-        if (LT)
-            return;  // a frame alone on its CU
-        mine -= groups;
-        while (mine < 0)
-            mine += nwaves;
-    };
     int32_t begin = 0, end = c.lay_ptr[1], w_ahead, first_ahead;
     int32_t end_ahead = c.lay_ptr[layer_after(0) + 1 + lane0];
     group_words(mine, w_ahead, first_ahead);
@@ -746,7 +739,8 @@ __device__ __forceinline__ int32_t decode_frame_layered(const Code &c, const Job
             const int32_t next_end = __builtin_amdgcn_readfirstlane(end_ahead);
             int32_t w = __builtin_amdgcn_readfirstlane(w_ahead), first = __builtin_amdgcn_readfirstlane(first_ahead);
             int g = begin + mine;
-            turn(end - begin);
+            if (!LT)
+                mine ^= turn;
             group_words(next_begin + mine, w_ahead, first_ahead);
             end_ahead = c.lay_ptr[layer_after(next) + 1 + lane0];
             while (g < end) {
@@ -882,7 +876,7 @@ __global__ __launch_bounds__(kFusedMaxThreads<A>) __attribute__((amdgpu_waves_pe
                 __syncthreads();  // the last frame's posteriors have been read
             int32_t it;
             if (INST == kLayered || (INST == kAnyJob && (job.flags & LDPC_LAYERED)))
-                it = decode_frame_layered<A, DB, INST, LT>(c, job, f, b.tables_at, vote);
+                it = decode_frame_layered<A, DB, INST, LT>(c, job, f, b.tables_at, b.layer_turn, vote);
             else
                 it = decode_frame<A, DB, INST, LT>(c, job, f, b.tables_at, vote);
             if (f == f0)
@@ -1111,6 +1105,30 @@ ldpc_status workgroup_threads(K kern, const Batch &b, size_t tsize, size_t lds, 
 
 }  // namespace fused
 
+namespace fused {
+
+// By what a wavefront's place in a layer changes (^) from each layer to the next.
+// Five to seven groups on the first of eight wavefronts give some of the four
+// SIMDs twice the work of the others, in both frames of a CU that holds two;
+// swapping the first two wavefronts with the next two, and the last, evens that
+// out.  us per call of 6 passes, 4000 frames, fixed and swapping: qc n = 1944 at
+// rate 1/2 992 and 920, n = 2304 at rate 2/3 669 and 617.  With any other share
+// there is nothing to even out, and a changing first wavefront costs up to 10%
+// (fixed and changing: one frame of ten groups to a CU, qc n = 3840 at rate 3/4
+// 715 and 753; one of eight groups, qc n = 3072, 64 frames 69 and 76; 700 frames of
+// n = 648 at rate 1/2, two groups, 91 and 95).
+inline int32_t layer_turn(const Batch &b, int threads, int per_cu, int cus)
+{
+    int32_t rows = 0;
+    for (int32_t i = 0; i < b.njobs; ++i)
+        if (b.jobs[i].flags & LDPC_LAYERED)
+            rows = std::max(rows, b.codes[b.jobs[i].code].layer_rows);
+    const int32_t groups = (rows + 15) / 16;
+    return threads == 512 && per_cu == 2 && b.nitems > cus && groups > 4 && groups < 8 ? 2 : 0;
+}
+
+}  // namespace fused
+
 // Sets a launch's item counter to 0.
 void launch_zero_counter(uint32_t *counter, hipStream_t s, bool profile);
 
@@ -1140,6 +1158,7 @@ ldpc_status launch_fused_kernel(K kern, fused::Batch &batch, size_t lds_bytes, u
         fused::launch_shape(reinterpret_cast<const void *>(kern), lds_bytes, threads, per_cu, cus);
     if (shape_rc != LDPC_OK)
         return shape_rc;
+    batch.layer_turn = fused::layer_turn(batch, threads, per_cu, cus);
     const int32_t resident = per_cu * cus;
     if (batch.nitems <= resident)
         counter = nullptr;  // one workgroup per item
