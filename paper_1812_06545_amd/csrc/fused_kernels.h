@@ -671,13 +671,16 @@ __device__ __forceinline__ int32_t decode_frame_layered(const Code &c, const Job
 
     // Whether some row is unsatisfied by the decision [L < 0], from the
     // flooding table.  A wavefront stops at its first group of 32 rows holding
-    // one (the answer is then known; in most passes that is the first group,
-    // whose addresses therefore stay in registers).
+    // one (the answer is then known; in most passes that is the first group).
+    // Alone on its CU (LT), a wavefront keeps that group's addresses in
+    // registers (24 frames of qc n = 1296, rate 2/3: 84.5 us per call without and
+    // 82.3 with); where frames share a CU, holding 8 to 16 registers through
+    // every layer costs resident wavefronts (kFusedWavesPerEU).
     const bool es = (job.flags & LDPC_EARLY_STOP) != 0;
-    constexpr int kFirstQuads = quads(DB / 2);
-    Quad first_quads[kFirstQuads];
+    constexpr int kFirstQuads = LT ? quads(DB / 2) : 0;
+    Quad first_quads[kFirstQuads + 1];
     int first_slots = 0;
-    if (es && wave < c.row_groups) {
+    if (LT && es && wave < c.row_groups) {
         first_slots = c.row_grp[2 * wave] >> 16;
         const Table<LT> tab = row_tab + c.row_grp[2 * wave + 1] * 64;
 #pragma unroll
@@ -697,7 +700,7 @@ __device__ __forceinline__ int32_t decode_frame_layered(const Code &c, const Job
             if (4 * i < first_slots)
                 parity_of(first_quads[i], par);
         bool odd = some_odd(par);
-        for (int g = wave + nwaves; g < c.row_groups && !odd; g += nwaves) {
+        for (int g = LT ? wave + nwaves : wave; g < c.row_groups && !odd; g += nwaves) {
             const int32_t w = c.row_grp[2 * g], first = c.row_grp[2 * g + 1];
             const Table<LT> tab = row_tab + first * 64;
             par = 0;
@@ -836,9 +839,18 @@ __device__ __forceinline__ int32_t next_item(const uint32_t *counter, uint32_t d
 
 // Batch kernel.  FP32 bodies are held to 128 VGPRs, so that a CU holds 16
 // wavefronts (4 per SIMD): two 512-thread workgroups for n = 1944, whose LDS
-// admits no third, or one of 1024.  FP64 bodies get 256 VGPRs.
-template <class A>
-constexpr int kFusedWavesPerEU = std::is_same<A, ArithF32>::value ? 4 : 2;
+// admits no third, or one of 1024.  FP64 bodies get 256 VGPRs.  The layered
+// instance is bound by the latency of a layer (gather, exchange, scatter,
+// barrier), which a CU's other frames hide, and its frames are small: where
+// frames share a CU it is held to the registers of 6 wavefronts per SIMD (5 for
+// rows longer than 24; both spill one pair, once per frame).  us per call of 6
+// passes, 4000 frames of qc n = 1584 at rates 2/3, 3/4 and 5/6 with 4 and 6
+// wavefronts per SIMD (and 8, with 61 registers and the terms parked in LDS): 588
+// and 455 (511), 440 and 349 (388), 303 and 241 (275); n = 648 at rate 1/2 358 and
+// 301 (545).
+template <class A, int DB, Instance INST, bool LT>
+constexpr int kFusedWavesPerEU =
+    !std::is_same<A, ArithF32>::value ? 2 : INST == kLayered && !LT ? (DB <= 24 ? 6 : 5) : 4;
 template <class A>
 constexpr int kFusedMaxThreads = std::is_same<A, ArithF32>::value ? kMaxThreads : kBaseThreads;
 
@@ -857,7 +869,7 @@ __device__ __forceinline__ void copy_tables(const Batch &b, const Code &c, const
 }
 
 template <class A, int DB, Instance INST = kAnyJob, bool LT = false>
-__global__ __launch_bounds__(kFusedMaxThreads<A>) __attribute__((amdgpu_waves_per_eu(kFusedWavesPerEU<A>))) void k_fused(const Batch b, uint32_t *counter)
+__global__ __launch_bounds__(kFusedMaxThreads<A>) __attribute__((amdgpu_waves_per_eu(kFusedWavesPerEU<A, DB, INST, LT>))) void k_fused(const Batch b, uint32_t *counter)
 {
     Lds<int32_t> *flags = lds_at<int32_t>(b.flags_at);
     if (threadIdx.x < kFlagWords)
