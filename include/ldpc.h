@@ -157,8 +157,9 @@ ldpc_status ldpc_workspace_bytes(ldpc_code code, ldpc_dtype dtype, int32_t frame
 /*
  * Decode `frames` frames of one code.  A code that fits the frame-resident
  * kernel (ldpc_batch_fits_fused) is decoded by one launch of it, as a job of
- * ldpc_decode_batch.  Otherwise the call runs
- * per-iteration kernel launches (the plain path, messages streamed through
+ * ldpc_decode_batch, unless the frames are so many and the code so short (or a
+ * frame's work so serial) that the other path is estimated to be faster.
+ * Otherwise the call runs per-iteration kernel launches (the plain path, messages streamed through
  * device memory; the same outputs bit for bit): flooding runs one
  * check-node and one variable-node kernel per iteration (Section II,
  * Algorithm 1: Loop 2, then Loops 3 and 4; the launch boundary is the

@@ -416,12 +416,73 @@ ldpc_status launch_group(const ldpc_job *jobs, const Group &g, char *ws, int thr
     }
 }
 
+// Whether ldpc_decode runs a code that fits the frame-resident kernel faster
+// there than with the streaming kernels.  Up to the frames that the device holds
+// at once it does.  Beyond, a workgroup per frame loses on very short codes:
+// frames are drawn from one counter, 11.5 ns each whatever their size, and a
+// frame of few rows leaves most of its workgroup idle, where the streaming
+// kernels pack 64 frames to a wavefront.  It also loses where a frame's time is
+// one long serial chain (a column of very high degree, many small layers), which
+// then repeats for every pass of frames over the device.  Both times are
+// estimated in us; the constants are a fit to 2184 calls on MI355X (38 codes of 12
+// to 16552 edges, 2048 to 131072 frames, 0 to 20 iterations, either schedule, rule
+// and type), of which the choice leaves 24 more than 5% slower than the streaming
+// kernels, the worst by 29%.  us per call, streaming and frame-resident kernels:
+// Hamming (7,4), 10 iterations, 4096 frames 50 and 53, 131072 frames 187 and 1938;
+// qc n = 96 of 808 edges, 32768 frames, 5 iterations 301 and 400, layered 515 and 1141;
+// n = 384 of degree 6, 131072 frames, 1 iteration 613 and 1504, 20 iterations 8302 and
+// 4367; n = 1536, 32768 frames, 5 iterations 2287 and 1124; a column of degree 3000,
+// 8192 frames, 5 iterations 8113 and 17362.
+bool frame_resident_faster(const ldpc_job &j, ldpc_dtype dt, size_t limit)
+{
+    const ldpc_code_s *c = j.code;
+    const bool layered = (j.flags & LDPC_LAYERED) != 0, ms = (j.flags & LDPC_MIN_SUM) != 0, f64 = dt == LDPC_F64;
+    const size_t tsize = f64 ? sizeof(double) : sizeof(float);
+    const int32_t groups = (c->m + 31) / 32, layers = static_cast<int32_t>(c->layer_dmax.size());
+    const int32_t layer_rows = (c->m + layers - 1) / layers;  // of a mean layer
+    // frames the device holds: wavefronts of a frame, wavefronts and LDS of a CU (workgroup_threads)
+    const int waves = layered ? (layer_rows <= 16 ? 2 : layer_rows <= 32 ? 3 : 8) : groups <= 12 ? 4 : 8;
+    const int cu_waves = f64 ? 8 : ms != layered ? 24 : 16;
+    const size_t slots = fused::lds_bytes(c->n, c->fused.slot_words, tsize);
+    const size_t lds = layered || slots > limit ? fused::lds_bytes(c->n, c->E, tsize) : slots;
+    const double held = 256.0 * std::max<double>(1, std::min<double>(cu_waves / waves, static_cast<double>(limit / lds)));
+    if (j.frames <= held)
+        return true;
+
+    const double frames = j.frames, ts = static_cast<double>(tsize), E = static_cast<double>(c->E), n = c->n;
+    // early stop: half the iterations, but every launch
+    const double iters = (j.flags & LDPC_EARLY_STOP) ? 0.5 * j.max_iter : j.max_iter;
+    // Streaming: launches of 3.1 us; 5.4 TB/s (FP64 sum-product: 5 ps of arithmetic per
+    // edge); 6.5 values per variable in and out; a column's chain of loads.
+    double launches = 2.0 + 2.0 * j.max_iter;
+    if (layered)
+        launches = 2.0 + static_cast<double>(j.max_iter) * (layers + ((j.flags & LDPC_EARLY_STOP) ? 2 : 0));
+    const double bytes = ts * (layered ? 4.0 * E : 3.0 * E + 2.0 * n);
+    const double streaming = 3.1 * launches +
+                             frames * (iters * (f64 && !ms ? 5e-6 * E : bytes / 5.4e6) + 6.5 * ts * n / 5.4e6) +
+                             (layered ? 0.0 : 0.17 * iters * c->max_col_deg);
+    // Frame-resident: the draws, or a frame's iteration: its latency over the frames
+    // held, or the issue time of its groups.
+    const double half = (c->max_row_deg + 1) / 2, quarter = ((c->max_row_deg + 1) / 2 + 1) / 2;
+    double latency, issue;
+    if (layered) {
+        latency = layers * (0.30 + 0.14 * quarter);
+        issue = 9.4e-5 * quarter * layers * ((layer_rows + 15) / 16);
+    } else {
+        latency = 0.71 + 0.22 * half + 0.015 * c->max_col_deg;
+        issue = 8.8e-5 * groups * half;
+    }
+    const double resident = 7.0 + frames * std::max(0.0115, iters * std::max(latency / held, issue));
+    return 1.1 * resident <= streaming;
+}
+
 }  // namespace
 
 bool fused_decode(const ldpc_job &job, ldpc_dtype dt, void *ws, hipStream_t stream, ldpc_status *rc)
 {
-    const FusedFit fit = fused_fit(job.code, dt, lds_limit());
-    if (!fit.ok)
+    const size_t limit = lds_limit();
+    const FusedFit fit = fused_fit(job.code, dt, limit);
+    if (!fit.ok || !frame_resident_faster(job, dt, limit))
         return false;
     const LaunchCfg cfg = cfg_for(&job, 1, dt);
     Group g;

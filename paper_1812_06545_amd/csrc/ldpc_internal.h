@@ -169,15 +169,15 @@ ldpc_status launch_link_copy16(void *dst, const void *src, size_t bytes, int32_t
 // and work counter).  A batch of J jobs needs at most J such launches.
 size_t fused_group_bytes();
 
-// ldpc_decode's frames as one frame-resident launch, if the code fits that
-// kernel, which is the faster route at every size measured (MI355X, FP32, 10
-// iterations, us per call, frames 1 / 256 / 1024, streaming and frame-resident:
+// ldpc_decode's frames as one frame-resident launch, if the code fits that kernel
+// and it is the faster route (frame_resident_faster): true, with the call's status
+// in *rc (nothing is left to do), or false, and the streaming path takes the
+// call.  ws: at least 4 bytes of device memory of the call's own.  (MI355X, FP32,
+// 10 iterations, us per call, frames 1 / 256 / 1024, streaming and frame-resident:
 // qc n = 648 88 / 119 / 186 and 31 / 35 / 96; qc n = 3840, one frame to a CU,
 // 125 / 273 / 761 and 111 / 131 / 505; n = 1999 of degrees 2 to 29 107 / 200 /
 // 487 and 58 / 67 / 224; layered qc n = 1944 446 / 533 / 734 and 157 / 170 /
-// 468; FP64 n = 504 131 / 156 / 304 and 25 / 29 / 82): true, with the call's
-// status in *rc (nothing is left to do), or false, and the streaming path
-// takes the call.  ws: at least 4 bytes of device memory of the call's own.
+// 468; FP64 n = 504 131 / 156 / 304 and 25 / 29 / 82.)
 bool fused_decode(const ldpc_job &job, ldpc_dtype dt, void *ws, hipStream_t stream, ldpc_status *rc);
 
 // Streaming (per-iteration) path.

@@ -1,0 +1,75 @@
+"""Which kernels ldpc_decode runs for codes that fit the frame-resident kernel.
+
+Frames beyond what the device holds at once go to the streaming kernels where
+those are the faster: very short codes, few iterations, layers of a few rows,
+columns of very high degree.  Each call's outputs must equal the
+frame-resident kernel's, which ldpc_decode_batch runs for them, bit for bit
+(no tolerance: the same operations in the same order).  The calls on each side
+lie well off the line (factors of 1.4 to 15 between the two routes' times).
+"""
+import numpy as np
+import pytest
+
+from workloads import codes
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def L():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1812_06545_amd as lib
+    return lib
+
+
+def regular(n):
+    return codes.random_rows(n // 2, n, 6, 6, 1)
+
+
+# code, frames, iterations, options, streaming?
+CALLS = {
+    "hamming": (codes.hamming74, 65536, 10, dict(early_stop=True), True),
+    "hamming_few": (codes.hamming74, 64, 10, dict(early_stop=True), False),
+    "tiny": (lambda: regular(24), 32768, 5, {}, True),
+    "tiny_resident": (lambda: regular(24), 700, 5, {}, False),
+    "one_iteration": (lambda: regular(192), 32768, 1, {}, True),
+    "twenty_iterations": (lambda: regular(384), 32768, 20, {}, False),
+    "no_iteration": (lambda: regular(384), 32768, 0, {}, True),
+    "small_layers": (lambda: codes.qc_code(12, 24, 4, 3), 32768, 5, dict(layered=True), True),
+    "large_layers": (lambda: codes.qc_code(12, 24, 27, 3), 4096, 10, dict(layered=True, early_stop=True), False),
+    "minsum_tiny": (lambda: regular(48), 32768, 5, dict(rule="minsum", ms_scale=0.75), True),
+    "minsum": (lambda: codes.qc_code(12, 24, 81, 3), 1999, 10, dict(rule="minsum", ms_scale=0.75), False),
+    "dense_column": (lambda: codes.random_rows(3000, 4000, 3, 8, 5, dense_col=True), 4096, 3, {}, True),
+    "dense_column_few": (lambda: codes.random_rows(3000, 4000, 3, 8, 5, dense_col=True), 64, 3, {}, False),
+    "throughput": (lambda: codes.qc_code(12, 24, 81, 3), 4096, 10, {}, False),
+}
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("name", list(CALLS))
+def test_route(L, name, dtype):
+    import torch
+    make, frames, iters, options, streaming = CALLS[name]
+    if dtype == "f64" and (name.startswith("dense") or "iteration" in name):
+        pytest.skip("the line lies elsewhere in FP64, or the code does not fit")
+    code = make()
+    h = L.Code.from_workload(code)
+    td = torch.float32 if dtype == "f32" else torch.float64
+    assert L.ldpc_batch_fits_fused(h, td)[0]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(51)
+    x = (2.2 + 1.8 * torch.randn((frames, code.n), generator=gen, device="cuda", dtype=torch.float64)).to(td)
+    print(f"[gpu] route {name} {dtype}", flush=True)
+    L.ldpc_profile_enable(True)
+    try:
+        L.ldpc_profile_collect()
+        bits, its, post = L.decode(h, x, iters, **options)
+        launched = {k: count for k, (_, count) in L.ldpc_profile_collect().items()}
+    finally:
+        L.ldpc_profile_enable(False)
+    assert (launched["fused"] == 0) == streaming, launched
+    job = L.Job(h, x, iters, **options)
+    L.decode_batch([job])
+    assert torch.equal(bits, job.bits) and torch.equal(its, job.iters) and torch.equal(post, job.posterior)
