@@ -348,7 +348,7 @@ __device__ __forceinline__ void variable_item(int group, int chunk, const int32_
 // store nothing, and one that reads the 0 skips it: the same result.
 // Measured on MI355X (stair64800, 256 frames): a launch over four running
 // chunks took 69-70 us instead of 91, one after every frame stopped 13 us
-// instead of 20.  Without early stop the strided form was 3% slower than one
+// instead of 20 (4.5 with the test at its start).  Without early stop the strided form was 3% slower than one
 // block per item, and a strided check kernel 13% slower per launch (a
 // block's items are fixed, so the CUs of an XCD cannot even out its row
 // groups' run times as the dispatcher does).
@@ -364,14 +364,19 @@ __global__ __launch_bounds__(256) void k_variable(const int32_t *__restrict__ co
     if constexpr (ES) {
         const int items = groups * nchunk;
         int tested = -1, running = 0;
-        // after the last frame has stopped, without a pass over the items
-        // (four chunks of n = 64800: 4.5 us instead of 12.8)
-        const int lane = static_cast<int>(threadIdx.x & 63);
-        bool some = false;
-        for (int c = 0; c < nchunk && !some; c += 64)
-            some = __any(c + lane < nchunk && chunk_active(done, nchunk, c + lane) != 0);
-        if (!some)
-            return;
+        // After the last frame has stopped, a block with items of several chunks
+        // ends without a pass over them (four chunks of n = 64800: 4.5 us instead
+        // of 12.8).  Where the loop makes one chunk test anyway, this one would
+        // only add its load to every launch (one chunk of n = 12007, 8
+        // iterations: 151 us a call instead of 143).
+        if (nchunk > 1 && items > static_cast<int>(gridDim.x)) {
+            const int lane = static_cast<int>(threadIdx.x & 63);
+            bool some = false;
+            for (int c = 0; c < nchunk && !some; c += 64)
+                some = __any(c + lane < nchunk && chunk_active(done, nchunk, c + lane) != 0);
+            if (!some)
+                return;
+        }
         for (int b = static_cast<int>(blockIdx.x); b < items; b += static_cast<int>(gridDim.x)) {
             map_block(b, groups, nchunk, group, chunk);
             if (chunk != tested) {
