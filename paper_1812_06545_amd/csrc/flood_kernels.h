@@ -198,8 +198,11 @@ __device__ __forceinline__ void check_row_exact(int d, const int32_t *__restrict
 // 64800, 256 frames 1777, 1681, 1694, 1731; n = 16200, 512 frames 852, 804, 816,
 // 828; n = 12007 of degree 16, 64 frames, 1501 groups 196, 190, 213, 259), and
 // where a stopped chunk's blocks cost as much as a quarter of a running one's.
+// Rows up to 16: held to the registers of 6 wavefronts per SIMD, which the bodies
+// need (66 to 71); left alone the compiler takes 99 with early stop (a chunk of n =
+// 12007, 8 iterations, 149 us a call; held, 142).
 template <class A, int DB, bool EXACT, bool FIRST, bool ES>
-__global__ __launch_bounds__(256) void k_check(const int32_t *__restrict__ row_ptr,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EXACT && DB == 16 ? 6 : 1))) void k_check(const int32_t *__restrict__ row_ptr,
                                                const int32_t *__restrict__ col_idx, int32_t m, int32_t n, int64_t E,
                                                int32_t groups, int32_t steps, int32_t nchunk,
                                                typename A::T *__restrict__ R, const typename A::T *__restrict__ L,
@@ -348,10 +351,10 @@ __device__ __forceinline__ void variable_item(int group, int chunk, const int32_
 // store nothing, and one that reads the 0 skips it: the same result.
 // Measured on MI355X (stair64800, 256 frames): a launch over four running
 // chunks took 69-70 us instead of 91, one after every frame stopped 13 us
-// instead of 20 (4.5 with the test at its start).  Without early stop the strided form was 3% slower than one
-// block per item, and a strided check kernel 13% slower per launch (a
-// block's items are fixed, so the CUs of an XCD cannot even out its row
-// groups' run times as the dispatcher does).
+// instead of 20 (4.5 with the test at its start).  Without early stop the
+// strided form was 3% slower than one block per item, and a strided check
+// kernel 13% slower per launch (a block's items are fixed, so the CUs of an
+// XCD cannot even out its row groups' run times as the dispatcher does).
 template <class A, bool ES>
 __global__ __launch_bounds__(256) void k_variable(const int32_t *__restrict__ col_ptr,
                                                   const int32_t *__restrict__ col_edge, int32_t n, int64_t E,

@@ -58,3 +58,9 @@ def test_layered_frames_that_share_a_cu(kernels, degree, waves):
     pair of registers may be, once per frame)."""
     (got,) = [v for k, v in kernels.items() if f"k_fusedINS_8ArithF32ELi{degree}ELNS0_8InstanceE2ELb0E" in k]
     assert got[0] <= 512 // waves // 8 * 8 and got[1] <= 2, got
+
+
+def test_check_kernel_of_rows_up_to_16(kernels):
+    """Its registers allow 6 wavefronts per SIMD, with and without early stop."""
+    got = [v for k, v in kernels.items() if "flood7k_checkINS_8ArithF32ELi16E" in k]
+    assert len(got) == 4 and all(v <= 80 and spilled == 0 for v, spilled in got), got
