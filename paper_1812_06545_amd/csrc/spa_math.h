@@ -49,6 +49,9 @@ namespace ldpc {
 // (As a plain condition the compiler recomputes it in vector registers.)
 using Lanes = uint64_t;
 __device__ __forceinline__ bool lane_of(Lanes m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+// The lanes whose value has its sign bit set.
+__device__ __forceinline__ Lanes sign_lanes(float v) { return __ballot(__float_as_int(v) < 0); }
+__device__ __forceinline__ Lanes sign_lanes(double v) { return __ballot(__double_as_longlong(v) < 0); }
 
 struct ArithF32 {
     using T = float;
@@ -97,7 +100,7 @@ struct ArithF32 {
         Term k;
         k.t = dh * ri2;
         k.u = e * ri2;
-        k.neg = __ballot(__float_as_int(q) < 0);
+        k.neg = sign_lanes(q);
         return k;
     }
     __device__ static __forceinline__ Acc add(Acc a, const Term &k)
@@ -224,7 +227,7 @@ struct ArithF64 {
         Term out;
         out.t = d * ri;
         out.u = (e + e) * ri;
-        out.neg = __ballot(__double_as_longlong(q) < 0);
+        out.neg = sign_lanes(q);
         return out;
     }
     __device__ static __forceinline__ Acc add(Acc a, const Term &k)
