@@ -25,6 +25,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "few_layout.h"
 #include "flood_kernels.h"
 #include "minsum_kernels.h"
 
@@ -56,19 +57,21 @@ template <class A>
 __global__ __launch_bounds__(256) void k_few_ingest(const typename A::T *__restrict__ llr, int32_t F, int32_t n,
                                                     int32_t W, typename A::T *__restrict__ Lch,
                                                     int32_t *__restrict__ done, int32_t *__restrict__ unsat,
-                                                    int32_t unsat_words)
+                                                    int64_t unsat_words, int64_t words)
 {
     using T = typename A::T;
-    const int32_t i = static_cast<int32_t>(blockIdx.x * blockDim.x + threadIdx.x);
-    if (i < W)
-        done[i] = -1;
-    if (i < unsat_words)
-        unsat[i] = 0;
-    const int32_t f = i % W, c = i / W;
-    if (c >= n)
-        return;
-    const T v = f < F ? llr[static_cast<int64_t>(f) * n + c] : T(1);
-    Lch[i] = v * T(A::kIn);
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
+    for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < words; i += stride) {
+        if (i < W)
+            done[i] = -1;
+        if (i < unsat_words)
+            unsat[i] = 0;
+        if (i < static_cast<int64_t>(n) * W) {
+            const int32_t f = static_cast<int32_t>(i) % W, c = static_cast<int32_t>(i) / W;
+            const T v = f < F ? llr[static_cast<int64_t>(f) * n + c] : T(1);
+            Lch[i] = v * T(A::kIn);
+        }
+    }
 }
 
 // Byte offset of frame f of item i in an array [items][W]: 24-bit factors and a
@@ -253,13 +256,12 @@ ldpc_status run_few(const ldpc_code_s *c, int32_t frames, int32_t max_iter, bool
     constexpr int32_t FW = few_width(KL);
     const int32_t W = (frames + FW - 1) / FW * FW;
     T *buffer[2] = {R, R + c->E * W};
-    const int32_t unsat_words = es ? max_iter * W : 0;
-    const int32_t words = std::max(c->n * W, unsat_words);
-    const dim3 vgrid(static_cast<unsigned>((words + 255) / 256)), ogrid(static_cast<unsigned>((c->n * W + 255) / 256));
+    const FewInit init = few_init(c->n, W, max_iter, es);
+    const dim3 vgrid(init.blocks), ogrid(static_cast<unsigned>((c->n * W + 255) / 256));
     {
         ProfScope ps(LDPC_KERNEL_INGEST, s);
         LDPC_LAUNCH(ps, (k_few_ingest<A>), vgrid, dim3(256), 0, s, llr, frames, c->n, W, Lch, done, unsat,
-                    unsat_words);
+                    init.unsat_words, init.words);
     }
     FewArgs<A> a{c->row_ptr, c->col_idx, c->col_ptr, c->col_edge, c->m, c->n, W, W / FW, Lch, nullptr, nullptr, done,
                  nullptr, nullptr, 0, scale, offset};
@@ -269,7 +271,7 @@ ldpc_status run_few(const ldpc_code_s *c, int32_t frames, int32_t max_iter, bool
         a.Rold = buffer[(t - 1) & 1];
         a.Rnew = buffer[t & 1];
         a.unsat = unsat + static_cast<int64_t>(t - 1) * W;
-        a.unsat_prev = a.unsat - W;
+        a.unsat_prev = t > 1 ? a.unsat - W : nullptr;
         ProfScope ps(LDPC_KERNEL_CHECK, s);
         if (t == 1 && es)
             LDPC_LAUNCH(ps, (k_few<A, KL, true, true, MS>), grid, dim3(256), 0, s, a);
