@@ -484,14 +484,15 @@ bool fused_decode(const ldpc_job &job, ldpc_dtype dt, void *ws, hipStream_t stre
     const FusedFit fit = fused_fit(job.code, dt, limit);
     if (!fit.ok || !frame_resident_faster(job, dt, limit))
         return false;
-    const LaunchCfg cfg = cfg_for(&job, 1, dt);
     Group g;
     g.tsize = dt == LDPC_F64 ? sizeof(double) : sizeof(float);
     g.jobs[g.njobs++] = 0;
     g.add_code(job.code);
     g.bucket = fit.bucket;
     char *w = static_cast<char *>(ws);
-    const int threads = job_threads(job, dt, cfg.threads);
+    // The workgroup size is the launch's choice: the batch path's settings and
+    // tuned sizes, made for its batches, are not this call's.
+    constexpr int threads = fused::kBaseThreads;
     *rc = dt == LDPC_F64 ? launch_group<ArithF64>(&job, g, w, threads, stream, true)
                          : launch_group<ArithF32>(&job, g, w, threads, stream, true);
     return true;
