@@ -432,11 +432,15 @@ ldpc_status ldpc_batch_job_threads(const ldpc_job *jobs, int32_t njobs, ldpc_dty
 /*
  * Autotuner of the batch path (Section III-A: the mapping of frames onto the
  * GPU).  Decodes the given jobs (their output buffers are overwritten,
- * inputs untouched) under candidate launch configurations, in two stages:
+ * inputs untouched) under candidate launch configurations, in three stages:
  * first, for each code (device architecture, code shape by sizes and degree
- * profiles, dtype, flags), that code's jobs alone at workgroup sizes 64, 128,
- * 192, 256, 384 and 512, recording the fastest size for the code (used by
- * every later batch with jobs of that code); then the whole batch with one
+ * profiles, dtype, flags, and whether the job's frames exceed the compute
+ * units), that code's jobs alone at workgroup sizes 64, 128, 192, 256, 384 and
+ * 512, recording the fastest size for the code (used by every later batch with
+ * jobs of that code and that many frames); then the whole batch with these
+ * sizes and with every size left to the launch, alternating, keeping the
+ * sizes only if the whole batch is faster with them (else 512 is recorded for
+ * each code); then the whole batch with one
  * frame per workgroup and, where some job can use it, two
  * (ldpc_batch_set_frames_per_group), recording the faster for this batch
  * shape (the codes, frame counts rounded up to a power of two, iteration

@@ -39,6 +39,7 @@ std::map<uint64_t, Tuned> g_code_tuned; // code key -> workgroup size chosen for
 constexpr int kMaxArchDevices = 64;
 uint64_t g_arch_hash[kMaxArchDevices];  // per device: hash of its architecture name, 0 until looked up
 char g_arch_name[kMaxArchDevices][64];
+int g_arch_cus[kMaxArchDevices];  // and its compute units
 
 uint64_t fnv(uint64_t x, uint64_t v)
 {
@@ -50,12 +51,15 @@ uint64_t fnv(uint64_t x, uint64_t v)
 }
 
 // The current device's architecture name (e.g. "gfx950:sramecc+:xnack-")
-// and its hash, looked up once per device.  Caller holds g_mu.
-const char *arch_of_current(uint64_t *hash)
+// and its hash and compute units (may be null), looked up once per device.
+// Caller holds g_mu.
+const char *arch_of_current(uint64_t *hash, int *cus = nullptr)
 {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxArchDevices) {
         *hash = 1;
+        if (cus)
+            *cus = 0;
         return "";
     }
     if (g_arch_hash[dev] == 0) {
@@ -65,10 +69,13 @@ const char *arch_of_current(uint64_t *hash)
             std::snprintf(g_arch_name[dev], sizeof(g_arch_name[dev]), "%s", prop.gcnArchName);
             for (const char *c = g_arch_name[dev]; *c; ++c)
                 x = fnv(x, static_cast<unsigned char>(*c));
+            g_arch_cus[dev] = prop.multiProcessorCount;
         }
         g_arch_hash[dev] = x | 1;
     }
     *hash = g_arch_hash[dev];
+    if (cus)
+        *cus = g_arch_cus[dev];
     return g_arch_name[dev];
 }
 
@@ -96,16 +103,21 @@ uint64_t shape_key(const ldpc_job *jobs, int32_t njobs, ldpc_dtype dt)
 }
 
 // Key of one job's code for the per-code workgroup size: device
-// architecture, dtype, the code's shape and the job's flags (the decoding
-// mode selects the kernel body).  Caller holds g_mu.
+// architecture, dtype, the code's shape, the job's flags (the decoding
+// mode selects the kernel body) and whether its frames are few enough for a CU
+// each: the best size of a large batch shares the CUs out among frames, and is
+// up to five times slower for frames that have a CU of their own (one frame of
+// n = 1944: 64 threads 473 us, 1024 81).  Caller holds g_mu.
 uint64_t code_key(const ldpc_job &j, ldpc_dtype dt)
 {
     uint64_t arch = 0;
-    arch_of_current(&arch);
+    int cus = 0;
+    arch_of_current(&arch, &cus);
     uint64_t x = fnv(fnv(1099511628211ull, arch), 0xc0de);
     x = fnv(x, static_cast<uint64_t>(dt));
     x = fnv(x, j.code->shape_hash);
-    return fnv(x, j.flags);
+    x = fnv(x, j.flags);
+    return j.frames > cus ? x : fnv(x, 0xce11);
 }
 
 // Workgroup size of one job's fused launch: its code's tuned size, else the
@@ -879,13 +891,17 @@ ldpc_status time_candidate(const ldpc_job *jobs, int32_t njobs, ldpc_dtype dtype
 
 }  // namespace
 
-// Two stages.  Per code (device architecture, shape, dtype, flags): the jobs
-// of that code alone, at each workgroup size; the fastest is recorded for
-// the code and used by every later batch (small codes keep more frames per
-// CU in flight with smaller workgroups, large ones decode each frame faster
-// with larger ones; jobs of different sizes run as separate launches).  Per
-// batch shape: frames per workgroup 1, and 2 where some job can use it, with
-// the per-code sizes.  Every candidate's outputs must equal the first run's.
+// Three stages.  Per code (device architecture, shape, dtype, flags, few frames or
+// many): the jobs of that code alone, at each workgroup size (512: the launch's
+// choice); the fastest is recorded for the code and used by every later batch.
+// Then the whole batch, with those sizes and with every size left to the launch, in
+// turn: jobs of different sizes run as launches of their own, each of which ends on
+// CUs that the next could use, and a size that is best alone need not be best
+// there.  The sizes stay only if the slowest run with them is faster than the
+// fastest without (12 codes, 16384 frames: sizes found alone, of three runs of the
+// tuner, 1.539, 1.556 and 1.419 ms, the launch's choice 1.463).  Last, per
+// batch shape: frames per workgroup 1, and 2 where some job can use it.
+// Every candidate's outputs must equal the first run's.
 extern "C" ldpc_status ldpc_autotune_batch(const ldpc_job *jobs, int32_t njobs, ldpc_dtype dtype, void *workspace,
                                            size_t workspace_bytes, void *stream, int32_t *best_threads,
                                            double *best_ms)
@@ -954,7 +970,41 @@ try {
             g_code_tuned[ckeys[c]] = Tuned{LaunchCfg{best_t, 0}, best};
         }
     }
-    // stage 2: frames per workgroup for the whole batch
+    // stage 2: the sizes together, against none
+    if (rc == LDPC_OK) {
+        std::vector<Tuned> sizes;
+        bool any = false;
+        {
+            std::lock_guard<std::mutex> lk(g_mu);
+            g_tuned.erase(key);
+            for (const uint64_t ck : ckeys) {
+                sizes.push_back(g_code_tuned[ck]);
+                any |= sizes.back().cfg.threads != fused::kBaseThreads;
+            }
+        }
+        const auto set = [&](bool sized) {
+            std::lock_guard<std::mutex> lk(g_mu);
+            for (size_t c = 0; c < ckeys.size(); ++c) {
+                Tuned t = sizes[c];
+                if (!sized)
+                    t.cfg.threads = fused::kBaseThreads;
+                g_code_tuned[ckeys[c]] = t;
+            }
+        };
+        constexpr int kRounds = 5;
+        double least[2] = {0.0, 0.0}, most[2] = {0.0, 0.0};  // of the runs without and with sizes
+        for (int round = 0; any && round < kRounds && rc == LDPC_OK; ++round)
+            for (int sized = 0; sized < 2 && rc == LDPC_OK; ++sized) {
+                set(sized != 0);
+                double ms = 0.0;
+                rc = time_candidate(jobs, njobs, dtype, workspace, workspace_bytes, s, e0, e1, ref, cur, ms);
+                least[sized] = round == 0 ? ms : std::min(least[sized], ms);
+                most[sized] = std::max(most[sized], ms);
+            }
+        if (any)
+            set(most[1] < least[0]);
+    }
+    // stage 3: frames per workgroup for the whole batch
     LaunchCfg best_cfg{default_threads, 1};
     double best_t = 0.0;
     bool have = false;

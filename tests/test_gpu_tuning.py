@@ -6,7 +6,6 @@ tells apart, whose measured times are given beside it.
 """
 import statistics
 
-import numpy as np
 import pytest
 
 from workloads import configs
@@ -57,3 +56,53 @@ def test_decode_takes_no_batch_setting(L):
     limited = _us(call)
     print(f"[gpu] ldpc_decode {usual:.1f} us, under 64 threads {limited:.1f} us", flush=True)
     assert limited < 2.0 * usual
+
+
+def test_tuning_does_not_slow_the_batch(L, tmp_path):
+    """16384 frames of twelve codes after ldpc_autotune_batch take no longer than
+    with every size left to the launch.  The limit is 3%: repeated runs differ by
+    less than 1%; with the sizes that are fastest for each code alone the batch
+    took 5% longer."""
+    import torch
+    mix = configs.qc_mix()
+    jobs = [L.Job(L.Code.from_workload(m.code), torch.from_numpy(m.llr).cuda(), 10, early_stop=True) for m in mix]
+    cj = [j.c_struct() for j in jobs]
+    need = L.ldpc_batch_workspace_bytes(cj, torch.float32)
+    ws = torch.empty(max(need, 1), dtype=torch.uint8, device="cuda")
+
+    def call():
+        assert L.ldpc_decode_batch(cj, torch.float32, ws, need) == 0
+    L.autotune_batch(jobs)
+    path = str(tmp_path / "tune.txt")
+    assert L.ldpc_tuning_save(path) == L.LDPC_OK
+    sizes = L.ldpc_batch_job_threads(cj, torch.float32)
+    with_table, without = [], []
+    for _ in range(5):
+        L.ldpc_tuning_clear()
+        without.append(_us(call, 7))
+        assert L.ldpc_tuning_load(path)[0] == L.LDPC_OK
+        with_table.append(_us(call, 7))
+    a, b = statistics.median(with_table), statistics.median(without)
+    print(f"[gpu] mix: tuned {a:.1f} us, not {b:.1f}, sizes {sizes}", flush=True)
+    assert a < 1.03 * b
+
+
+def test_sizes_of_a_large_batch_leave_few_frames_alone(L, tmp_path):
+    """A workgroup size recorded for many frames of a code is not used for a batch
+    of a few of them, whose frames have a CU each."""
+    import torch
+    b = configs.qc1944(2.0, frames=1024)
+    h = L.Code.from_workload(b.code)
+    x = torch.from_numpy(b.llr).cuda()
+    many, few = L.Job(h, x, 10), L.Job(h, x[:3].contiguous(), 10)
+    L.autotune_batch([many])
+    path = tmp_path / "tune.txt"
+    assert L.ldpc_tuning_save(str(path)) == L.LDPC_OK
+    lines = [line.split() for line in path.read_text().splitlines()]
+    for line in lines:  # as if 64 threads had been the fastest
+        line[2] = "64" if line[3] == "0" else line[2]
+    path.write_text("".join(" ".join(line) + "\n" for line in lines))
+    L.ldpc_tuning_clear()
+    assert L.ldpc_tuning_load(str(path))[0] == L.LDPC_OK
+    assert L.ldpc_batch_job_threads([many.c_struct()], torch.float32) == [64]
+    assert L.ldpc_batch_job_threads([few.c_struct()], torch.float32) == [512]
