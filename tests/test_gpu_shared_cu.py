@@ -63,3 +63,57 @@ def test_layered(L, name, es):
     import torch
     mb, Z = LAYERED[name]
     _compare(L, name, codes.qc_code(mb, 24, Z, 47), torch.float32, 700, 4, es, layered=True)
+
+
+# rows of each degree bucket of the frame-resident kernel
+DEGREES = {
+    "d8": lambda: codes.random_rows(170, 400, 3, 8, 711),
+    "d16": lambda: codes.qc_row_degrees([16, 14, 12, 10, 9, 9], 16, 27, 701),
+    "d24": lambda: codes.qc_row_degrees([24, 22, 20, 18, 17], 24, 27, 702),
+    "d32": lambda: codes.random_rows(40, 400, 25, 32, 705, dense_col=True),
+}
+RULES = {
+    "flooding": {},
+    "layered": dict(layered=True),
+    "minsum": dict(rule="minsum", ms_scale=0.8125, ms_offset=0.25),
+    "layered_minsum": dict(layered=True, rule="minsum"),
+}
+
+
+@pytest.mark.parametrize("rule", list(RULES))
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("name", list(DEGREES))
+def test_degree_buckets(L, name, dtype, rule):
+    """More frames of a short code than the device holds at once in any instance
+    (24 wavefronts a CU in workgroups of two)."""
+    import torch
+    td = torch.float32 if dtype == "f32" else torch.float64
+    for es in (False, True):
+        _compare(L, name, DEGREES[name](), td, 3300, 4, es, **RULES[rule])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_jobs_of_every_kind(L, dtype):
+    """One launch of jobs of every schedule, rule and bucket, drawn from one queue,
+    against each job's own launch."""
+    import torch
+    td = torch.float32 if dtype == "f32" else torch.float64
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(52)
+
+    def jobs_of():
+        return [L.Job(h, x, 5, early_stop=es, **kw) for h, x, es, kw in specs]
+    specs = []
+    for i, make in enumerate(DEGREES.values()):
+        code = make()
+        h = L.Code.from_workload(code)
+        for k, kw in enumerate(RULES.values()):
+            x = 2.5 + 1.7 * torch.randn((150 + 37 * k + i, code.n), generator=gen, device="cuda", dtype=torch.float64)
+            specs.append((h, x.to(td), (i + k) % 2 == 0, kw))
+    print(f"[gpu] shared: jobs of every kind {dtype}", flush=True)
+    together, alone = jobs_of(), jobs_of()
+    L.decode_batch(together)
+    for job in alone:
+        L.decode_batch([job])
+    for a, b in zip(together, alone):
+        assert torch.equal(a.bits, b.bits) and torch.equal(a.iters, b.iters) and torch.equal(a.posterior, b.posterior)
