@@ -39,18 +39,24 @@ ldpc_status build_host_layout(int32_t m, int32_t n, const int32_t *row_ptr, cons
     h.m = m;
     h.n = n;
     h.row_ptr.assign(row_ptr, row_ptr + m + 1);
-    h.col_idx.resize(E);
+    h.col_idx.assign(col_idx, col_idx + E);
     for (int32_t i = 0; i < m; ++i) {
         const int32_t b = row_ptr[i], e = row_ptr[i + 1];
+        int32_t last = -1;
+        bool ascending = true;
         for (int32_t k = b; k < e; ++k) {
-            if (col_idx[k] < 0 || col_idx[k] >= n)
+            const int32_t c = col_idx[k];
+            if (c < 0 || c >= n)
                 return LDPC_EINVAL;
-            h.col_idx[k] = col_idx[k];
+            ascending &= c > last;
+            last = c;
         }
-        std::sort(h.col_idx.begin() + b, h.col_idx.begin() + e);
-        for (int32_t k = b + 1; k < e; ++k)
-            if (h.col_idx[k] == h.col_idx[k - 1])
-                return LDPC_EINVAL;  // duplicate edge
+        if (!ascending) {
+            std::sort(h.col_idx.begin() + b, h.col_idx.begin() + e);
+            for (int32_t k = b + 1; k < e; ++k)
+                if (h.col_idx[k] == h.col_idx[k - 1])
+                    return LDPC_EINVAL;  // duplicate edge
+        }
         h.max_row_deg = std::max(h.max_row_deg, e - b);
     }
     if (h.max_row_deg > LDPC_MAX_ROW_DEGREE)
@@ -63,12 +69,9 @@ ldpc_status build_host_layout(int32_t m, int32_t n, const int32_t *row_ptr, cons
         h.col_ptr[j + 1] += h.col_ptr[j];
     }
     h.col_edge.resize(E);
-    std::vector<int32_t> fill(n, 0);
-    for (int32_t i = 0; i < m; ++i)
-        for (int32_t k = row_ptr[i]; k < row_ptr[i + 1]; ++k) {
-            const int32_t j = h.col_idx[k];
-            h.col_edge[h.col_ptr[j] + fill[j]++] = k;
-        }
+    std::vector<int32_t> next(h.col_ptr.begin(), h.col_ptr.end() - 1);
+    for (int32_t k = 0; k < static_cast<int32_t>(E); ++k)  // E is at most LDPC_MAX_EDGES
+        h.col_edge[next[h.col_idx[k]]++] = k;
     return LDPC_OK;
 }
 
