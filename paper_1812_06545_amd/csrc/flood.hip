@@ -411,8 +411,8 @@ ldpc_status decode_impl(const ldpc_code_s *c, int32_t frames, int32_t max_iter, 
             launch_ms<A>(c->max_row_deg, false, first, es, rgrid, s, ma);
         } else {
             // (guarded rows, FP64 or longer than 32, take one)
-            const bool exact = std::is_same<T, float>::value && c->max_row_deg <= 32;
-            const int32_t steps = exact && rgrid.x >= 6000 ? 2 : 1, takings = (rgroups + steps - 1) / steps;
+            const int32_t steps = std::is_same<T, float>::value ? row_group_steps(c->max_row_deg, rgrid.x) : 1;
+            const int32_t takings = (rgroups + steps - 1) / steps;
             const CheckArgs<A> ca{c->row_ptr, c->col_idx, c->m, c->n, c->E, takings, steps, nchunk,
                                   R, L, done, unsat_t};
             launch_check<A>(c, first, es, dim3(static_cast<unsigned>(takings) * nchunk), s, ca);

@@ -196,14 +196,25 @@ __device__ __forceinline__ void check_row_exact(int d, const int32_t *__restrict
     }
 }
 
+// Row groups a block of the check kernel takes, from the launch's row groups and the
+// longest row.  Two pay on large launches of short rows, whose blocks are brief;
+// longer rows only lose the evening-out between CUs.  us per call of 10 iterations,
+// one and two: rows of degree 7, 2025 groups 186 and 190, 8100 493 and 475, 32400
+// 1788 and 1687 (with early stop 1727 and 1646); up to 16, 6004 groups 430 and 442,
+// 12008 716 and 715, 24016 1420 and 1399; up to 24, 6000 groups 738 and 760, 12000 1473
+// and 1482; up to 32, 5200 groups 861 and 916.
+constexpr int kStepRows = 16;
+inline int row_group_steps(int max_row_deg, int64_t row_groups)
+{
+    return row_groups >= (max_row_deg <= 8 ? 8000 : max_row_deg <= kStepRows ? 20000 : INT64_MAX) ? 2 : 1;
+}
+
 // Check-node kernel (Loop 2): one wavefront = one check row x 64 frames.
 // Rows must have degree <= DB.  EXACT selects straight-line bodies per degree.
 // A block takes `steps` consecutive row groups of a chunk (`groups` counts
-// those takings): two on launches of 6000 row groups or more, where dispatching
-// a block for each costs (us per call of 10 iterations, 1, 2, 4 and 8 steps: n =
-// 64800, 256 frames 1777, 1681, 1694, 1731; n = 16200, 512 frames 852, 804, 816,
-// 828; n = 12007 of degree 16, 64 frames, 1501 groups 196, 190, 213, 259), and
-// where a stopped chunk's blocks cost as much as a quarter of a running one's.
+// those takings): one, or two on large launches of short rows (row_group_steps),
+// where dispatching a block for each costs, and where a stopped chunk's blocks
+// cost as much as a quarter of a running one's.
 // Rows up to 16: held to the registers of 6 wavefronts per SIMD, which the bodies
 // need (66 to 71); left alone the compiler takes 99 with early stop (a chunk of n =
 // 12007, 8 iterations, 149 us a call; held, 142).
@@ -241,7 +252,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EXACT && DB
                 check_row_guarded<A, DB, FIRST, ES>(col_idx + e0, d, Lc, Rrow, off, odd);
         }
     };
-    if constexpr (EXACT) {
+    if constexpr (EXACT && DB <= kStepRows) {
         for (int step = 0; step < steps; ++step) {
             const int row = (group * steps + step) * kWaves + wave;
             if (row >= m)
@@ -251,7 +262,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(EXACT && DB
             parity |= odd;
         }
     } else {
-        // the guarded rows' registers (FP64: 88) grow by half in a loop
+        // (in a loop the guarded rows' registers, FP64: 88, grow by half)
         const int row = group * kWaves + wave;
         if (row >= m)
             return;
@@ -433,7 +444,7 @@ void launch_check_bucket(const CheckArgs<A> &a, bool first, bool es, dim3 grid, 
     do {                                                                                                         \
         ProfScope ps(LDPC_KERNEL_CHECK, s);                                                                      \
         LDPC_LAUNCH(ps, (flood::k_check<A_, DB_, EX_, F_, E_>), grid, dim3(256), 0, s, a.row_ptr, a.col_idx, a.m, \
-                    a.n, a.E, a.groups, a.steps, a.nchunk, a.R, a.L, a.done, a.unsat);                                   \
+                    a.n, a.E, a.groups, a.steps, a.nchunk, a.R, a.L, a.done, a.unsat);                         \
     } while (0)
 
 #define LDPC_DEFINE_CHECK_BUCKET(A_, DB_, EX_)                                                                  \

@@ -86,18 +86,23 @@ def test_minsum(L, name, dtype, layered):
         compare(ref, bits, iters, post, llr.dtype, f"streaming min-sum {name}")
 
 
+# the row groups from which a block of the check kernel takes two
+TWO_GROUPS = {"d8": 8000, "qc_d16": 20000}
+
+
 @pytest.mark.parametrize("es", [False, True])
-@pytest.mark.parametrize("name", ["d8", "qc_d16", "qc_d24", "qc_d32"])
+@pytest.mark.parametrize("name", list(TWO_GROUPS))
 def test_two_row_groups_a_block(L, name, es):
-    """Launches of 6000 row groups or more, of which a block of the check kernel
-    takes two: an odd number of groups and a last one of fewer than four rows."""
+    """Launches of which a block of the check kernel takes two row groups: an odd
+    number of groups and a last one of fewer than four rows."""
     if name == "d8":
         code = codes.random_rows(135, 400, 3, 8, 707)
         llr = (2.5 + 1.6 * np.random.default_rng(708).standard_normal((FRAMES, code.n))).astype(np.float32)
     else:
         code, llr = workload(name, "f32")
     chunks = -(-FRAMES // 64)
-    K = next(k for k in range(1, 200) if code.m * k % 4 and -(-code.m * k // 4) % 2 and -(-code.m * k // 4) * chunks >= 6000)
+    K = next(k for k in range(1, 400) if code.m * k % 4 and -(-code.m * k // 4) % 2
+             and -(-code.m * k // 4) * chunks >= TWO_GROUPS[name])
     T = 20 if es else 4
     print(f"[gpu] two row groups a block: {name} K={K} es={es}", flush=True)
     got = _decode_stacked(L, code, llr, K, T, es)

@@ -72,3 +72,9 @@ def test_check_kernel_of_long_rows(kernels):
     registers): no sign masks beside them."""
     got = [v for k, v in kernels.items() if "flood7k_checkINS_8ArithF32ELi64E" in k]
     assert len(got) == 4 and all(scalars < 250 for _, _, scalars in got), got
+
+
+def test_check_kernel_with_early_stop(kernels):
+    """Rows of up to 32 edges: the sign masks stay in scalar registers."""
+    got = [v for k, v in kernels.items() for d in (8, 16, 24, 32) if f"flood7k_checkINS_8ArithF32ELi{d}E" in k]
+    assert len(got) == 16 and all(scalars < 10 for _, _, scalars in got), got
