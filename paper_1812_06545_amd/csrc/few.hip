@@ -292,14 +292,18 @@ ldpc_status run_few(const ldpc_code_s *c, int32_t frames, int32_t max_iter, bool
 }  // namespace
 
 // The streaming kernels cost the same from 1 to 64 frames; a launch here costs
-// in proportion to its wavefronts, m x (frame groups), beyond its latency.
-// Measured on MI355X, 20 iterations, us per call, streaming kernels and 1, 2,
-// 3, 4 groups: n = 16200 of degree 7 FP32 335 and 161, 223, 307, -, FP64 600
-// and 207, 300, 420, 512; n = 64800 FP32 905 and 414, 688, FP64 1840 and 550,
-// 928, 1396; n = 12007 of degree 16 FP32 350 and 147, 213, -, 338 (four groups:
-// left to the streaming kernels), FP64 730 and 199, 286, -, 450.  The bound on
-// the reads keeps out codes whose dense columns would be summed by very many
-// rows (near it: a column of degree 2503, 19.3 and 3.3 to 17.5 ms).
+// in proportion to its wavefronts, m x (frame groups), beyond its latency, and
+// more for long rows, whose lanes gather more.  Measured on MI355X, us per call,
+// streaming kernels and 1, 2, 3, 4 groups, 20 iterations: n = 16200 of degree 7 FP32
+// 335 and 161, 223, 307, -, FP64 600 and 207, 300, 420, 512; n = 64800 FP32 905 and
+// 414, 688, FP64 1840 and 550, 928, 1396; n = 12007 of degree 16 FP32 350 and 147, 213,
+// -, 338 (four groups: left to the streaming kernels), FP64 730 and 199, 286, -, 450.
+// The third group in FP32, 8 iterations, streaming and here, sum-product with early
+// stop and min-sum: degree 7, 14000 rows 197 and 196, 199 and 162; 20000 rows 250 and 265,
+// - ; degree 9 to 16, 14000 rows 285 and 241, 277 and 220; degree 20 to 32, 6000 rows 297
+// and 252, 243 and 238; 9000 rows 406 and 375, 336 and 355; 18000 rows 716 and 778, 630 and
+// 749.  The bound on the reads keeps out codes whose dense columns would be summed by
+// very many rows (near it: a column of degree 2503, 19.3 and 3.3 to 17.5 ms).
 bool few_frames_path(const ldpc_code_s *c, bool f64, int32_t frames)
 {
     if (frames > kFewFrames || c->max_row_deg > 32)
@@ -307,7 +311,9 @@ bool few_frames_path(const ldpc_code_s *c, bool f64, int32_t frames)
     const int32_t width = few_width(c->max_row_deg), groups = (frames + width - 1) / width;
     if (std::max<int64_t>(c->E, c->n) * groups * width >= 1 << 24)  // 24-bit factors, 32-bit byte offsets
         return false;
-    return groups <= (c->m <= 20000 ? 3 : 2) + (f64 ? 1 : 0) && c->column_reads * groups * width <= 1 << 26;
+    const int32_t third = c->max_row_deg <= 16 ? 14000 : 6000;  // rows up to which FP32 takes three groups
+    const int32_t most = f64 ? (c->m <= 20000 ? 4 : 3) : c->m <= third ? 3 : 2;
+    return groups <= most && c->column_reads * groups * width <= 1 << 26;
 }
 
 template <class A>

@@ -73,3 +73,39 @@ def test_route(L, name, dtype):
     job = L.Job(h, x, iters, **options)
     L.decode_batch([job])
     assert torch.equal(bits, job.bits) and torch.equal(its, job.iters) and torch.equal(post, job.posterior)
+
+
+# code, frames, one launch per iteration?  (5 to 20% either way between the two forms)
+FEW = {
+    "d7_three_groups": (lambda: codes.staircase_irregular(16200, 502), 24, True),
+    "d7_large": (lambda: codes.staircase_irregular(40000, 41), 24, False),
+    "d7_large_two_groups": (lambda: codes.staircase_irregular(40000, 41), 16, True),
+    "d32_three_groups": (lambda: codes.random_rows(5000, 16000, 20, 32, 42), 6, True),
+    "d32_large": (lambda: codes.random_rows(12000, 40000, 20, 32, 42), 6, False),
+    "d32_large_two_groups": (lambda: codes.random_rows(12000, 40000, 20, 32, 42), 4, True),
+}
+
+
+@pytest.mark.parametrize("name", list(FEW))
+def test_few_frames_route(L, name):
+    """A few frames of a code that streams: one launch per iteration (no variable
+    kernel) where that is the faster form; the outputs are those of a call of
+    more frames, which never takes it."""
+    import torch
+    make, frames, one_launch = FEW[name]
+    code = make()
+    h = L.Code.from_workload(code)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(53)
+    x = 2.2 + 1.8 * torch.randn((64, code.n), generator=gen, device="cuda")
+    print(f"[gpu] few route {name}", flush=True)
+    L.ldpc_profile_enable(True)
+    try:
+        L.ldpc_profile_collect()
+        got = L.decode(h, x[:frames].contiguous(), 4, early_stop=True)
+        launched = {k: count for k, (_, count) in L.ldpc_profile_collect().items()}
+    finally:
+        L.ldpc_profile_enable(False)
+    assert launched["fused"] == 0 and (launched["variable"] == 0) == one_launch, launched
+    for a, b in zip(got, L.decode(h, x, 4, early_stop=True)):
+        assert torch.equal(a, b[:frames])
