@@ -157,8 +157,8 @@ ldpc_status ldpc_workspace_bytes(ldpc_code code, ldpc_dtype dtype, int32_t frame
 /*
  * Decode `frames` frames of one code.  A code that fits the frame-resident
  * kernel (ldpc_batch_fits_fused) is decoded by one launch of it, as a job of
- * ldpc_decode_batch, unless the frames are so many and the code so short (or a
- * frame's work so serial) that the other path is estimated to be faster.
+ * ldpc_decode_batch, unless the other path is estimated to be faster (very
+ * many frames of a short code, a few of a long one, columns of very high degree).
  * Otherwise the call runs per-iteration kernel launches (the plain path, messages streamed through
  * device memory; the same outputs bit for bit): flooding runs one
  * check-node and one variable-node kernel per iteration (Section II,

@@ -8,6 +8,7 @@
 // argument.
 #include <algorithm>
 #include <chrono>
+#include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <map>
@@ -429,63 +430,74 @@ ldpc_status launch_group(const ldpc_job *jobs, const Group &g, char *ws, int thr
 }
 
 // Whether ldpc_decode runs a code that fits the frame-resident kernel faster
-// there than with the streaming kernels.  Up to the frames that the device holds
-// at once it does.  Beyond, a workgroup per frame loses on very short codes:
-// frames are drawn from one counter, 11.5 ns each whatever their size, and a
-// frame of few rows leaves most of its workgroup idle, where the streaming
-// kernels pack 64 frames to a wavefront.  It also loses where a frame's time is
-// one long serial chain (a column of very high degree, many small layers), which
-// then repeats for every pass of frames over the device.  Both times are
-// estimated in us; the constants are a fit to 2184 calls on MI355X (38 codes of 12
-// to 16552 edges, 2048 to 131072 frames, 0 to 20 iterations, either schedule, rule
-// and type), of which the choice leaves 24 more than 5% slower than the streaming
-// kernels, the worst by 29%.  us per call, streaming and frame-resident kernels:
-// Hamming (7,4), 10 iterations, 4096 frames 50 and 53, 131072 frames 187 and 1938;
-// qc n = 96 of 808 edges, 32768 frames, 5 iterations 301 and 400, layered 515 and 1141;
-// n = 384 of degree 6, 131072 frames, 1 iteration 613 and 1504, 20 iterations 8302 and
-// 4367; n = 1536, 32768 frames, 5 iterations 2287 and 1124; a column of degree 3000,
-// 8192 frames, 5 iterations 8113 and 17362.
+// there than with the streaming kernels.  It mostly does, but
+//   - frames beyond those the device holds at once are drawn from one counter, 11.5
+//     ns each whatever their size, and a frame of few rows leaves most of its
+//     workgroup idle, where the streaming kernels pack 64 frames to a wavefront;
+//   - a frame's time may be one long chain (a column of very high degree, many small
+//     layers), which repeats for every pass of frames over the device;
+//   - a few frames of a long code use a CU each, where the streaming kernels spread
+//     their rows over the device.
+// Both times are estimated in us.  The constants are a fit to 4300 calls on
+// MI355X (69 codes of 12 to 30449 edges, 1 to 131072 frames, 0 to 20 iterations, either
+// schedule, rule and type), of which the choice leaves 37 more than 5% slower than
+// the streaming kernels, the worst by 46%.  us per call, streaming and
+// frame-resident kernels: Hamming (7,4), 10 iterations, 4096 frames 50 and 53, 131072 frames
+// 187 and 1938; qc n = 96 of 808 edges, 32768 frames, 5 iterations 301 and 400, layered
+// 515 and 1141; n = 384 of degree 6, 131072 frames, 1 iteration 613 and 1504, 20 iterations
+// 8302 and 4367; a column of degree 3000, 8192 frames, 5 iterations 8113 and 17362; n =
+// 8000 of degree 7, 8 iterations, 1 frame 46 and 113, 32 frames 90 and 116, 128 frames
+// 131 and 117; qc n = 3360, 1 frame 53 and 87, 8 frames 95 and 89.
 bool frame_resident_faster(const ldpc_job &j, ldpc_dtype dt, size_t limit)
 {
     const ldpc_code_s *c = j.code;
     const bool layered = (j.flags & LDPC_LAYERED) != 0, ms = (j.flags & LDPC_MIN_SUM) != 0, f64 = dt == LDPC_F64;
+    const bool es = (j.flags & LDPC_EARLY_STOP) != 0;
     const size_t tsize = f64 ? sizeof(double) : sizeof(float);
-    const int32_t groups = (c->m + 31) / 32, layers = static_cast<int32_t>(c->layer_dmax.size());
+    const double ts = static_cast<double>(tsize), E = static_cast<double>(c->E), n = c->n;
+    const double column = c->max_col_deg, half = (c->max_row_deg + 1) / 2, quarter = ((c->max_row_deg + 1) / 2 + 1) / 2;
+    const int32_t layers = static_cast<int32_t>(c->layer_dmax.size());
     const int32_t layer_rows = (c->m + layers - 1) / layers;  // of a mean layer
-    // frames the device holds: wavefronts of a frame, wavefronts and LDS of a CU (workgroup_threads)
+    const double launched = j.max_iter, run = es ? 0.8 * j.max_iter : j.max_iter;  // iterations
+
+    // Streaming: a launch's latency, longer for longer rows; the bytes of the padded
+    // frames at 6 TB/s, 7.7 values per variable among them for the way in and
+    // out; a column's chain of loads.
+    const double padded = static_cast<double>(frames_padded(j.frames));
+    const double way = 7.7 * padded * ts * n / 6e6;
+    double streaming;
+    if (layered) {
+        streaming = 8.0 + 3.0 * launched * (layers + (es ? 2 : 0)) + run * padded * ts * 4.0 * E / 6e6 + way;
+    } else if (const int32_t few = few_frames_groups(c, f64, j.frames)) {
+        streaming = 10.0 + 2.6 * launched + run * (7e-6 * ts * E * few + 0.053 * column);
+    } else {
+        streaming = 8.0 + launched * (3.8 + 0.1 * c->max_row_deg) +
+                    run * (padded * ts * (3.0 * E + 2.0 * n) / 6e6 + 0.19 * column) + way;
+    }
+
+    // Frame-resident: an iteration's latency and, on one CU, its issue time.
+    const double groups = (c->m + 31) / 32, column_groups = (c->n + 63) / 64;
+    const double slow = (f64 ? 2.0 : 1.0) * (ms ? 0.57 : 1.0);  // of a slot
+    double latency, issue;
+    if (layered) {
+        latency = layers * (0.25 + 0.15 * quarter);
+        issue = 0.022 * slow * quarter * layers * ((layer_rows + 15) / 16);
+    } else {
+        latency = 0.69 + 0.18 * half + 0.016 * column;
+        issue = groups * (0.013 * (f64 ? 3.0 : 1.0) + 0.015 * slow * half) + 0.021 * column_groups;
+    }
+    // frames that the device holds: wavefronts of a frame, wavefronts and LDS of a CU (workgroup_threads)
+    constexpr double kCus = 256.0;
     const int waves = layered ? (layer_rows <= 16 ? 2 : layer_rows <= 32 ? 3 : 8) : groups <= 12 ? 4 : 8;
     const int cu_waves = f64 ? 8 : ms != layered ? 24 : 16;
     const size_t slots = fused::lds_bytes(c->n, c->fused.slot_words, tsize);
     const size_t lds = layered || slots > limit ? fused::lds_bytes(c->n, c->E, tsize) : slots;
-    const double held = 256.0 * std::max<double>(1, std::min<double>(cu_waves / waves, static_cast<double>(limit / lds)));
-    if (j.frames <= held)
-        return true;
-
-    const double frames = j.frames, ts = static_cast<double>(tsize), E = static_cast<double>(c->E), n = c->n;
-    // early stop: half the iterations, but every launch
-    const double iters = (j.flags & LDPC_EARLY_STOP) ? 0.5 * j.max_iter : j.max_iter;
-    // Streaming: launches of 3.1 us; 5.4 TB/s (FP64 sum-product: 5 ps of arithmetic per
-    // edge); 6.5 values per variable in and out; a column's chain of loads.
-    double launches = 2.0 + 2.0 * j.max_iter;
-    if (layered)
-        launches = 2.0 + static_cast<double>(j.max_iter) * (layers + ((j.flags & LDPC_EARLY_STOP) ? 2 : 0));
-    const double bytes = ts * (layered ? 4.0 * E : 3.0 * E + 2.0 * n);
-    const double streaming = 3.1 * launches +
-                             frames * (iters * (f64 && !ms ? 5e-6 * E : bytes / 5.4e6) + 6.5 * ts * n / 5.4e6) +
-                             (layered ? 0.0 : 0.17 * iters * c->max_col_deg);
-    // Frame-resident: the draws, or a frame's iteration: its latency over the frames
-    // held, or the issue time of its groups.
-    const double half = (c->max_row_deg + 1) / 2, quarter = ((c->max_row_deg + 1) / 2 + 1) / 2;
-    double latency, issue;
-    if (layered) {
-        latency = layers * (0.30 + 0.14 * quarter);
-        issue = 9.4e-5 * quarter * layers * ((layer_rows + 15) / 16);
-    } else {
-        latency = 0.71 + 0.22 * half + 0.015 * c->max_col_deg;
-        issue = 8.8e-5 * groups * half;
-    }
-    const double resident = 7.0 + frames * std::max(0.0115, iters * std::max(latency / held, issue));
-    return 1.1 * resident <= streaming;
+    const double held = kCus * std::max<double>(1, std::min<double>(cu_waves / waves, static_cast<double>(limit / lds)));
+    const double frames = j.frames;
+    const double resident = frames <= held
+                                ? run * std::max(latency, std::ceil(frames / kCus) * issue)
+                                : frames * std::max(0.0115, run * std::max(latency / held, issue / kCus));
+    return 1.1 * (3.4 + resident) <= streaming;
 }
 
 }  // namespace

@@ -10,7 +10,7 @@
 // order, from the messages of the iteration before, so no variable launch has
 // to come first.  A column's sum is formed once per row that holds it, which
 // multiplies the reads of r by the mean column degree; the rule that picks
-// this path (few_frames_path) bounds that product.  The messages alternate
+// this path (few_frames_groups) bounds that product.  The messages alternate
 // between two buffers; nothing else passes from launch to launch.
 //
 // One wavefront is one check row of FW frames: lane k FW + f holds edge k of
@@ -75,7 +75,7 @@ __global__ __launch_bounds__(256) void k_few_ingest(const typename A::T *__restr
 }
 
 // Byte offset of frame f of item i in an array [items][W]: 24-bit factors and a
-// 32-bit product (few_frames_path bounds them).
+// 32-bit product (few_frames_groups bounds them).
 template <class T>
 __device__ __forceinline__ uint32_t frame_offset(uint32_t i, uint32_t W, uint32_t f)
 {
@@ -304,16 +304,16 @@ ldpc_status run_few(const ldpc_code_s *c, int32_t frames, int32_t max_iter, bool
 // and 252, 243 and 238; 9000 rows 406 and 375, 336 and 355; 18000 rows 716 and 778, 630 and
 // 749.  The bound on the reads keeps out codes whose dense columns would be summed by
 // very many rows (near it: a column of degree 2503, 19.3 and 3.3 to 17.5 ms).
-bool few_frames_path(const ldpc_code_s *c, bool f64, int32_t frames)
+int32_t few_frames_groups(const ldpc_code_s *c, bool f64, int32_t frames)
 {
     if (frames > kFewFrames || c->max_row_deg > 32)
-        return false;
+        return 0;
     const int32_t width = few_width(c->max_row_deg), groups = (frames + width - 1) / width;
     if (std::max<int64_t>(c->E, c->n) * groups * width >= 1 << 24)  // 24-bit factors, 32-bit byte offsets
-        return false;
+        return 0;
     const int32_t third = c->max_row_deg <= 16 ? 14000 : 6000;  // rows up to which FP32 takes three groups
     const int32_t most = f64 ? (c->m <= 20000 ? 4 : 3) : c->m <= third ? 3 : 2;
-    return groups <= most && c->column_reads * groups * width <= 1 << 26;
+    return groups <= most && c->column_reads * groups * width <= 1 << 26 ? groups : 0;
 }
 
 template <class A>

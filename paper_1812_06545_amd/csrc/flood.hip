@@ -348,7 +348,7 @@ ldpc_status decode_impl(const ldpc_code_s *c, int32_t frames, int32_t max_iter, 
     int32_t *done = cv.take<int32_t>(Fp + nchunk);  // per frame, then per chunk (flood_kernels.h)
     int32_t *unsat = cv.take<int32_t>(static_cast<size_t>(std::max(max_iter, 1)) * Fp);
 
-    if ((flags & LDPC_LAYERED) == 0 && few_frames_path(c, std::is_same<A, ArithF64>::value, frames))
+    if ((flags & LDPC_LAYERED) == 0 && few_frames_groups(c, std::is_same<A, ArithF64>::value, frames) != 0)
         return decode_few<A>(c, frames, max_iter, flags, llr, bits, iters, post, R, Lch, done, unsat, s,
                              static_cast<T>(ms_scale), static_cast<T>(ms_offset * A::kIn));
 

@@ -188,8 +188,9 @@ ldpc_status stream_decode(const ldpc_code_s *c, ldpc_dtype dt, int32_t frames, i
                           const void *llr, uint8_t *bits, int32_t *iters, void *posterior, void *ws,
                           hipStream_t stream, double ms_scale, double ms_offset);
 // Flooding of a few frames with one launch per iteration (few.hip), on the
-// streaming workspace; few_frames_path says whether it is the faster form.
-bool few_frames_path(const ldpc_code_s *c, bool f64, int32_t frames);
+// streaming workspace.  few_frames_groups: the groups of frames it would run, or 0
+// where the check and variable kernels are the faster form.
+int32_t few_frames_groups(const ldpc_code_s *c, bool f64, int32_t frames);
 template <class A>
 ldpc_status decode_few(const ldpc_code_s *c, int32_t frames, int32_t max_iter, uint32_t flags,
                        const typename A::T *llr, uint8_t *bits, int32_t *iters, typename A::T *post,

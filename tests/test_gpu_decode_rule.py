@@ -1,8 +1,8 @@
 """Which kernels ldpc_decode runs for codes that fit the frame-resident kernel.
 
-Frames beyond what the device holds at once go to the streaming kernels where
-those are the faster: very short codes, few iterations, layers of a few rows,
-columns of very high degree.  Each call's outputs must equal the
+Calls go to the streaming kernels where those are the faster: frames beyond what
+the device holds at once of very short codes, of few iterations, of layers of a
+few rows or with columns of very high degree; and a few frames of long codes.  Each call's outputs must equal the
 frame-resident kernel's, which ldpc_decode_batch runs for them, bit for bit
 (no tolerance: the same operations in the same order).  The calls on each side
 lie well off the line (factors of 1.4 to 15 between the two routes' times).
@@ -43,6 +43,11 @@ CALLS = {
     "minsum": (lambda: codes.qc_code(12, 24, 81, 3), 1999, 10, dict(rule="minsum", ms_scale=0.75), False),
     "dense_column": (lambda: codes.random_rows(3000, 4000, 3, 8, 5, dense_col=True), 4096, 3, {}, True),
     "dense_column_few": (lambda: codes.random_rows(3000, 4000, 3, 8, 5, dense_col=True), 64, 3, {}, False),
+    "long_one": (lambda: codes.random_rows(4500, 9000, 3, 7, 5), 1, 10, {}, True),
+    "long_few": (lambda: codes.random_rows(4500, 9000, 3, 7, 5), 16, 10, dict(early_stop=True), True),
+    "long_many": (lambda: codes.random_rows(4500, 9000, 3, 7, 5), 200, 10, {}, False),
+    "short_one": (lambda: codes.qc_code(12, 24, 27, 3), 1, 10, dict(early_stop=True), False),
+    "middle_one_f64": (lambda: codes.random_rows(1250, 2500, 3, 7, 5), 8, 10, {}, True),
     "throughput": (lambda: codes.qc_code(12, 24, 81, 3), 4096, 10, {}, False),
 }
 
@@ -52,7 +57,9 @@ CALLS = {
 def test_route(L, name, dtype):
     import torch
     make, frames, iters, options, streaming = CALLS[name]
-    if dtype == "f64" and (name.startswith("dense") or "iteration" in name):
+    if dtype == "f32" and name.endswith("f64"):
+        pytest.skip("the line lies elsewhere in FP32")
+    if dtype == "f64" and (name.startswith(("dense", "long")) or "iteration" in name):
         pytest.skip("the line lies elsewhere in FP64, or the code does not fit")
     code = make()
     h = L.Code.from_workload(code)
