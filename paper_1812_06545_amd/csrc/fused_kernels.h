@@ -939,7 +939,7 @@ inline ldpc_status launch_shape(const void *fn, size_t lds, int threads, int &pe
         int dev;
         size_t lds;
     };
-    constexpr int kShapes = 256, kLimits = 128;
+    constexpr int kShapes = 256, kLimits = 512;  // (38 kernels, on up to 13 devices)
     static std::mutex mu;
     static Shape shapes[kShapes];
     static Limit limits[kLimits];
