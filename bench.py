@@ -57,38 +57,45 @@ def parse():
 HBM_PEAK_GBS = 8000.0
 PROFILE_EVERY = 10  # timed steps per step whose launches are bracketed by HIP events
 
-# HBM bytes per check-kernel launch on this workload, from two rocprofv3
-# --pmc runs (FETCH_SIZE, WRITE_SIZE; reads scaled by 2.0 and writes by 1.0,
-# the ratios of true bytes to counter readings for the library's copy
-# kernel), averaged over one first-iteration and nine later launches.  Valid
-# only for the kernel source they were taken on (hash below); otherwise null.
-CHECK_TRAFFIC = {
-    "bytes_per_launch": 543.1e6,
-    "source_sha256": "a3106c90e407f8897c1385d47829ff15770e00aa0a419879e150a4f24eae300e",
-    "profile": "profiles/hbm_traffic_check_qc1944.md",
+# The headline's kernel, the frame-resident decoder, keeps its messages in LDS and
+# is bound by VALU issue.  Wavefront VALU instructions per launch on this workload,
+# from an SQ_INSTS_VALU counter run; valid only for the kernel source it was taken
+# on (hash below), otherwise null.  Issue peak: 1024 SIMDs x 2.4 GHz / 4 cycles per
+# wave64 instruction (the transcendentals among them hold their SIMD longer, so
+# the fraction understates the issue load).
+FUSED_VALU = {
+    "insts_per_launch": 4.122e8,
+    "source_sha256": "bc146410cef80b2e26ccd9334e02031a0d72132a43e17e7561869f14b3b797af",
+    "profile": "profiles/fused_qc1944_batch.md",
 }
-CHECK_SOURCES = ("flood_kernels.h", "spa_math.h", "check_f32_d24.hip")
-
-# The check kernel is co-limited by VALU issue.  Wavefront VALU instructions
-# per launch on this workload, from the SQ_INSTS_VALU counter run (same
-# source hash, same averaging over one first-iteration and nine later
-# launches).  Issue peak: 1024 SIMDs x 2.4 GHz / 4 cycles per wave64
-# instruction (4 of the instructions per edge and chunk are transcendentals,
-# which hold their SIMD longer, so this fraction understates the issue load).
-CHECK_VALU = {
-    "insts_per_launch": 36.21e6,
-    "source_sha256": CHECK_TRAFFIC["source_sha256"],
-    "profile": "profiles/check_variable_qc1944_plain.md",
-}
+FUSED_SOURCES = ("fused_kernels.h", "spa_math.h", "fused_f32_d24.hip")
 VALU_ISSUE_PEAK = 1024 * 2.4e9 / 4  # wavefront instructions per second
 
 
-def check_source_hash():
+def fused_source_hash():
     import hashlib
     here = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_1812_06545_amd", "csrc")
     lines = "".join(f"{hashlib.sha256(open(os.path.join(here, f), 'rb').read()).hexdigest()}  "
-                    f"paper_1812_06545_amd/csrc/{f}\n" for f in CHECK_SOURCES)
+                    f"paper_1812_06545_amd/csrc/{f}\n" for f in FUSED_SOURCES)
     return hashlib.sha256(lines.encode()).hexdigest()
+
+
+def roofline_of(name, avg_ms, bytes_per_launch, fused_hash, layered=False):
+    """The roofline entry of the dominant kernel: the streaming kernels ("check",
+    "layer") against HBM, on their algorithmic bytes; the frame-resident kernel
+    ("fused") against VALU issue, on its counted instructions (null for other sources
+    or the layered schedule, on which they were not counted).  avg_ms None: not timed."""
+    gbs = bytes_per_launch / (avg_ms * 1e-3) / 1e9 if avg_ms else None
+    hbm = {"achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS if gbs else None,
+           "bytes_per_launch": bytes_per_launch}
+    if name != "fused":
+        return {"bound": "hbm", "kernel": name, **hbm, "traffic": None}
+    counted = avg_ms and not layered and fused_hash == FUSED_VALU["source_sha256"]
+    rate = FUSED_VALU["insts_per_launch"] / (avg_ms * 1e-3) if counted else None
+    return {"bound": "valu", "kernel": name, "achieved": rate / 1e9 if rate else None, "peak": VALU_ISSUE_PEAK / 1e9,
+            "unit": "G wavefront instructions/s", "frac": rate / VALU_ISSUE_PEAK if rate else None,
+            "insts_per_launch": FUSED_VALU["insts_per_launch"] if rate else None,
+            "profile": FUSED_VALU["profile"] if rate else None, "traffic": None, "hbm": hbm}
 
 
 def main():
@@ -197,21 +204,10 @@ def main():
         # frame-resident kernel: reads the channel LLRs and writes bits and the
         # posterior once per frame; messages live in LDS
         bytes_per_launch = F * (4 * n + n + 4 * n + 4)
-    avg_ms = kms / max(kcount, 1)
-    achieved = bytes_per_launch / (avg_ms * 1e-3) / 1e9 if kcount else None
-    traffic = None
-    if name == "check" and check_source_hash() == CHECK_TRAFFIC["source_sha256"]:
-        traffic = CHECK_TRAFFIC["bytes_per_launch"]
-    roofline = {"bound": "hbm", "kernel": name, "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                "frac": (achieved / HBM_PEAK_GBS) if achieved else None, "traffic": traffic,
-                "traffic_unit": "bytes per launch", "traffic_profile": CHECK_TRAFFIC["profile"] if traffic else None,
-                "launch_ms": avg_ms, "launches": kcount, "bytes_per_launch": bytes_per_launch,
-                "timed_launches": f"HIP events on every launch of every {args.profile_every}th timed step"}
-    if name == "check" and kcount and check_source_hash() == CHECK_VALU["source_sha256"]:
-        insts = CHECK_VALU["insts_per_launch"]
-        roofline["valu"] = {"achieved": insts / (avg_ms * 1e-3) / 1e9, "peak": VALU_ISSUE_PEAK / 1e9,
-                            "unit": "G wavefront instructions/s", "frac": insts / (avg_ms * 1e-3) / VALU_ISSUE_PEAK,
-                            "insts_per_launch": insts, "profile": CHECK_VALU["profile"]}
+    avg_ms = kms / kcount if kcount else None
+    roofline = roofline_of(name, avg_ms, bytes_per_launch, fused_source_hash(), args.path == "layered")
+    roofline.update({"launch_ms": avg_ms, "launches": kcount,
+                     "timed_launches": f"HIP events on every launch of every {args.profile_every}th timed step"})
     # the whole step against its algorithmic floor (every frame runs T iterations)
     roofline["step_floor"] = floor_frac(E, n, 4, F * T, ms_per_step)
     kernels = {k: {"ms_total": v[0], "launches": v[1]} for k, v in prof.items() if v[1]}
@@ -226,8 +222,8 @@ def main():
     mstream = mstream_run() if rest else None
 
     copy = copy_probe(args.copy_probe_mb) if args.copy_probe_mb > 0 else None
-    if copy and achieved:
-        roofline["frac_of_copy"] = achieved / copy["gbs"]
+    if copy and roofline["bound"] == "hbm" and roofline["achieved"]:
+        roofline["frac_of_copy"] = roofline["achieved"] / copy["gbs"]
 
     serving = serve_run(args.serve_seconds, args.serve_rate, warmup_s=args.serve_warmup) \
         if args.serve_seconds > 0 else None
@@ -270,11 +266,12 @@ def main():
 
 
 def floor_frac(E, n, tsize, frame_iters, ms):
-    """Fraction of HBM peak that the whole step's algorithmic floor traffic
-    would need: per frame-iteration one stored message per edge read and
+    """Fraction of HBM peak that the whole step's floor traffic in the streaming
+    form would need: per frame-iteration one stored message per edge read and
     written once (2 tsize E) and one posterior per variable (tsize n),
     summed over the iterations each frame actually ran, divided by the
-    measured time."""
+    measured time.  A yardstick across paths: the frame-resident kernel keeps
+    these bytes in LDS."""
     floor_bytes = frame_iters * (2 * tsize * E + tsize * n)
     gbs = floor_bytes / (ms * 1e-3) / 1e9
     return {"floor_bytes": floor_bytes, "achieved_gbs": gbs, "frac": gbs / HBM_PEAK_GBS}
@@ -427,11 +424,9 @@ def layered_workloads(steps):
     chain = copy_chain(per_decode / (10 * layers), 10 * layers) if kcount else None
     out["qc1944_2dB_10passes"] = {
         "plain_ms": ms, "plain_mbps": F * n / (ms * 1e-3) / 1e6, "layers": layers,
-        "layer_kernel": {"launches": kcount, "avg_us": kms * 1e3 / max(kcount, 1),
-                         "bytes_per_decode": per_decode, "achieved_gbs": achieved,
-                         "frac_of_peak": achieved / HBM_PEAK_GBS if achieved else None,
-                         "copy_chain": chain,
-                         "frac_of_copy_chain": achieved / chain["gbs"] if chain and achieved else None},
+        "layer_kernel": {"launches": kcount, "avg_us": kms * 1e3 / kcount, "bytes_per_decode": per_decode,
+                         "achieved_gbs": achieved, "frac_of_peak": achieved / HBM_PEAK_GBS, "copy_chain": chain,
+                         "frac_of_copy_chain": achieved / chain["gbs"]} if kcount else None,
         "batch_ms": fused_ms, "batch_mbps": F * n / (fused_ms * 1e-3) / 1e6}
 
     def converge(batch, dtype, T, reps):
@@ -489,8 +484,8 @@ def minsum_workloads(steps):
     lay = _time_ms(plain(layered=True), steps)
     out["qc1944_2dB_10it_nms0.75"] = {
         "plain_ms": ms, "plain_mbps": F * n / (ms * 1e-3) / 1e6,
-        "check_kernel": {"avg_us": kms * 1e3 / max(kcount, 1), "bytes_per_launch": bytes_per_launch,
-                         "achieved_gbs": achieved, "frac_of_peak": achieved / HBM_PEAK_GBS if achieved else None},
+        "check_kernel": {"avg_us": kms * 1e3 / kcount, "bytes_per_launch": bytes_per_launch,
+                         "achieved_gbs": achieved, "frac_of_peak": achieved / HBM_PEAK_GBS} if kcount else None,
         "batch_ms": fused, "batch_mbps": F * n / (fused * 1e-3) / 1e6,
         "layered_plain_ms": lay, "layered_plain_mbps": F * n / (lay * 1e-3) / 1e6}
     hi = torch.from_numpy(configs.qc1944(3.5).llr).cuda()

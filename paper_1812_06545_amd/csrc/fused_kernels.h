@@ -1036,8 +1036,8 @@ inline size_t batch_table_lds_bytes(const Batch &b, size_t tsize, uint32_t &tabl
 // wavefronts 325 and 299), and with early stop the wider always, which ends the
 // last pass's long frames sooner.  Layered frames: a layer's rows in one round, at
 // most 8 wavefronts where a CU holds two frames (4000 frames of qc n = 1944: 4,
-// 6, 8, 16 wavefronts 2239, 1638, 1633, 2603), and one to spare for the layers
-// of two wavefronts or less (n = 648: 1, 2, 3, 8 wavefronts 753, 481, 475, 800).
+// 6, 7, 8 wavefronts 2210, 1651, 1651, 1517), and one to spare for the layers of two
+// wavefronts or less (n = 648: 1, 2, 3, 6 wavefronts 723, 489, 492, 796).
 template <class K>
 ldpc_status workgroup_threads(K kern, const Batch &b, size_t tsize, size_t lds, int max_threads, int &threads)
 {
