@@ -672,35 +672,46 @@ __device__ __forceinline__ int32_t decode_frame_layered(const Code &c, const Job
     // Whether some row is unsatisfied by the decision [L < 0], from the
     // flooding table.  A wavefront stops at its first group of 32 rows holding
     // one (the answer is then known; in most passes that is the first group).
-    // Alone on its CU (LT), a wavefront keeps that group's addresses in
-    // registers (24 frames of qc n = 1296, rate 2/3: 84.5 us per call without and
-    // 82.3 with); where frames share a CU, holding 8 to 16 registers through
-    // every layer costs resident wavefronts (kFusedWavesPerEU).
+    // That group's addresses are loaded at once; alone on its CU (LT), a wavefront
+    // keeps them in registers from pass to pass (24 frames of qc n = 1296, rate
+    // 2/3: 84.5 us per call without and 82.3 with), where frames share a CU, holding
+    // 8 to 16 registers through every layer would cost resident wavefronts
+    // (kFusedWavesPerEU).
     const bool es = (job.flags & LDPC_EARLY_STOP) != 0;
-    constexpr int kFirstQuads = LT ? quads(DB / 2) : 0;
-    Quad first_quads[kFirstQuads + 1];
-    int first_slots = 0;
-    if (LT && es && wave < c.row_groups) {
-        first_slots = c.row_grp[2 * wave] >> 16;
-        const Table<LT> tab = row_tab + c.row_grp[2 * wave + 1] * 64;
+    constexpr int kFirstQuads = quads(DB / 2);
+    struct First {
+        Quad quad[kFirstQuads];
+        int slots = 0;
+    };
+    auto load_first = [&]() {
+        First f;
+        if (wave < c.row_groups) {
+            f.slots = c.row_grp[2 * wave] >> 16;
+            const Table<LT> tab = row_tab + c.row_grp[2 * wave + 1] * 64;
 #pragma unroll
-        for (int i = 0; i < kFirstQuads; ++i)
-            if (4 * i < first_slots)
-                first_quads[i] = tab[i * 64];
-    }
+            for (int i = 0; i < kFirstQuads; ++i)
+                if (4 * i < f.slots)
+                    f.quad[i] = tab[i * 64];
+        }
+        return f;
+    };
+    First kept;
+    if (LT && es)
+        kept = load_first();
     auto parity_of = [&](const Quad &q, uint64_t &par) {
 #pragma unroll
         for (int k = 0; k < 4; ++k)
             par ^= __ballot(lds_ld<T>(static_cast<uint32_t>(q[k]) * static_cast<uint32_t>(sizeof(T) / 4)) < T(0));
     };
     auto unsatisfied = [&]() -> int32_t {
+        const First first_group = LT ? kept : load_first();
         uint64_t par = 0;
 #pragma unroll
         for (int i = 0; i < kFirstQuads; ++i)
-            if (4 * i < first_slots)
-                parity_of(first_quads[i], par);
+            if (4 * i < first_group.slots)
+                parity_of(first_group.quad[i], par);
         bool odd = some_odd(par);
-        for (int g = LT ? wave + nwaves : wave; g < c.row_groups && !odd; g += nwaves) {
+        for (int g = wave + nwaves; g < c.row_groups && !odd; g += nwaves) {
             const int32_t w = c.row_grp[2 * g], first = c.row_grp[2 * g + 1];
             const Table<LT> tab = row_tab + first * 64;
             par = 0;
@@ -846,8 +857,8 @@ __device__ __forceinline__ int32_t next_item(const uint32_t *counter, uint32_t d
 // rows longer than 24; both spill one pair, once per frame).  us per call of 6
 // passes, 4000 frames of qc n = 1584 at rates 2/3, 3/4 and 5/6 with 4 and 6
 // wavefronts per SIMD (and 8, with 61 registers and the terms parked in LDS): 588
-// and 455 (511), 440 and 349 (388), 303 and 241 (275); n = 648 at rate 1/2 358 and
-// 301 (545).
+// and 460 (511), 440 and 349 (388), 303 and 241 (275); n = 648 at rate 1/2 358 and
+// 303 (545).
 template <class A, int DB, Instance INST, bool LT>
 constexpr int kFusedWavesPerEU =
     !std::is_same<A, ArithF32>::value ? 2 : INST == kLayered && !LT ? (DB <= 24 ? 6 : 5) : 4;
