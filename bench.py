@@ -65,7 +65,7 @@ PROFILE_EVERY = 10  # timed steps per step whose launches are bracketed by HIP e
 # the fraction understates the issue load).
 FUSED_VALU = {
     "insts_per_launch": 4.122e8,
-    "source_sha256": "bc146410cef80b2e26ccd9334e02031a0d72132a43e17e7561869f14b3b797af",
+    "source_sha256": "8ad040bf692a8f9067fea9344ca5a9438118e3333bf9a221d71825c63c8975a0",
     "profile": "profiles/fused_qc1944_batch.md",
 }
 FUSED_SOURCES = ("fused_kernels.h", "spa_math.h", "fused_f32_d24.hip")
