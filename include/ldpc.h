@@ -440,11 +440,11 @@ ldpc_status ldpc_batch_job_threads(const ldpc_job *jobs, int32_t njobs, ldpc_dty
  * jobs of that code and that many frames); then the whole batch with these
  * sizes and with every size left to the launch, alternating, keeping the
  * sizes only if the whole batch is faster with them (else 512 is recorded for
- * each code); then the whole batch with one
- * frame per workgroup and, where some job can use it, two
- * (ldpc_batch_set_frames_per_group), recording the faster for this batch
- * shape (the codes, frame counts rounded up to a power of two, iteration
- * caps, flags, dtype).  Every candidate's outputs must be bit-identical to
+ * each code); then, where some job can use it, the whole batch with two
+ * frames per workgroup (ldpc_batch_set_frames_per_group) and with one,
+ * alternating, recording two for this batch shape (the codes, frame counts
+ * rounded up to a power of two, iteration caps, flags, dtype) only if that is
+ * faster.  Every candidate's outputs must be bit-identical to
  * the first run's; each is timed with HIP events (3 runs after a warm-up).
  * Blocks until done.  *best_threads and *best_ms (may be NULL) receive the
  * first fused job's workgroup size and the batch's time

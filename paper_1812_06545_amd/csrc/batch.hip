@@ -912,7 +912,9 @@ ldpc_status time_candidate(const ldpc_job *jobs, int32_t njobs, ldpc_dtype dtype
 // there.  The sizes stay only if the slowest run with them is faster than the
 // fastest without (12 codes, 16384 frames: sizes found alone, of three runs of the
 // tuner, 1.539, 1.556 and 1.419 ms, the launch's choice 1.463).  Last, per
-// batch shape: frames per workgroup 1, and 2 where some job can use it.
+// batch shape: two frames per workgroup where some job can use it, against one, by
+// the same comparison (here 1.479 against 1.467 ms; one timing of each, in this
+// order, took two now and then).
 // Every candidate's outputs must equal the first run's.
 extern "C" ldpc_status ldpc_autotune_batch(const ldpc_job *jobs, int32_t njobs, ldpc_dtype dtype, void *workspace,
                                            size_t workspace_bytes, void *stream, int32_t *best_threads,
@@ -957,6 +959,23 @@ try {
     }
     std::vector<char> ref, cur;
     ldpc_status rc = LDPC_OK;
+    // Five timings of the whole batch with set(true) and with set(false), in turn:
+    // whether the slowest with is faster than the fastest without.
+    const auto faster_in_turn = [&](const auto &set) {
+        constexpr int kRounds = 5;
+        double least = 0.0, most = 0.0;
+        for (int round = 0; round < kRounds && rc == LDPC_OK; ++round)
+            for (int with = 0; with < 2 && rc == LDPC_OK; ++with) {
+                set(with != 0);
+                double ms = 0.0;
+                rc = time_candidate(jobs, njobs, dtype, workspace, workspace_bytes, s, e0, e1, ref, cur, ms);
+                if (with)
+                    most = std::max(most, ms);
+                else
+                    least = round == 0 ? ms : std::min(least, ms);
+            }
+        return rc == LDPC_OK && most < least;
+    };
     // stage 1: workgroup size per code
     for (size_t c = 0; c < ckeys.size() && rc == LDPC_OK; ++c) {
         std::vector<char> cref;
@@ -1003,45 +1022,32 @@ try {
                 g_code_tuned[ckeys[c]] = t;
             }
         };
-        constexpr int kRounds = 5;
-        double least[2] = {0.0, 0.0}, most[2] = {0.0, 0.0};  // of the runs without and with sizes
-        for (int round = 0; any && round < kRounds && rc == LDPC_OK; ++round)
-            for (int sized = 0; sized < 2 && rc == LDPC_OK; ++sized) {
-                set(sized != 0);
-                double ms = 0.0;
-                rc = time_candidate(jobs, njobs, dtype, workspace, workspace_bytes, s, e0, e1, ref, cur, ms);
-                least[sized] = round == 0 ? ms : std::min(least[sized], ms);
-                most[sized] = std::max(most[sized], ms);
-            }
         if (any)
-            set(most[1] < least[0]);
+            set(faster_in_turn(set));
     }
     // stage 3: frames per workgroup for the whole batch
     LaunchCfg best_cfg{default_threads, 1};
     double best_t = 0.0;
-    bool have = false;
-    for (int fpw = 1; fpw <= fpw_max && rc == LDPC_OK; ++fpw) {
-        const LaunchCfg cand{default_threads, fpw};
-        {
+    if (rc == LDPC_OK) {
+        const auto set = [&](bool pairs) {
             std::lock_guard<std::mutex> lk(g_mu);
-            g_tuned[key] = Tuned{cand, 0.0};
-        }
-        double ms = 0.0;
-        rc = time_candidate(jobs, njobs, dtype, workspace, workspace_bytes, s, e0, e1, ref, cur, ms);
-        if (rc == LDPC_OK && (!have || ms < best_t)) {
-            best_cfg = cand;
-            best_t = ms;
-            have = true;
-        }
+            g_tuned[key] = Tuned{LaunchCfg{default_threads, pairs ? 2 : 1}, 0.0};
+        };
+        set(false);
+        if (fpw_max == 2)
+            best_cfg.fpw = faster_in_turn(set) ? 2 : 1;
+        set(best_cfg.fpw == 2);
+        if (rc == LDPC_OK)
+            rc = time_candidate(jobs, njobs, dtype, workspace, workspace_bytes, s, e0, e1, ref, cur, best_t);
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    if (rc != LDPC_OK || !have) {
+    if (rc != LDPC_OK) {
         std::lock_guard<std::mutex> lk(g_mu);
         g_tuned.erase(key);
         for (const uint64_t ck : ckeys)
             g_code_tuned.erase(ck);
-        return rc != LDPC_OK ? rc : LDPC_EDEVICE;
+        return rc;
     }
     {
         std::lock_guard<std::mutex> lk(g_mu);

@@ -106,3 +106,20 @@ def test_sizes_of_a_large_batch_leave_few_frames_alone(L, tmp_path):
     assert L.ldpc_tuning_load(str(path))[0] == L.LDPC_OK
     assert L.ldpc_batch_job_threads([many.c_struct()], torch.float32) == [64]
     assert L.ldpc_batch_job_threads([few.c_struct()], torch.float32) == [512]
+
+
+def test_pairs_of_frames_are_taken_only_where_they_gain(L):
+    """Two frames per workgroup take the twelve-code mix 0.8% longer than one; runs
+    of one configuration differ by 0.2% once the clocks are up.  The tuner takes one
+    each time."""
+    import torch
+    mix = configs.qc_mix()
+    jobs = [L.Job(L.Code.from_workload(m.code), torch.from_numpy(m.llr).cuda(), 10, early_stop=True) for m in mix]
+    cj = [j.c_struct() for j in jobs]
+    for _ in range(3):
+        L.ldpc_tuning_clear()
+        L.autotune_batch(jobs)
+        cfg = L.ldpc_batch_launch_config(cj, torch.float32)
+        print(f"[gpu] mix: {cfg}", flush=True)
+        assert cfg["tuned"] and cfg["frames_per_group"] == 1
+    L.ldpc_tuning_clear()
