@@ -364,8 +364,12 @@ def extra_workloads(only=None):
             L.ldpc_autotune_batch(cj, dtype, bws, bw)
             chosen = L.ldpc_batch_launch_config(cj, dtype)
             per_job = L.ldpc_batch_job_threads(cj, dtype)
+            for _ in range(10):  # making a tuning or a plan leaves the device idle and the clocks fall
+                batched()
             tt = _time_ms(batched, reps)
             plan = L.Plan(jobs)
+            for _ in range(10):
+                plan.launch()
             tg = _time_ms(plan.launch, reps)
             plan.close()
             L.ldpc_tuning_clear()  # later workloads are measured with the defaults
